@@ -121,10 +121,16 @@ def _samples(case, seed):
     n_change = torch.randint(1, most + 1, (S, 1), device="cuda", generator=g)
     at = 1 + (torch.rand((S, most), device="cuda", generator=g, dtype=torch.float64) * (Kd[:, None] - 1)).long()
     at = torch.where(torch.arange(most, device="cuda")[None, :] < n_change, at, 1 << 30).sort(1).values
-    lo, hi = (1.05, 1.2) if noise == "hard" else (1.5, 2.7)
-    ratio = lo + (hi - lo) * torch.rand((S, most), device="cuda", generator=g)
-    first = 120.0 * (0.9 + 0.2 * torch.rand((S, 1), device="cuda", generator=g))
-    level = torch.cat([first, first * torch.cumprod(ratio, 1)], 1)
+    # "hard": adjacent levels close together; otherwise rising steps of the load latencies of a GPU's memory elements
+    if noise == "hard":
+        first = 120.0 * (0.9 + 0.2 * torch.rand((S, 1), device="cuda", generator=g))
+        ratio = 1.05 + 0.15 * torch.rand((S, most), device="cuda", generator=g)
+        level = torch.cat([first, first * torch.cumprod(ratio, 1)], 1)
+    else:
+        ladder = torch.tensor([120.0, 300.0, 550.0, 850.0, 1300.0, 1300.0, 1300.0, 1300.0, 1300.0], device="cuda")
+        step0 = (torch.rand((S, 1), device="cuda", generator=g) * (5 - n_change)).long()
+        level = ladder[step0 + torch.arange(most + 1, device="cuda")[None, :]]
+        level = level * (0.9 + 0.2 * torch.rand((S, most + 1), device="cuda", generator=g))
     sid = torch.repeat_interleave(torch.arange(S, device="cuda"), Kd)
     start = torch.cumsum(Kd, 0) - Kd
     row = torch.arange(len(sid), device="cuda") - start[sid]
