@@ -19,7 +19,8 @@ struct LearnWs {
   uint64_t* s1;     // [num_series * SR] (row slot of series s: s * SR + 2 + i)
   uint64_t* s2lo;
   uint32_t* s2hi;
-  uint32_t* smin;   // [num_series]
+  uint32_t* smin;   // [num_series]: written by the pack step
+  uint32_t* cmin;   // [num_series * C]: minima of the feature pass's row chunks
   uint32_t* K;      // [num_series]: K when the series was valid, 0 otherwise
 };
 
@@ -42,56 +43,32 @@ struct FeatStage {
   uint32_t s2hi[S];
 };
 
-// First step, workgroup t of the launch of row class NB (rows in 1, 2 or 4
-// load batches held in registers, kStreamed, or kGrouped) takes the t-th
-// series of that class in the plan's order (the NB = 1 launch also marks
-// malformed series with K = 0). One wave per row (four per step for kGrouped);
-// wave w of W takes rows [w B, (w + 1) B) with B = ceil(K / W). Writes per row
+// The calling wave's rows `sp` of one series of row class NB. Writes per row
 // the deciles (as raw samples, at row slot s * SR + 2 + i of feat_ws) and the
-// refine workspace's moments, and per series its minimum and K.
-template <int NB, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(feat_waves_per_eu(NB)))) void features_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
-                                                      const ks_desc* __restrict__ desc, uint32_t num_series,
-                                                      uint32_t max_K, uint32_t SR, LearnWs lw,
-                                                      float* __restrict__ feat_ws,
-                                                      const uint32_t* __restrict__ plan) {
-  constexpr int W = NT / kWave;
-  __shared__ RowLds sel[W];
+// refine workspace's moments; returns the least of its rows' minima.
+template <int NB, int W>
+__device__ __forceinline__ uint32_t feature_rows(RowLds* sel, CoopLds<W>& co, void* stage,
+                                                 const uint32_t* __restrict__ samples, const ks_desc& d, uint32_t c,
+                                                 uint32_t C, uint32_t w, uint32_t lane, uint64_t slot, LearnWs lw,
+                                                 float* __restrict__ feat_ws) {
   constexpr uint32_t kFeatStage = feat_stage_rows(NB);
   static_assert(kFeatStage <= (uint32_t)kWave, "a flush writes one row's moments per lane");
-  __shared__ FeatStage<kFeatStage> stage[W];
-  __shared__ uint32_t red[W];
-  const uint32_t ci = feat_class_index(NB);
-  if (blockIdx.x >= plan[num_series + kFeatClasses + ci]) return;
-  const uint32_t s = plan[plan[num_series + ci] + blockIdx.x];
-  const ks_desc d = desc[s];
-  const uint32_t tid = threadIdx.x, lane = lane_id();
-  const uint32_t w = wave_id();
-  const bool bad = check_desc(d, num_samples, max_K) || d.N > KS_FEATURE_MAX_N;
-  if ((bad ? 1u : feat_batches(d.N)) != (uint32_t)NB) return;
-  if (bad) {  // the pack step zeroes its network input rows
-    if (tid == 0) lw.K[s] = 0;
-    return;
-  }
-  const uint32_t K = d.K, N = d.N;
-  const uint64_t slot = (uint64_t)s * SR + 2;
-  RowLds& L = sel[w];
-  FeatStage<kFeatStage>& st = stage[w];
-  const uint32_t B = (K + W - 1) / W;
-  const uint32_t begin = min(w * B, K), end = min(begin + B, K);
+  const RowSpan sp = row_span<NB, W>(d.K, c, C, w);
+  FeatStage<kFeatStage>& st = reinterpret_cast<FeatStage<kFeatStage>*>(stage)[w];
   uint32_t gmin = 0xffffffffu;
   // row i's results; its deciles on lanes first .. first + 8
-  auto emit = [&](uint32_t i, uint64_t s1, uint64_t s2, uint32_t s2h, uint32_t rmin, uint32_t dec, uint32_t first) {
-    const uint32_t j = (i - begin) % kFeatStage;
+  select_rows<NB, DecileRanks, W>(sel, co, samples, d.offset, d.N, sp, w, lane,
+                                  [&](uint32_t i, const RowOut& o, uint32_t first) {
+    const uint32_t j = (i - sp.begin) % kFeatStage;
     if (lane == 0) {
-      st.s1[j] = s1;
-      st.s2lo[j] = s2;
-      st.s2hi[j] = s2h;
+      st.s1[j] = o.s1;
+      st.s2lo[j] = o.s2;
+      st.s2hi[j] = o.s2h;
     }
-    gmin = min(gmin, rmin);
+    gmin = min(gmin, o.rmin);
     // feature numerators x - m need the series minimum: keep x itself
-    if (lane - first < 9u) st.dec[j * 9 + lane - first] = dec;
-    if (j + 1 == kFeatStage || i + 1 == end) {  // flush rows i - j .. i
+    if (lane - first < 9u) st.dec[j * 9 + lane - first] = o.sel;
+    if (j + 1 == kFeatStage || i + 1 == sp.end) {  // flush rows i - j .. i
       wave_lds_sync();
       const uint64_t r0 = slot + i - j;
       for (uint32_t q = lane; q < (j + 1) * 9; q += kWave)
@@ -103,42 +80,56 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(feat_waves_p
       }
       wave_lds_sync();
     }
-  };
-  if constexpr (NB == (int)kStreamed) {
-    select_rows_long<DecileRanks>(L, samples, d.offset, N, end, begin, 1u, lane,
-                                  [&](uint32_t i, const RowOut& o) { emit(i, o.s1, o.s2, o.s2h, o.rmin, o.sel, 0u); });
-  } else if constexpr (NB == (int)kGrouped) {
-    select_rows_grouped<DecileRanks>(L, samples, d.offset, N, begin, end, lane,
-                                     [&](uint32_t i, const RowOut& o, uint32_t first) {
-                                       emit(i, o.s1, o.s2, o.s2h, o.rmin, o.sel, first);
-                                     });
-  } else {
-    Batch cur[NB];
-    RowGeo g;
-    if (begin < end) g = load_row<NB>(cur, samples, d.offset + (uint64_t)begin * N, N, lane);
-    uint32_t p = 0;  // window base from the previous row (none for the first)
-    for (uint32_t i = begin; i < end; ++i) {
-      uint64_t s1, s2;
-      uint32_t s2h;
-      RowScan rs;
-      const bool based = i > begin && row_scan_based<NB>(L, cur, g, N, p, s1, s2, s2h, rs, lane);
-      if (!based) rs = row_scan<NB>(L, cur, g, N, s1, s2, s2h, lane);
-      // the next row's loads are in flight while this row's order statistics are found
-      const RowGeo gi = g;
-      if (i + 1 < end) g = load_row<NB>(cur, samples, d.offset + (uint64_t)(i + 1) * N, N, lane);
-      const uint32_t sel = based ? select_from_window<DecileRanks>(L, samples, gi, p, rs.rmax, N, lane)
-                                 : row_select<NB, DecileRanks>(L, samples, gi, rs, N, lane);
-      p = rs.rmin > kRowMargin ? rs.rmin - kRowMargin : 0u;
-      emit(i, s1, s2, s2h, rs.rmin, sel, 0u);
-    }
+  });
+  return gmin;
+}
+
+// First step: one launch over the row classes of MASK, one workgroup per
+// (series, chunk of its rows; row_pass_chunks), the series in the plan's order
+// (descriptor order without one). Malformed series (class 1's) are marked with
+// K = 0. Each chunk leaves its minimum in cmin; chunk 0 writes the series' K.
+template <uint32_t MASK>
+__global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves_per_eu(row_pass_waves(MASK)))) void features_kernel(
+    const uint32_t* __restrict__ samples, uint64_t num_samples, const ks_desc* __restrict__ desc, uint32_t num_series,
+    uint32_t max_K, uint32_t SR, LearnWs lw, float* __restrict__ feat_ws, const uint32_t* __restrict__ plan,
+    uint32_t C) {
+  constexpr int W = row_pass_threads(MASK) / kWave;
+  constexpr uint32_t kStageMax = MASK == kRowsOne ? 16u : 64u;
+  __shared__ RowLds sel[W];
+  __shared__ FeatStage<kStageMax> stage[W];
+  __shared__ CoopLds<W> co;
+  __shared__ uint32_t red[W];
+  const uint32_t t = blockIdx.x / C, c = blockIdx.x - t * C;
+  const uint32_t s = row_pass_series<MASK>(plan, num_series, t);
+  if (s >= num_series) return;
+  const ks_desc d = desc[s];
+  const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  const bool bad = check_desc(d, num_samples, max_K) || d.N > KS_FEATURE_MAX_N;
+  const uint32_t nb = bad ? 1u : feat_batches(d.N);
+  if (!((MASK >> feat_class_index(nb)) & 1u)) return;
+  if (bad) {  // the pack step zeroes its network input rows
+    if (tid == 0 && c == 0) lw.K[s] = 0;
+    return;
   }
+  uint32_t gmin = 0xffffffffu;
+  auto rows = [&](auto tag) {
+    constexpr int NB = decltype(tag)::value;
+    if constexpr ((MASK >> feat_class_index(NB)) & 1u)
+      if (nb == (uint32_t)NB)
+        gmin = feature_rows<NB, W>(sel, co, stage, samples, d, c, C, w, lane, (uint64_t)s * SR + 2, lw, feat_ws);
+  };
+  rows(std::integral_constant<int, 1>{});
+  rows(std::integral_constant<int, 2>{});
+  rows(std::integral_constant<int, 4>{});
+  rows(std::integral_constant<int, (int)kStreamed>{});
+  rows(std::integral_constant<int, (int)kGrouped>{});
   if (lane == 0) red[w] = gmin;
   __syncthreads();
   if (tid == 0) {
 #pragma unroll
     for (int u = 0; u < W; ++u) gmin = min(gmin, red[u]);
-    lw.smin[s] = gmin;
-    lw.K[s] = K;
+    lw.cmin[(uint64_t)s * C + c] = gmin;  // 0xffffffff for a chunk past the series' rows
+    if (c == 0) lw.K[s] = d.K;
   }
 }
 
@@ -156,8 +147,10 @@ template <int NT>
 __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restrict__ desc, uint32_t num_series,
                                                           float* __restrict__ feat_out, uint64_t feat_rows,
                                                           uint16_t* __restrict__ x0, uint32_t SR, LearnWs lw,
-                                                          float* __restrict__ feat_ws) {
+                                                          float* __restrict__ feat_ws, uint32_t C) {
+  static_assert(kRowPassChunks <= (uint32_t)NT, "one thread per chunk minimum");
   __shared__ __align__(16) uint16_t bf[NT * 16];
+  __shared__ uint32_t red[NT / kWave];
   const uint32_t s = blockIdx.x;
   if (s >= num_series) return;
   const uint32_t tid = threadIdx.x;
@@ -171,7 +164,8 @@ __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restr
   const uint32_t lo = r0 < 2u ? 2u - r0 : 0u;
   const uint32_t hi = K + 2u > r0 ? (K + 2u - r0 < nr ? K + 2u - r0 : nr) : 0u;
   if (lo < hi) {
-    const uint32_t gmin = lw.smin[s];
+    const uint32_t gmin = block_min_u32<NT>(tid < C ? lw.cmin[(uint64_t)s * C + tid] : 0xffffffffu, red);
+    if (blockIdx.y == 0 && tid == 0) lw.smin[s] = gmin;
     const double denom = (double)(gmin > 1 ? gmin : 1u);
     const ks_desc d = desc[s];
     const bool to_user = feat_out && d.aux_offset <= feat_rows && K <= feat_rows - d.aux_offset;

@@ -20,7 +20,7 @@ namespace C = ks::cnn;
 namespace ks_host {
 
 void free_learn(LearnBuffers& b) {
-  void* ptrs[] = {b.s1, b.s2lo, b.s2hi, b.smin, b.K, b.feat, b.x0, b.act[0], b.act[1], b.act[2], b.logits,
+  void* ptrs[] = {b.s1, b.s2lo, b.s2hi, b.smin, b.cmin, b.K, b.feat, b.x0, b.act[0], b.act[1], b.act[2], b.logits,
                   b.dy16, b.dy16f, b.dy[0], b.dy[1], b.dy[2], b.dyf[0], b.dyf[1], b.dyf[2], b.part, b.grad[0], b.grad[1],
                   b.grad[2], b.grad[3], b.nsig};
   for (void* p : ptrs) (void)hipFree(p);
@@ -52,7 +52,8 @@ int ensure_learn(ks_ctx* c, uint64_t rows, uint64_t series, bool train) {
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_learn(b);
-  bool ok = alloc(b.s1, R) && alloc(b.s2lo, R) && alloc(b.s2hi, R) && alloc(b.smin, S) && alloc(b.K, S) &&
+  bool ok = alloc(b.s1, R) && alloc(b.s2lo, R) && alloc(b.s2hi, R) && alloc(b.smin, S) && alloc(b.cmin, S + ks::kRowPassWGs) &&
+            alloc(b.K, S) &&
             alloc(b.feat, R * 9) && alloc(b.x0, R * 16) && alloc(b.act[0], R * 64) && alloc(b.act[1], R * 64) &&
             alloc(b.act[2], R * 64) && alloc(b.logits, R);
   if (ok && T) {
@@ -75,7 +76,7 @@ int ensure_learn(ks_ctx* c, uint64_t rows, uint64_t series, bool train) {
 }
 
 ks::LearnWs learn_ws(ks_ctx* c) {
-  return ks::LearnWs{c->learn.s1, c->learn.s2lo, c->learn.s2hi, c->learn.smin, c->learn.K};
+  return ks::LearnWs{c->learn.s1, c->learn.s2lo, c->learn.s2hi, c->learn.smin, c->learn.cmin, c->learn.K};
 }
 
 uint32_t conv_grid(const ks_ctx* c, uint64_t rows) {
@@ -364,31 +365,26 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
   if (int rc = ensure_learn(ctx, (uint64_t)num_series * SR, num_series, false)) return rc;
   hipStream_t st = (hipStream_t)stream;
   LearnBuffers& b = ctx->learn;
-  // the series order per row class, kept in the logits buffer (num_series + 10
-  // words <= its rows; nothing reads the logits before the forward rewrites
-  // them), then one launch per row class (1, 2 or 4 load batches per row,
-  // streamed, or short rows four to a wave): its workgroups past the class's
-  // count return at once
-  uint32_t* plan = reinterpret_cast<uint32_t*>(b.logits);
-  hipLaunchKernelGGL(ks::feature_plan_kernel, dim3(1), dim3(ks::kFeatPlanNT), 0, st, desc, num_series, num_samples,
-                     max_K, plan);
-  hipLaunchKernelGGL((ks::features_kernel<1, ks::row_pass_threads(1)>), dim3(num_series),
-                     dim3(ks::row_pass_threads(1)), 0, st, samples, num_samples, desc,
-                     num_series, max_K, SR, learn_ws(ctx), b.feat, plan);
-  hipLaunchKernelGGL((ks::features_kernel<2, ks::row_pass_threads(2)>), dim3(num_series),
-                     dim3(ks::row_pass_threads(2)), 0, st, samples, num_samples, desc,
-                     num_series, max_K, SR, learn_ws(ctx), b.feat, plan);
-  hipLaunchKernelGGL((ks::features_kernel<4, ks::row_pass_threads(4)>), dim3(num_series),
-                     dim3(ks::row_pass_threads(4)), 0, st, samples, num_samples, desc,
-                     num_series, max_K, SR, learn_ws(ctx), b.feat, plan);
-  hipLaunchKernelGGL((ks::features_kernel<ks::kStreamed, ks::row_pass_threads(ks::kStreamed)>), dim3(num_series),
-                     dim3(ks::row_pass_threads(ks::kStreamed)), 0, st, samples,
-                     num_samples, desc, num_series, max_K, SR, learn_ws(ctx), b.feat, plan);
-  hipLaunchKernelGGL((ks::features_kernel<ks::kGrouped, ks::row_pass_threads(ks::kGrouped)>), dim3(num_series),
-                     dim3(ks::row_pass_threads(ks::kGrouped)), 0, st, samples,
-                     num_samples, desc, num_series, max_K, SR, learn_ws(ctx), b.feat, plan);
+  const uint32_t C = ks::row_pass_chunks(num_series, max_K);
+  auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
+    hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
+                       num_series, max_K, SR, learn_ws(ctx), b.feat, plan, C);
+  };
+  if (num_series <= ks::kRowPassOneLaunch) {
+    launch(ks::features_kernel<ks::kRowsAll>, ks::kRowsAll, nullptr);
+  } else {
+    // the series order per row class, kept in the logits buffer (num_series +
+    // 10 words <= its rows; nothing reads the logits before the forward
+    // rewrites them)
+    uint32_t* plan = reinterpret_cast<uint32_t*>(b.logits);
+    hipLaunchKernelGGL(ks::feature_plan_kernel, dim3(1), dim3(ks::kFeatPlanNT), 0, st, desc, num_series, num_samples,
+                       max_K, plan);
+    launch(ks::features_kernel<ks::kRowsOne>, ks::kRowsOne, plan);
+    launch(ks::features_kernel<ks::kRowsMid>, ks::kRowsMid, plan);
+    launch(ks::features_kernel<ks::kRowsFour>, ks::kRowsFour, plan);
+  }
   hipLaunchKernelGGL((ks::feature_pack_kernel<kNT>), dim3(num_series, (SR + kNT - 1) / kNT), dim3(kNT), 0, st, desc,
-                     num_series, features, feature_rows, b.x0, SR, learn_ws(ctx), b.feat);
+                     num_series, features, feature_rows, b.x0, SR, learn_ws(ctx), b.feat, C);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "features launch");
   b.stamp_desc = desc;

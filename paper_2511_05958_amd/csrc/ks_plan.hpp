@@ -25,7 +25,7 @@ constexpr int kFeatPlanNT = 1024;
 constexpr uint32_t kFeatBuckets = 40;
 
 constexpr uint32_t kFeatClasses = 5;
-__device__ __forceinline__ uint32_t feat_class_index(uint32_t NB) {
+__host__ __device__ constexpr uint32_t feat_class_index(uint32_t NB) {
   return NB == 1 ? 0u : (NB == 2 ? 1u : (NB == 4 ? 2u : (NB == kStreamed ? 3u : 4u)));
 }
 
@@ -60,6 +60,30 @@ __global__ __launch_bounds__(kFeatPlanNT) void feature_plan_kernel(const ks_desc
   __syncthreads();
   for (uint32_t s = tid; s < num_series; s += kFeatPlanNT) plan[atomicAdd(&cnt[key(s)], 1u)] = s;
 }
+
+// Series of workgroup group t of a row-pass launch over the classes of MASK:
+// t itself without a plan, else the t-th of the plan's series of these classes
+// (a class after the other, longest rows first); num_series when there is none.
+template <uint32_t MASK>
+__device__ __forceinline__ uint32_t row_pass_series(const uint32_t* __restrict__ plan, uint32_t num_series,
+                                                    uint32_t t) {
+  if (!plan) return t;
+  constexpr uint32_t order[kFeatClasses] = {3u, 2u, 1u, 0u, 4u};
+#pragma unroll
+  for (uint32_t q = 0; q < kFeatClasses; ++q) {
+    const uint32_t ci = order[q];
+    if (!((MASK >> ci) & 1u)) continue;
+    const uint32_t n = plan[num_series + kFeatClasses + ci];
+    if (t < n) return plan[plan[num_series + ci] + t];
+    t -= n;
+  }
+  return num_series;
+}
+
+// Batches of up to this many series skip the plan and take one launch for all
+// row classes: their workgroups are chunks of series, small enough that the
+// order does not matter, and the plan and the second launch would cost 8 us.
+constexpr uint32_t kRowPassOneLaunch = 64;
 
 }  // namespace
 }  // namespace ks

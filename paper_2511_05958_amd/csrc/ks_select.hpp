@@ -904,6 +904,162 @@ __device__ __forceinline__ void select_rows_long(RowLds& L, const uint32_t* __re
   }
 }
 
+// One long row by all W waves of a workgroup, for launches with too few rows to
+// keep the chip busy with a wave a row (8 x 64 rows of 65537 samples are 512
+// waves, two to a CU: 64 dependent batches each). Wave w streams batches w,
+// w + W, ...; every wave takes the same provisional base from batch 0 (read by
+// all of them, one batch), counts into its own window, and the windows and
+// sums meet in LDS. Results as select_rows_long; the radix levels past the
+// window stay with wave 0.
+template <int W>
+struct CoopLds {
+  uint64_t s1[W], s2[W];
+  uint32_t s2h[W], mn[W], mx[W];
+};
+
+// Adds the windows of all waves into wave 0's (W windows of kSelWin bins).
+template <int W>
+__device__ __forceinline__ void coop_merge(RowLds* sel, uint32_t tid) {
+  __syncthreads();
+  for (uint32_t q = tid; q < kSelWin; q += W * kWave) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) t += sel[v].hist[q];
+    sel[0].hist[q] = t;
+  }
+  __syncthreads();
+}
+
+template <class RANKS, int W, class Emit>
+__device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, const uint32_t* __restrict__ samples,
+                                                 uint64_t off0, uint32_t N, uint32_t begin, uint32_t end, uint32_t w,
+                                                 uint32_t lane, Emit&& emit) {
+  RowLds& L = sel[w];
+  uint32_t* hist = L.hist;
+  u32x4* hv = reinterpret_cast<u32x4*>(hist);
+  auto share = [&](uint64_t s1, uint64_t s2, uint32_t s2h) {  // this wave's totals -> LDS
+    if (lane == 0) {
+      co.s1[w] = s1;
+      co.s2[w] = s2;
+      co.s2h[w] = s2h;
+    }
+  };
+  auto total = [&](uint64_t& s1, uint64_t& s2, uint32_t& s2h) {
+    u128 a2 = 0;
+    s1 = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      s1 += co.s1[v];
+      a2 += ((u128)co.s2h[v] << 64) | co.s2[v];
+    }
+    s2 = (uint64_t)a2;
+    s2h = (uint32_t)(a2 >> 64);
+  };
+  for (uint32_t i = begin; i < end; ++i) {
+    const RowGeo g = row_geo(samples, off0 + (uint64_t)i * N, N);
+    __syncthreads();  // the previous row's windows and totals have been read
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hv[lane * 4 + q] = u32x4{0u, 0u, 0u, 0u};
+    Batch A, B;
+    load_batch(A, samples, g, 0u, lane);
+    if (w && w < g.nb) load_batch(B, samples, g, w, lane);
+    uint32_t m0 = 0xffffffffu;
+    for_batch(A, g, 0u, [&](uint32_t x) { m0 = min(m0, x); });
+    m0 = wave_min_u32(m0);
+    const uint32_t base = m0 > kSelMargin ? m0 - kSelMargin : 0u;
+    if (w) A = B;
+    uint32_t mn = 0xffffffffu, mx = 0u;
+    uint64_t t1 = 0, t2 = 0;
+    wave_lds_sync();
+    auto process = [&](const Batch& X, uint32_t u) {
+      uint32_t t1b = 0, t2b = 0;
+      for_batch(X, g, u, [&](uint32_t x) {
+        mn = min(mn, x);
+        mx = max(mx, x);
+        const uint32_t z = x - base;  // wraps for x < base: the row is then read again below
+        t1b += z;
+        t2b = __umul24(z, z) + t2b;
+        atomicAdd(&hist[min(z, kSelWin - 1u)], 1u);
+      });
+      t1 += t1b;
+      t2 += t2b;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (uint32_t u = w; u < g.nb;) {
+      if (u + W < g.nb) load_batch(B, samples, g, u + W, lane);
+      process(A, u);
+      u += W;
+      if (u >= g.nb) break;
+      if (u + W < g.nb) load_batch(A, samples, g, u + W, lane);
+      process(B, u);
+      u += W;
+    }
+    uint32_t t2h = 0;
+    wave_total_64_96(t1, t2, t2h);
+    mn = wave_min_u32(mn);
+    mx = wave_max_u32(mx);
+    share(t1, t2, t2h);
+    if (lane == 0) {
+      co.mn[w] = mn;
+      co.mx[w] = mx;
+    }
+    coop_merge<W>(sel, threadIdx.x);
+    RowOut o;
+    o.rmin = co.mn[0];
+    o.rmax = co.mx[0];
+#pragma unroll
+    for (int v = 1; v < W; ++v) {
+      o.rmin = min(o.rmin, co.mn[v]);
+      o.rmax = max(o.rmax, co.mx[v]);
+    }
+    const uint32_t range = o.rmax - o.rmin;  // from here on every branch is workgroup-uniform
+    const uint32_t b = range ? 32u - __clz(range) : 0u;
+    uint32_t wbase = base;
+    if (o.rmin >= base && o.rmax - base < (1u << kFastBits)) {
+      uint64_t a1, a2;
+      uint32_t a2h;
+      total(a1, a2, a2h);
+      const u128 q2 = (((u128)a2h << 64) | a2) + (u128)(2ull * base) * a1 + (u128)((uint64_t)base * base) * N;
+      o.s1 = a1 + (uint64_t)base * N;
+      o.s2 = (uint64_t)q2;
+      o.s2h = (uint32_t)(q2 >> 64);
+    } else {  // the row again: 96-bit moments, keys from its own minimum
+      __syncthreads();  // wave 0's window and the totals have been read
+#pragma unroll
+      for (int q = 0; q < 4; ++q) hv[lane * 4 + q] = u32x4{0u, 0u, 0u, 0u};
+      wave_lds_sync();
+      const bool window = b >= 1 && b < 32;
+      uint32_t unused = 0xffffffffu, s2h = 0;
+      uint64_t s1 = 0, s2 = 0;
+#pragma unroll 1
+      for (uint32_t u = w; u < g.nb; u += W) {
+        load_batch(A, samples, g, u, lane);
+        for_batch(A, g, u, [&](uint32_t x) {
+          acc_sample(x, unused, s1, s2, s2h);
+          if (window) atomicAdd(&hist[min(x - o.rmin, kSelWin - 1u)], 1u);
+        });
+      }
+      wave_total_64_96(s1, s2, s2h);
+      share(s1, s2, s2h);
+      coop_merge<W>(sel, threadIdx.x);
+      total(o.s1, o.s2, o.s2h);
+      wbase = o.rmin;
+    }
+    if (w == 0) {
+      if (b == 0) {
+        o.sel = o.rmin;
+      } else if (b < 32) {
+        o.sel = select_from_window<RANKS>(L, samples, g, wbase, o.rmax, N, lane);
+      } else {  // no window: radix levels over every key
+        const bool tl = lane < RANKS::kCount;
+        const uint32_t R = tl ? RANKS::rank(lane, N) : 0u;
+        o.sel = stream_select(L, samples, g, o.rmin, 0u, 32u, R, tl, lane) + o.rmin;
+      }
+      emit(i, o);
+    }
+  }
+}
+
 // ------------------------------------------------- short rows, four to a wave
 // Rows of up to kGroupMaxN samples go four to a wave, one to each 16-lane DPP
 // row (g = lane / 16), loaded like the scan's grouped rows (load_group: up to
@@ -1112,20 +1268,20 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 // ceil(floor(N / 4) / 256) load batches at most, and rows of up to 1, 2 or 4
 // of them are held in registers (class 1, 2, 4), longer rows are streamed
 // (class kStreamed).
-// Waves per SIMD the row-pass kernels are compiled for, by row class (1 = the
-// compiler's choice). With 4.3 KiB of LDS per wave the register file sets the
-// occupancy; these are the largest targets met without spills (6 at 80
-// registers), which run rows of up to 1027 samples 6 - 9% faster than the 5
-// waves the compiler picks by itself. Rows of 2048 samples keep the
-// compiler's 4 (5 spills and runs slower), and so do short rows (higher
-// targets spill).
-__host__ __device__ constexpr int feat_waves_per_eu(int NB) { return NB == 1 ? 6 : NB == 4 ? 3 : 1; }
-__host__ __device__ constexpr int stats_waves_per_eu(int NB) { return NB == 1 ? 6 : 1; }
-// Workgroup threads of the row-pass kernels by row class: rows of two load
-// batches (1028 - 2051 samples) run in 512-thread workgroups, eight waves on
-// a series (two workgroups per CU at the same four waves per SIMD; 1% faster
-// than 256 threads on 8192 x 1024 x 2048), the other classes in 256.
-__host__ __device__ constexpr int row_pass_threads(int NB) { return NB == 2 ? 512 : 256; }
+// A launch serves a set of classes (a mask of 1 << feat_class_index), classes of
+// like register use together, since an empty launch costs 4.5 us (with one per
+// class four of the five were empty): rows of one load batch; short rows, rows
+// of two batches and streamed rows (four waves per SIMD each); rows of four
+// batches (three); or, for a batch of few series, all of them at once.
+// Workgroups of 256 threads, 512 where rows of two batches are served (eight
+// waves on a series; 1% faster than 256 threads on 8192 x 1024 x 2048).
+constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 8u | 16u, kRowsFour = 4u, kRowsAll = 31u;
+__host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return (mask & 2u) ? 512 : 256; }
+// Waves per SIMD the row-pass kernels are compiled for (1 = the compiler's
+// choice): 6 (80 registers) for rows of one batch, the largest target met
+// without spills, runs rows of up to 1027 samples 6 - 9% faster than the 5 the
+// compiler picks by itself.
+__host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 6 : mask == kRowsFour ? 3 : 1; }
 __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
   return N <= kGroupMaxN ? kGrouped
          : (N / 4 + 4u * kWave - 1) / (4u * kWave) <= 1
@@ -1133,6 +1289,79 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
              : ((N / 4 + 4u * kWave - 1) / (4u * kWave) <= 2
                     ? 2u
                     : ((N / 4 + 4u * kWave - 1) / (4u * kWave) <= 4 ? 4u : kStreamed));
+}
+
+// Split of the row passes over workgroups. A series' rows are cut into C chunks
+// (row_pass_chunks, the same for the whole launch), one workgroup each, so that
+// a batch of few series still fills the chip: the statistics of 8 series of 64
+// rows of 65537 samples take 41 us (3.3 TB/s) so split, 1440 us with a workgroup
+// per series; of 8 x 256 rows of 1024 samples 15 us against 145, of 256 x 512
+// rows of 256 samples (four waves per CU unsplit) 91 us against 246. A chunk is not made
+// smaller than a row (or a step of four short rows) per wave; rows too long for
+// the registers go a row at a time to all waves of the workgroup
+// (select_rows_coop) where a chunk has fewer than two rows per wave.
+constexpr uint32_t kRowPassWGs = 2048;   // eight workgroups per CU
+constexpr uint32_t kRowPassChunks = 256; // at most, per series
+__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K) {
+  const uint32_t c = num_series >= kRowPassWGs ? 1u : (kRowPassWGs + num_series - 1) / num_series;
+  const uint32_t m = max_K < kRowPassChunks ? max_K : kRowPassChunks;
+  return c < m ? c : m;
+}
+
+// Rows of chunk c of a K-row series of row class NB in a workgroup of W waves,
+// and the calling wave's share of them (all of them where coop).
+struct RowSpan {
+  uint32_t begin, end;
+  bool coop;
+};
+template <int NB, int W>
+__device__ __forceinline__ RowSpan row_span(uint32_t K, uint32_t c, uint32_t C, uint32_t w) {
+  uint32_t R = (K + C - 1) / C;
+  if (NB != (int)kStreamed) R = max(R, (uint32_t)W * (NB == (int)kGrouped ? kGroupRows : 1u));
+  const uint32_t r0 = min((uint64_t)c * R, (uint64_t)K), r1 = min(r0 + R, K);
+  if (NB == (int)kStreamed && R < 2u * W) return RowSpan{r0, r1, true};
+  const uint32_t B = (r1 - r0 + W - 1) / W;
+  const uint32_t begin = min(r0 + w * B, r1);
+  return RowSpan{begin, min(begin + B, r1), false};
+}
+
+// The rows of `sp` of one series of row class NB: emit(i, o, first) gets row
+// i's results with its targets on lanes first .. of o.sel.
+template <int NB, class RANKS, int W, class Emit>
+__device__ __forceinline__ void select_rows(RowLds* sel, CoopLds<W>& co, const uint32_t* __restrict__ samples,
+                                            uint64_t off0, uint32_t N, const RowSpan& sp, uint32_t w, uint32_t lane,
+                                            Emit&& emit) {
+  RowLds& L = sel[w];
+  if constexpr (NB == (int)kStreamed) {
+    if (sp.coop)
+      select_rows_coop<RANKS, W>(sel, co, samples, off0, N, sp.begin, sp.end, w, lane,
+                                 [&](uint32_t i, const RowOut& o) { emit(i, o, 0u); });
+    else
+      select_rows_long<RANKS>(L, samples, off0, N, sp.end, sp.begin, 1u, lane,
+                              [&](uint32_t i, const RowOut& o) { emit(i, o, 0u); });
+  } else if constexpr (NB == (int)kGrouped) {
+    select_rows_grouped<RANKS>(L, samples, off0, N, sp.begin, sp.end, lane, emit);
+  } else {
+    Batch cur[NB];
+    RowGeo g;
+    if (sp.begin < sp.end) g = load_row<NB>(cur, samples, off0 + (uint64_t)sp.begin * N, N, lane);
+    uint32_t p = 0;  // window base from the previous row (none for the first)
+    for (uint32_t i = sp.begin; i < sp.end; ++i) {
+      RowOut o;
+      RowScan rs;
+      const bool based = i > sp.begin && row_scan_based<NB>(L, cur, g, N, p, o.s1, o.s2, o.s2h, rs, lane);
+      if (!based) rs = row_scan<NB>(L, cur, g, N, o.s1, o.s2, o.s2h, lane);
+      // the next row's loads are in flight while this row's order statistics are found
+      const RowGeo gi = g;
+      if (i + 1 < sp.end) g = load_row<NB>(cur, samples, off0 + (uint64_t)(i + 1) * N, N, lane);
+      o.rmin = rs.rmin;
+      o.rmax = rs.rmax;
+      o.sel = based ? select_from_window<RANKS>(L, samples, gi, p, rs.rmax, N, lane)
+                    : row_select<NB, RANKS>(L, samples, gi, rs, N, lane);
+      p = rs.rmin > kRowMargin ? rs.rmin - kRowMargin : 0u;
+      emit(i, o, 0u);
+    }
+  }
 }
 
 }  // namespace ks

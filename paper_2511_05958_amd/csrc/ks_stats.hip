@@ -42,112 +42,104 @@ __device__ double u128_to_double(u128 v) {
   return ldexp((double)(top | (uint64_t)sticky), sh);
 }
 
-template <int NB>
-__global__ __launch_bounds__(ks::row_pass_threads(NB)) __attribute__((amdgpu_waves_per_eu(ks::stats_waves_per_eu(NB)))) void row_stats_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
-                                                        const ks_desc* __restrict__ desc, uint32_t num_series,
-                                                        uint32_t max_K, ks_row_stats* __restrict__ out,
-                                                        uint64_t out_rows, const uint32_t* __restrict__ plan) {
-  constexpr int W = ks::row_pass_threads(NB) / ks::kWave;
-  // rows per contiguous write of a wave's records (64 for rows of two or more
-  // load batches: fewer, longer write bursts among the reads)
-  constexpr uint32_t kStage = NB == 1 || NB == (int)ks::kGrouped ? 16u : 64u;
+// a row's exact results, staged until S rows are done; the records (mean, std
+// in FP64) are then made by S lanes at once. 64 rows for rows of two or more
+// load batches (fewer, longer write bursts among the reads), 16 otherwise.
+template <uint32_t S>
+struct RowStage {
+  uint64_t s1[S], s2[S];
+  uint32_t s2h[S], rmin[S], rmax[S], p50[S], p95[S];
+};
+constexpr uint32_t stats_stage_rows(int NB) { return NB == 1 || NB == (int)ks::kGrouped ? 16u : 64u; }
+
+// The calling wave's rows `sp` of one series of row class NB; every kStage
+// rows' records are written as contiguous 16-byte stores (records written one
+// at a time, by waves interleaved row by row, left partly written cache lines
+// behind).
+template <int NB, int W>
+__device__ __forceinline__ void stats_rows(ks::RowLds* sel, ks::CoopLds<W>& co, void* stage,
+                                           const uint32_t* __restrict__ samples, const ks_desc& d, uint32_t c,
+                                           uint32_t C, uint32_t w, uint32_t lane, ks_row_stats* __restrict__ o) {
+  constexpr uint32_t kStage = stats_stage_rows(NB);
   static_assert(kStage <= (uint32_t)ks::kWave, "a flush makes one record per lane");
-  // a row's exact results, staged until kStage rows are done; the records
-  // (mean, std in FP64) are then made by kStage lanes at once
-  struct RowStage {
-    uint64_t s1[kStage], s2[kStage];
-    uint32_t s2h[kStage], rmin[kStage], rmax[kStage], p50[kStage], p95[kStage];
-  };
-  __shared__ ks::RowLds sel[W];
-  __shared__ RowStage stage[W];
-  // workgroup t takes the t-th series of this row class in the plan's order
-  // (largest first; malformed series in class 1)
-  const uint32_t ci = ks::feat_class_index(NB);
-  if (blockIdx.x >= plan[num_series + ks::kFeatClasses + ci]) return;
-  const uint32_t s = plan[plan[num_series + ci] + blockIdx.x];
-  const ks_desc d = desc[s];
-  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
-  const bool bad = ks::check_desc(d, num_samples, max_K) || d.N > KS_FEATURE_MAX_N;
-  if ((bad ? 1u : ks::feat_batches(d.N)) != (uint32_t)NB) return;
-  const bool fits = d.aux_offset <= out_rows && (uint64_t)d.K <= out_rows - d.aux_offset;
-  if (!fits) return;
-  ks_row_stats* o = out + d.aux_offset;
-  if (bad) {
-    for (uint32_t i = threadIdx.x; i < d.K; i += (uint32_t)ks::row_pass_threads(NB)) o[i] = ks_row_stats{NAN, NAN, 0u, 0u, 0u, 0u};
-    return;
-  }
-  const uint32_t K = d.K, N = d.N;
-  ks::RowLds& L = sel[w];
-  // wave w takes rows [w B, (w + 1) B) and writes every kStage rows' records as
-  // contiguous 16-byte stores (records written one at a time, by waves
-  // interleaved row by row, left partly written cache lines behind)
-  const uint32_t B = (K + W - 1) / W;
-  const uint32_t begin = min(w * B, K), end = min(begin + B, K);
-  RowStage& st = stage[w];
-  // row i's results; its p50 and p95 on lanes first and first + 1 of sel_x
-  auto emit = [&](uint32_t i, uint64_t s1, uint64_t s2, uint32_t s2h, uint32_t rmin, uint32_t rmax, uint32_t sel_x,
-                  uint32_t first) {
-    const uint32_t p50 = (uint32_t)__builtin_amdgcn_readlane((int)sel_x, (int)first);
-    const uint32_t p95 = (uint32_t)__builtin_amdgcn_readlane((int)sel_x, (int)first + 1);
-    const uint32_t j = (i - begin) % kStage;
+  const uint32_t N = d.N;
+  const ks::RowSpan sp = ks::row_span<NB, W>(d.K, c, C, w);
+  RowStage<kStage>& st = reinterpret_cast<RowStage<kStage>*>(stage)[w];
+  // row i's results; its p50 and p95 on lanes first and first + 1
+  ks::select_rows<NB, StatRanks, W>(sel, co, samples, d.offset, N, sp, w, lane,
+                                    [&](uint32_t i, const ks::RowOut& r, uint32_t first) {
+    const uint32_t p50 = (uint32_t)__builtin_amdgcn_readlane((int)r.sel, (int)first);
+    const uint32_t p95 = (uint32_t)__builtin_amdgcn_readlane((int)r.sel, (int)first + 1);
+    const uint32_t j = (i - sp.begin) % kStage;
     if (lane == 0) {
-      st.s1[j] = s1;
-      st.s2[j] = s2;
-      st.s2h[j] = s2h;
-      st.rmin[j] = rmin;
-      st.rmax[j] = rmax;
+      st.s1[j] = r.s1;
+      st.s2[j] = r.s2;
+      st.s2h[j] = r.s2h;
+      st.rmin[j] = r.rmin;
+      st.rmax[j] = r.rmax;
       st.p50[j] = p50;
       st.p95[j] = p95;
     }
-    if (j + 1 == kStage || i + 1 == end) {  // rows i - j .. i: lane q makes row i - j + q's record
+    if (j + 1 == kStage || i + 1 == sp.end) {  // rows i - j .. i: lane q makes row i - j + q's record
       ks::wave_lds_sync();
       if (lane <= j) {
         const uint64_t a1 = st.s1[lane];
         const u128 S2 = ((u128)st.s2h[lane] << 64) | st.s2[lane];
         const u128 num = (u128)N * S2 - (u128)a1 * a1;  // >= 0 (Cauchy-Schwarz), < 2^113
         const double nn = (double)N * (double)N;
-        const ks_row_stats r{(double)a1 / (double)N, sqrt(u128_to_double(num) / nn), st.rmin[lane], st.p50[lane],
-                             st.p95[lane], st.rmax[lane]};
+        const ks_row_stats rec{(double)a1 / (double)N, sqrt(u128_to_double(num) / nn), st.rmin[lane], st.p50[lane],
+                               st.p95[lane], st.rmax[lane]};
         static_assert(sizeof(ks_row_stats) == 32, "a record is two 16-byte stores");
         ks::u32x4 v0, v1;
-        __builtin_memcpy(&v0, &r, 16);
-        __builtin_memcpy(&v1, reinterpret_cast<const char*>(&r) + 16, 16);
+        __builtin_memcpy(&v0, &rec, 16);
+        __builtin_memcpy(&v1, reinterpret_cast<const char*>(&rec) + 16, 16);
         ks::u32x4* dst = reinterpret_cast<ks::u32x4*>(o + (i - j) + lane);
         ks::row_out_store<NB>(v0, dst);
         ks::row_out_store<NB>(v1, dst + 1);
       }
       ks::wave_lds_sync();
     }
-  };
-  if constexpr (NB == (int)ks::kStreamed) {
-    ks::select_rows_long<StatRanks>(L, samples, d.offset, N, end, begin, 1u, lane, [&](uint32_t i, const ks::RowOut& r) {
-      emit(i, r.s1, r.s2, r.s2h, r.rmin, r.rmax, r.sel, 0u);
-    });
-  } else if constexpr (NB == (int)ks::kGrouped) {
-    ks::select_rows_grouped<StatRanks>(L, samples, d.offset, N, begin, end, lane,
-                                       [&](uint32_t i, const ks::RowOut& r, uint32_t first) {
-                                         emit(i, r.s1, r.s2, r.s2h, r.rmin, r.rmax, r.sel, first);
-                                       });
-  } else {
-    ks::Batch cur[NB];
-    ks::RowGeo g;
-    if (begin < end) g = ks::load_row<NB>(cur, samples, d.offset + (uint64_t)begin * N, N, lane);
-    uint32_t p = 0;  // window base from the previous row (none for the first)
-    for (uint32_t i = begin; i < end; ++i) {
-      uint64_t s1, s2;
-      uint32_t s2h;
-      ks::RowScan rs;
-      const bool based = i > begin && ks::row_scan_based<NB>(L, cur, g, N, p, s1, s2, s2h, rs, lane);
-      if (!based) rs = ks::row_scan<NB>(L, cur, g, N, s1, s2, s2h, lane);
-      // the next row's loads are in flight while this row's percentiles are found
-      const ks::RowGeo gi = g;
-      if (i + 1 < end) g = ks::load_row<NB>(cur, samples, d.offset + (uint64_t)(i + 1) * N, N, lane);
-      const uint32_t sel = based ? ks::select_from_window<StatRanks>(L, samples, gi, p, rs.rmax, N, lane)
-                                 : ks::row_select<NB, StatRanks>(L, samples, gi, rs, N, lane);
-      p = rs.rmin > ks::kRowMargin ? rs.rmin - ks::kRowMargin : 0u;
-      emit(i, s1, s2, s2h, rs.rmin, rs.rmax, sel, 0u);
-    }
+  });
+}
+
+// One launch over the row classes of MASK, one workgroup per (series, chunk of
+// its rows). With a plan the series come in its order (each class largest
+// first), without one in descriptor order. Malformed series are class 1's.
+template <uint32_t MASK>
+__global__ __launch_bounds__(ks::row_pass_threads(MASK)) __attribute__((amdgpu_waves_per_eu(ks::row_pass_waves(MASK)))) void row_stats_kernel(
+    const uint32_t* __restrict__ samples, uint64_t num_samples, const ks_desc* __restrict__ desc, uint32_t num_series,
+    uint32_t max_K, ks_row_stats* __restrict__ out, uint64_t out_rows, const uint32_t* __restrict__ plan, uint32_t C) {
+  constexpr int NT = ks::row_pass_threads(MASK), W = NT / ks::kWave;
+  constexpr uint32_t kStageMax = MASK == ks::kRowsOne ? 16u : 64u;
+  __shared__ ks::RowLds sel[W];
+  __shared__ RowStage<kStageMax> stage[W];
+  __shared__ ks::CoopLds<W> co;
+  const uint32_t t = blockIdx.x / C, c = blockIdx.x - t * C;
+  const uint32_t s = ks::row_pass_series<MASK>(plan, num_series, t);
+  if (s >= num_series) return;
+  const ks_desc d = desc[s];
+  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
+  const bool bad = ks::check_desc(d, num_samples, max_K) || d.N > KS_FEATURE_MAX_N;
+  const uint32_t nb = bad ? 1u : ks::feat_batches(d.N);
+  if (!((MASK >> ks::feat_class_index(nb)) & 1u)) return;
+  const bool fits = d.aux_offset <= out_rows && (uint64_t)d.K <= out_rows - d.aux_offset;
+  if (!fits) return;
+  ks_row_stats* o = out + d.aux_offset;
+  if (bad) {
+    for (uint64_t i = (uint64_t)c * NT + threadIdx.x; i < d.K; i += (uint64_t)C * NT)
+      o[i] = ks_row_stats{NAN, NAN, 0u, 0u, 0u, 0u};
+    return;
   }
+  auto rows = [&](auto tag) {
+    constexpr int NB = decltype(tag)::value;
+    if constexpr ((MASK >> ks::feat_class_index(NB)) & 1u)
+      if (nb == (uint32_t)NB) stats_rows<NB, W>(sel, co, stage, samples, d, c, C, w, lane, o);
+  };
+  rows(std::integral_constant<int, 1>{});
+  rows(std::integral_constant<int, 2>{});
+  rows(std::integral_constant<int, 4>{});
+  rows(std::integral_constant<int, (int)ks::kStreamed>{});
+  rows(std::integral_constant<int, (int)ks::kGrouped>{});
 }
 
 }  // namespace
@@ -162,24 +154,24 @@ extern "C" int ks_stats_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t st = (hipStream_t)stream;
-  // the series order per row class (the feature pass's plan), kept in the
-  // context's scan workspace (its queue items: 512 bytes per series); then one
-  // launch per row class (1, 2 or 4 load batches per row, streamed, or short
-  // rows four to a wave), each taking its own series largest first
-  if (int rc = ks_reserve(ctx, num_series, 0)) return rc;
-  uint32_t* plan = reinterpret_cast<uint32_t*>(ctx->items);
-  hipLaunchKernelGGL(ks::feature_plan_kernel, dim3(1), dim3(ks::kFeatPlanNT), 0, st, desc, num_series, num_samples,
-                     max_K, plan);
-  hipLaunchKernelGGL(row_stats_kernel<1>, dim3(num_series), dim3(ks::row_pass_threads(1)), 0, st, samples, num_samples, desc, num_series,
-                     max_K, out, out_rows, (const uint32_t*)plan);
-  hipLaunchKernelGGL(row_stats_kernel<2>, dim3(num_series), dim3(ks::row_pass_threads(2)), 0, st, samples, num_samples, desc, num_series,
-                     max_K, out, out_rows, (const uint32_t*)plan);
-  hipLaunchKernelGGL(row_stats_kernel<4>, dim3(num_series), dim3(ks::row_pass_threads(4)), 0, st, samples, num_samples, desc, num_series,
-                     max_K, out, out_rows, (const uint32_t*)plan);
-  hipLaunchKernelGGL(row_stats_kernel<ks::kStreamed>, dim3(num_series), dim3(ks::row_pass_threads(ks::kStreamed)), 0, st, samples, num_samples, desc,
-                     num_series, max_K, out, out_rows, (const uint32_t*)plan);
-  hipLaunchKernelGGL(row_stats_kernel<ks::kGrouped>, dim3(num_series), dim3(ks::row_pass_threads(ks::kGrouped)), 0, st, samples, num_samples, desc,
-                     num_series, max_K, out, out_rows, (const uint32_t*)plan);
+  const uint32_t C = ks::row_pass_chunks(num_series, max_K);
+  auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
+    hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
+                       num_series, max_K, out, out_rows, plan, C);
+  };
+  if (num_series <= ks::kRowPassOneLaunch) {
+    launch(row_stats_kernel<ks::kRowsAll>, ks::kRowsAll, nullptr);
+  } else {
+    // the series order per row class (the feature pass's plan), kept in the
+    // context's scan workspace (its queue items: 512 bytes per series)
+    if (int rc = ks_reserve(ctx, num_series, 0)) return rc;
+    uint32_t* plan = reinterpret_cast<uint32_t*>(ctx->items);
+    hipLaunchKernelGGL(ks::feature_plan_kernel, dim3(1), dim3(ks::kFeatPlanNT), 0, st, desc, num_series, num_samples,
+                       max_K, plan);
+    launch(row_stats_kernel<ks::kRowsOne>, ks::kRowsOne, plan);
+    launch(row_stats_kernel<ks::kRowsMid>, ks::kRowsMid, plan);
+    launch(row_stats_kernel<ks::kRowsFour>, ks::kRowsFour, plan);
+  }
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "row stats launch");
 }
