@@ -161,7 +161,8 @@ int ks_reserve(ks_ctx *ctx, uint32_t max_series, uint64_t max_total_steps);
  *
  * Launch plan (ks_launch_set / ks_autotune; default KS_LAUNCH_ORDERED): an
  * on-device planning kernel orders the series largest first, then either one
- * workgroup per series in that order, or a persistent kernel drains the
+ * workgroup per series in that order (a batch of few series is instead split
+ * over the device by rows and candidates and launched directly), or a persistent kernel drains the
  * ordered items (large series split into row ranges whose moments meet in
  * the workspace) followed by a finish kernel. Planned launches are replayed
  * from a hipGraph cached per (mode, max_K class, grid) with updated

@@ -16,6 +16,7 @@
 #include "ks.h"
 #include "ks_ctx.hpp"
 #include "ks_persist.hpp"
+#include "ks_split.hpp"
 
 using namespace ks_host;
 
@@ -81,6 +82,22 @@ unsigned char* scratch_of(int device) {
   return g_scratch[device];
 }
 
+// Batches of few series under the ordered plan (ks_split.hpp). The spread scan
+// serves up to 384 series (one and a half per CU) of 64 to 2048 rows: there it
+// is ahead at every size measured (256 series of 1024 x 1024: 363 us, 492 with a
+// workgroup per series; 384 of 256 x 1024: 111 against 129, 384 of 1024 x 64: 297
+// against 282), at 512 it is behind for most (512 of 1024 x 64: 393 against
+// 284), since each of its workgroups makes its series' keys again. The
+// one-launch scan serves up to 1024 series of at most 256 rows and (on average)
+// 256 KB: 1024 of 64 x 256 take 24 us against 37, 2048 of 256 x 64 111 against
+// 109; a series of more than 256 KB keeps its one workgroup busy for longer than
+// the spread scan's two more launches take.
+constexpr uint32_t kSplitMaxSeries = 384;
+constexpr uint32_t kSplitWGs = 2048;             // eight workgroups per CU stream the rows
+constexpr uint32_t kTinyMaxSeries = 1024;
+constexpr int kTinyMaxClass = 2;                 // K <= 256
+constexpr uint64_t kTinyMaxSamples = 1u << 16;   // 256 KB a series
+
 void free_workspace(ks_ctx* c) {
   (void)hipFree(c->hdr);
   (void)hipFree(c->items);
@@ -88,6 +105,14 @@ void free_workspace(ks_ctx* c) {
   (void)hipFree(c->done);
   (void)hipFree(c->smin);
   (void)hipFree(c->mom);
+  (void)hipFree(c->split_mom);
+  (void)hipFree(c->split_sorted);
+  (void)hipFree(c->split_best);
+  (void)hipFree(c->split_ticket);
+  c->split_mom = nullptr;
+  c->split_sorted = nullptr;
+  c->split_best = nullptr;
+  c->split_ticket = nullptr;
   c->hdr = nullptr;
   c->items = nullptr;
   c->mom_base = nullptr;
@@ -102,13 +127,19 @@ int ensure_workspace(ks_ctx* c, uint64_t num_series, uint64_t rows) {
   if (num_series <= c->cap_series && rows <= c->cap_rows && c->hdr) return KS_OK;
   const uint64_t ns = num_series > c->cap_series ? num_series : c->cap_series;
   const uint64_t nr = rows > c->cap_rows ? rows : c->cap_rows;
+  // the split scan's share: batches of up to kSplitMaxSeries series of any K
+  const uint64_t nsp = ns < kSplitMaxSeries ? (ns ? ns : 1) : kSplitMaxSeries;
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_workspace(c);
   if (hipMalloc(&c->hdr, 256) != hipSuccess || hipMalloc(&c->items, sizeof(ks::Item) * ks::kMaxChunks * ns) != hipSuccess ||
       hipMalloc(&c->mom_base, sizeof(uint64_t) * ns) != hipSuccess || hipMalloc(&c->done, sizeof(uint32_t) * ns) != hipSuccess ||
       hipMalloc(&c->smin, sizeof(uint32_t) * ns) != hipSuccess ||
-      hipMalloc(&c->mom, sizeof(ks::RowMom) * (nr ? nr : 1)) != hipSuccess) {
+      hipMalloc(&c->mom, sizeof(ks::RowMom) * (nr ? nr : 1)) != hipSuccess ||
+      hipMalloc(&c->split_mom, sizeof(ks::RowMom) * nsp * KS_MAX_K) != hipSuccess ||
+      hipMalloc(&c->split_sorted, sizeof(ks::SortKey) * nsp * KS_MAX_K) != hipSuccess ||
+      hipMalloc(&c->split_best, sizeof(uint32_t) * 2 * nsp * ks::kSplitSlots) != hipSuccess ||
+      hipMalloc(&c->split_ticket, sizeof(uint32_t) * nsp) != hipSuccess) {
     free_workspace(c);
     (void)hipGetLastError();
     return KS_E_NOMEM;
@@ -227,6 +258,43 @@ int launch_plan(ks_ctx* c, int kc, int v, int mode, const ScanArgs& a, bool use_
   return KS_OK;
 }
 
+// Whether a batch takes the one-launch scan (by the mean size of its series, if
+// the sample buffer holds no more than the batch; any series is scanned right).
+bool tiny_batch(int kc, const ScanArgs& a) {
+  return kc <= kTinyMaxClass && a.num_series <= kTinyMaxSeries && a.num_samples / a.num_series <= kTinyMaxSamples;
+}
+
+// The scan of a batch of few series. Launched directly: replaying one or three
+// kernels from a graph costs more on the host (27 us a call for one sweep,
+// against 8).
+int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
+  if (tiny_batch(kc, a)) {
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(a.num_series), dim3(ks::kTinyNT), 0, st, a.samples, a.num_samples, a.desc, a.prm,
+                         a.max_K, a.out, a.allU, a.allU_len);
+    };
+    switch (kc) {
+      case 0: run(ks::tiny_scan_kernel<64>); break;
+      case 1: run(ks::tiny_scan_kernel<128>); break;
+      default: run(ks::tiny_scan_kernel<256>);
+    }
+  } else {
+    if (int rc = ensure_workspace(c, a.num_series, 0)) return rc;
+    const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
+    const uint32_t chunks = (kSplitWGs + a.num_series - 1) / a.num_series;
+    const uint32_t C = chunks < a.max_K ? chunks : a.max_K;
+    hipLaunchKernelGGL(ks::split_moments_kernel, dim3(C, a.num_series), dim3(ks::kSplitNT), 0, st, a.samples,
+                       a.num_samples, a.desc, a.max_K, a.out, ws);
+    hipLaunchKernelGGL(ks::split_rank_kernel, dim3((a.max_K + ks::kWave - 1) / ks::kWave, a.num_series),
+                       dim3(ks::kSplitNT), 0, st, a.num_samples, a.desc, a.max_K, ws);
+    hipLaunchKernelGGL(ks::split_walk_kernel, dim3((a.max_K - 1 + ks::kWave - 1) / ks::kWave, a.num_series),
+                       dim3(ks::kSplitWalkNT), 0, st, a.num_samples, a.desc, a.max_K, a.prm, a.out, a.allU,
+                       a.allU_len, ws);
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? KS_OK : hip_fail(e, "split scan launch");
+}
+
 LaunchCfg config_for(const ks_ctx* c, int kc, uint32_t num_series, uint32_t opts) {
   LaunchCfg cfg;
   auto it = c->tuned.find(std::make_tuple(kc, num_series));
@@ -242,6 +310,7 @@ int scan_with(ks_ctx* ctx, const ScanArgs& a, int kc, const LaunchCfg& cfg, hipS
     hipError_t e = launch_grid(kc, cfg.variant, a, st);
     return e == hipSuccess ? KS_OK : hip_fail(e, "scan launch");
   }
+  if (cfg.mode == KS_LAUNCH_ORDERED && (a.num_series <= kSplitMaxSeries || tiny_batch(kc, a))) return launch_split(ctx, kc, a, st);
   const bool split = cfg.mode == KS_LAUNCH_PERSISTENT;
   if (int rc = ensure_workspace(ctx, a.num_series, split ? (uint64_t)a.num_series * a.max_K : 0)) return rc;
   ScanArgs b = a;

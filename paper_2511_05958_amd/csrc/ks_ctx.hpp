@@ -15,6 +15,7 @@
 namespace ks {
 struct Item;
 struct RowMom;
+struct SortKey;
 }  // namespace ks
 
 namespace ks_host {
@@ -157,6 +158,10 @@ struct ks_ctx {
   uint32_t* done = nullptr;
   uint32_t* smin = nullptr;
   ks::RowMom* mom = nullptr;
+  ks::RowMom* split_mom = nullptr;  // the split scan's workspace (ks::SplitWs)
+  ks::SortKey* split_sorted = nullptr;
+  uint32_t* split_best = nullptr;
+  uint32_t* split_ticket = nullptr;
   uint64_t cap_series = 0, cap_rows = 0;
   std::map<std::tuple<int, int, int, uint32_t>, ks_host::GraphEntry> graphs;  // (mode, K class, variant, grid)
   std::map<std::tuple<int, uint32_t>, ks_host::LaunchCfg> tuned;         // (K class, num_series)

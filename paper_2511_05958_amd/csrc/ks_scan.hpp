@@ -132,6 +132,18 @@ __device__ __forceinline__ void write_result(ks_result* o, uint32_t cp, uint32_t
   o->pad = 0;
 }
 
+// The result of a series whose most significant split is c (statistic U).
+__device__ __forceinline__ void write_choice(ks_result* out, uint32_t U, uint32_t c, uint32_t K, const ks_params& prm,
+                                             uint32_t extra_flags) {
+  const uint32_t n = c, m = K - c;
+  const double U2 = (double)((uint64_t)U * U);
+  const double nmK = (double)((uint64_t)n * m * K);
+  const double lambda2 = U2 / nmK;
+  const double p = U == 0 ? 1.0 : kolmogorov_q(lambda2);
+  const uint32_t flags = ((U2 > prm.c_alpha * nmK) ? KS_SIGNIFICANT : 0u) | extra_flags;
+  write_result(out, c, n, m, U, (double)U / (double)((uint64_t)n * m), sqrt(lambda2), p, flags);
+}
+
 // ---------------------------------------------------------------- phases
 
 // ---------------------------------------------------------------- streaming
@@ -828,13 +840,7 @@ __device__ void finish_series(ScanSmem<KMAX, NT, RB>& sm, uint32_t K, uint32_t N
       c = c_lo;
       U = 0;
     }
-    const uint32_t n = c, m = K - c;
-    const double U2 = (double)((uint64_t)U * U);
-    const double nmK = (double)((uint64_t)n * m * K);
-    const double lambda2 = U2 / nmK;
-    const double p = U == 0 ? 1.0 : kolmogorov_q(lambda2);
-    const uint32_t flags = ((U2 > prm.c_alpha * nmK) ? KS_SIGNIFICANT : 0u) | extra_flags;
-    write_result(out, c, n, m, U, (double)U / (double)((uint64_t)n * m), sqrt(lambda2), p, flags);
+    write_choice(out, U, c, K, prm, extra_flags);
   }
   __syncthreads();
 }
