@@ -15,6 +15,8 @@
 // with W'[i][o][k] = W[o][i][4 - k], so one kernel serves both directions.
 #pragma once
 
+#include <type_traits>
+
 #include "ks.h"
 #include "ks_wave.hpp"
 
@@ -47,6 +49,14 @@ __device__ __forceinline__ bool row_valid(uint64_t row, uint64_t rows, uint32_t 
 __device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
                                                  0, 0);
+}
+
+// Position channels of row t of a K-row series (double, rounded to float).
+__device__ __forceinline__ float pos_frac(uint32_t t, uint32_t K) {
+  return (float)((double)t / (double)(K > 1 ? K - 1 : 1));
+}
+__device__ __forceinline__ float pos_centre(uint32_t t, uint32_t K) {
+  return (float)(4.0 * (double)t * (double)(K - t) / ((double)K * (double)K));
 }
 
 enum Epi { EPI_RELU = 0, EPI_LOGIT = 1, EPI_BWD = 2 };
@@ -135,195 +145,247 @@ __global__ __launch_bounds__(NTC) void conv_kernel(const uint16_t* __restrict__ 
 }
 
 // ------------------------------------------------------------ fused forward
-// The whole network over tiles of FT rows, for inference. Tiles follow the
-// series: tile f of series s starts at its row f FT (slot row s SR + 2 + f FT),
-// for f < ceil(K / FT), so no tile is spent on a slot's padding, and a tile
-// writes the logits of its own series' rows only (the padding's logits are
-// never read). A tile's frame is its FT rows plus FH = 8 halo rows on each
-// side (2 per layer): frame row f is slot row r0 - FH + f. Every layer
-// computes all FR = FT + 16 frame rows (nine 16-row MFMA blocks); the rows
-// within 2l of the frame's ends are wrong after layer l (their inputs fall off
-// the frame) but never reach the rows [FH, FH + FT) whose logits are written. Activations stay in LDS as bf16,
-// zeroed on rows outside their series exactly as the per-layer kernels write
-// them, and each output accumulates over j in the per-layer kernels' order
-// (same MFMA steps, bias added last). Wave w owns output channels 16w .. 16w + 15
-// of layers 0..2 and keeps their weights in registers for the whole launch.
-constexpr int FT = 128;
-constexpr int FH = 8;
-constexpr int FR = FT + 2 * FH;  // 144
-constexpr int FBLK = FR / 16;    // 9 row blocks
-constexpr int FST = 64 + 8;      // LDS row stride of a 64-channel activation buffer (bf16)
-constexpr int FXS = 16 + 8;      // LDS row stride of the 16-channel input buffer
-constexpr int FW3 = 320 + 8;     // LDS row stride of the last layer's weights
+// The whole network over tiles of at most FT rows of one series. A K-row series
+// has ceil(K / FT) tiles of equal length (so that none is nearly empty), and a
+// tile computes only the 16-row blocks that its own rows need.
+//
+// What bounds it: with one 16-channel tile per wave every activation operand was
+// read from LDS by all four waves, 1 KB per 16-cycle MFMA and SIMD, twice what
+// LDS delivers; one wave now owns 32 output channels (its weights of layers 1
+// and 2 stay in registers, 160 of them, which leaves two waves per SIMD) and
+// half of the row blocks, so each operand read feeds two MFMAs. Weights are the
+// A operand and rows the B operand: a lane then holds four consecutive channels
+// of one row, stored as one 8-byte LDS write after two v_cvt_pk_bf16_f32 (the
+// other way round it held one channel of four rows: four 2-byte writes and the
+// rounding in integer code). Each output accumulates the same products in the
+// same MFMA steps, bias last, so logits are the same bits.
+//
+// Buffers hold bf16 rows: x row r is series row t0 - 8 + r, layer l's output
+// row r (l = 0, 1, 2) is series row t0 - 6 + 2 l + r and reads input rows
+// r .. r + 4; rows outside the series are zero (the convolutions' padding).
+// FT + 12 = 128 rows of layer 0 make eight blocks.
+constexpr int FT = 116;
+constexpr int FROWS = 16 * 8 + 4;  // buffer rows: eight blocks and the taps past them
+constexpr int FST = 64 + 8;        // LDS row stride of a 64-channel buffer (bf16)
+constexpr int FXS = 16 + 8;        // LDS row stride of the 16-channel input buffer
+constexpr int FW3 = 320 + 8;       // LDS row stride of the last layer's weights
+constexpr int FWGS = 2;            // workgroups per CU (registers)
 
 struct FusedSmem {
-  uint16_t act[2][(FR + 4) * FST];  // buffer row f + 2 holds frame row f; rows 0, 1, FR + 2, FR + 3 stay zero
-  uint16_t x[(FR + 4) * FXS];
-  uint16_t w3[2 * FW3];             // row 0: W3[0][j]; row 1: zeros (output channels 1..15)
-  uint64_t valid[4];                // bit f % 64 of word f / 64: frame row f lies inside a series
+  uint16_t act[2][FROWS * FST];
+  uint16_t x[FROWS * FXS];
+  uint16_t w3[2 * FW3];  // row 0: W3[0][j]; row 1: zeros (output channels 1..15)
+  float bias[3 * 64];
 };
 
-// Bits 4 b + e (b < FBLK, e < 4) of a lane's row mask: frame row 16 b + 4 kg + e
-// is valid (the rows whose outputs this lane holds in an MFMA result).
-__device__ __forceinline__ uint64_t fused_lane_rows(const uint64_t (&v)[3], uint32_t kg) {
-  uint64_t m = 0;
-#pragma unroll
-  for (int b = 0; b < FBLK; ++b) {
-    const int f0 = 16 * b;  // + 4 kg
-    const uint64_t word = v[f0 / 64];
-    m |= ((word >> ((f0 % 64) + 4 * kg)) & 0xFull) << (4 * b);
-  }
-  return m;
+// Two floats as bf16 bits, rounded to nearest even (v_cvt_pk_bf16_f32; the same
+// bits as f2bf for every number).
+__device__ __forceinline__ uint32_t pack_bf(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v{a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// One 64-output-channel layer over the frame for this wave's 16 channels:
-// out[f][16 w + m] = bf16(relu(b + sum_j W[16 w + m][j] in[f + k - 2][i])) on
-// valid rows, 0 elsewhere (j = k CIN + i).
-template <int CIN, int NQ>
-__device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in, int ist, const u32x4 (&B)[NQ],
-                                            float bias, uint16_t* __restrict__ out, uint64_t rows,
-                                            uint32_t w, uint32_t m, uint32_t kg) {
-  constexpr int J = KW * CIN;
+// Products of a CIN-channel kernel-5 layer for G row blocks 32 rows apart and
+// this wave's 32 output channels: in points at this lane's row of the first
+// block (tap 0), Wt holds W[o][32 q + 8 kg .. + 7] of its two channel tiles.
+template <int CIN, int NQ, int G>
+__device__ __forceinline__ void conv_blocks(const uint16_t* __restrict__ in, const u32x4 (&Wt)[NQ][2], uint32_t kg,
+                                            f32x4 (&acc)[G][2]) {
+  constexpr int ST = CIN == 64 ? FST : FXS;
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) acc[g][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // row operands one step ahead of the MFMAs; the scheduling barrier keeps the
+  // compiler from hoisting every step's loads (and their registers)
+  auto load = [&](int q, u32x4 (&x)[G]) {
+    const int j0 = q * 32 + (int)kg * 8;
+    const int k = CIN == 64 ? q / 2 : j0 / CIN, i0 = CIN == 64 ? (q & 1) * 32 + (int)kg * 8 : j0 % CIN;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      x[g] = (NQ * 32 <= KW * CIN || j0 < KW * CIN) ? *reinterpret_cast<const u32x4*>(&in[(32 * g + k) * ST + i0])
+                                                    : u32x4{0u, 0u, 0u, 0u};
+  };
+  u32x4 x0[G], x1[G];
+  load(0, x0);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    u32x4(&cur)[G] = (q & 1) ? x1 : x0;
+    u32x4(&nxt)[G] = (q & 1) ? x0 : x1;
+    if (q + 1 < NQ) load(q + 1, nxt);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) acc[g][n] = mfma16(Wt[q][n], cur[g], acc[g][n]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Calls run(tag<G>, first block) over a wave's nb <= 4 row blocks, at most GM
+// (4 or 2) at once.
+template <int GM, class Run>
+__device__ __forceinline__ void for_blocks(uint32_t nb, Run&& run) {
+  if (GM == 4 && nb == 4) {
+    run(std::integral_constant<int, GM>{}, 0u);
+  } else {
 #pragma unroll 1
-  for (int g = 0; g < FBLK; g += 3) {
-    f32x4 acc[3];
-#pragma unroll
-    for (int t = 0; t < 3; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // A operands one k-step ahead of the MFMAs; the scheduling barrier keeps
-    // the compiler from hoisting every step's loads (and their registers)
-    auto load_a = [&](int q, u32x4 (&a)[3]) {
-      const int j0 = q * 32 + (int)kg * 8;
-      const int k = j0 / CIN, i0 = j0 - k * CIN;
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        // frame row 16 (g + t) + m, tap k: buffer row 16 (g + t) + m + k
-        a[t] = (NQ * 32 <= J || j0 < J) ? *reinterpret_cast<const u32x4*>(&in[((g + t) * 16 + (int)m + k) * ist + i0])
-                                        : u32x4{0u, 0u, 0u, 0u};
-      }
-    };
-    u32x4 a0[3], a1[3];
-    load_a(0, a0);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      u32x4(&cur)[3] = (q & 1) ? a1 : a0;
-      u32x4(&nxt)[3] = (q & 1) ? a0 : a1;
-      if (q + 1 < NQ) load_a(q + 1, nxt);
-#pragma unroll
-      for (int t = 0; t < 3; ++t) acc[t] = mfma16(cur[t], B[q], acc[t]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int f = (g + t) * 16 + (int)kg * 4 + e;
-        const bool v = (rows >> (4 * (g + t) + e)) & 1u;
-        out[(f + 2) * FST + w * 16 + m] = v ? f2bf(relu(acc[t][e] + bias)) : (uint16_t)0;
-      }
+    for (uint32_t b = 0; b + 2 <= nb; b += 2) run(std::integral_constant<int, 2>{}, b);
+    if (nb & 1) run(std::integral_constant<int, 1>{}, nb - 1);
   }
 }
 
-// x0 [rows][16] bf16 (channels 11..15 zero), wf[l] as for conv_kernel,
-// logits [rows] fp32 (0 on rows outside every series).
-__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(3))) void fused_forward_kernel(const uint16_t* __restrict__ x0, uint64_t rows,
-                                                            uint32_t SR, const uint32_t* __restrict__ Ks,
-                                                            uint32_t num_series, uint32_t tiles_per_series,
-                                                            const uint16_t* __restrict__ w0,
-                                                            const uint16_t* __restrict__ w1,
-                                                            const uint16_t* __restrict__ w2,
-                                                            const uint16_t* __restrict__ w3,
-                                                            const float* __restrict__ b0, const float* __restrict__ b1,
-                                                            const float* __restrict__ b2, const float* __restrict__ b3,
-                                                            float* __restrict__ logits) {
+// One layer with 64 output channels over nb row blocks for this wave's 32
+// channels: out row r = bf16(relu(b + products)) where series row tb + r is in
+// [0, K), else 0.
+template <int CIN, int NQ>
+__device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in, const u32x4 (&Wt)[NQ][2],
+                                            const float* __restrict__ bias, uint16_t* __restrict__ out, int32_t tb,
+                                            uint32_t K, uint32_t nb, uint32_t rh, uint32_t ch, uint32_t m,
+                                            uint32_t kg) {
+  constexpr int ST = CIN == 64 ? FST : FXS;
+  // layer 0's weights are not kept: two blocks at a time leave them room
+  for_blocks<CIN == 64 ? 4 : 2>((nb + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
+    constexpr int G = decltype(tag)::value;
+    const uint32_t r0 = 32 * b0 + 16 * rh + m;  // blocks rh, rh + 2, ...
+    f32x4 acc[G][2];
+    conv_blocks<CIN, NQ, G>(in + r0 * ST, Wt, kg, acc);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const f32x4 bv = *reinterpret_cast<const f32x4*>(&bias[ch + 16 * n + 4 * kg]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const uint32_t r = r0 + 32 * g;
+        const bool v = (uint32_t)(tb + (int32_t)r) < K;
+        const f32x4 y = acc[g][n] + bv;
+        const uint32_t lo = pack_bf(relu(y[0]), relu(y[1])), hi = pack_bf(relu(y[2]), relu(y[3]));
+        *reinterpret_cast<uint2*>(&out[r * FST + ch + 16 * n + 4 * kg]) = v ? make_uint2(lo, hi) : make_uint2(0u, 0u);
+      }
+    }
+  });
+}
+
+struct ForwardArgs {
+  // input: slot rows x0 [rows][16] bf16 with each series' K in Ks, or (feat
+  // given) the caller's features with K from the descriptors
+  const uint16_t* x0;
+  uint32_t* Ks;
+  const float* feat;
+  uint64_t feat_rows;
+  const ks_desc* desc;
+  uint32_t max_K, SR, num_series, tiles_per_series;
+  const uint16_t* w[4];
+  const float* b[4];
+  float* logits;  // slot rows, or
+  float* out;     // the caller's rows aux_offset + t (series that fit in out_rows)
+  uint64_t out_rows;
+};
+
+// K of series s under the caller's descriptor, 0 where it is skipped.
+__device__ __forceinline__ uint32_t feature_K(const ks_desc& d, uint32_t max_K, uint64_t feat_rows) {
+  return d.K >= 2 && d.K <= max_K && d.aux_offset <= feat_rows && d.K <= feat_rows - d.aux_offset ? d.K : 0u;
+}
+
+template <bool FEAT>
+__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS))) void fused_forward_kernel(ForwardArgs A) {
   __shared__ __align__(16) FusedSmem sm;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t m = lane & 15u, kg = lane >> 4;
-  const uint32_t o = w * 16 + m;
-  // B operands of this wave's channels: W[o][32 q + 8 kg .. + 7]; layers 1 and
-  // 2 stay in registers, layer 0's (three k-steps) are read again per tile
-  u32x4 B1[10], B2[10];
+  const uint32_t ch = 32 * (w & 1u), rh = w >> 1;  // this wave's channels and row blocks
+  u32x4 W1[10][2], W2[10][2];
 #pragma unroll
-  for (int q = 0; q < 10; ++q) {
-    B1[q] = *reinterpret_cast<const u32x4*>(w1 + o * 320 + q * 32 + kg * 8);
-    B2[q] = *reinterpret_cast<const u32x4*>(w2 + o * 320 + q * 32 + kg * 8);
-  }
-  const float bias0 = b0[o], bias1 = b1[o], bias2 = b2[o], bias3 = b3[0];
-  for (uint32_t q = tid; q < 2u * FW3; q += NTC) sm.w3[q] = q < 320u ? w3[q] : (uint16_t)0;
-  for (uint32_t q = tid; q < 4u * FST; q += NTC) {
-    const uint32_t r = q / FST, c = q - r * FST, br = r < 2 ? r : FR + r;
-    sm.act[0][br * FST + c] = 0;
-    sm.act[1][br * FST + c] = 0;
-  }
-  for (uint32_t q = tid; q < 4u * FXS; q += NTC) {
-    const uint32_t r = q / FXS, c = q - r * FXS, br = r < 2 ? r : FR + r;
-    sm.x[br * FXS + c] = 0;
-  }
-  const uint64_t ntiles = (uint64_t)num_series * tiles_per_series;
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint32_t ser = (uint32_t)(tile / tiles_per_series);
-    const uint32_t t0 = (uint32_t)(tile - (uint64_t)ser * tiles_per_series) * FT;  // the tile's first row in its series
-    const uint32_t K = Ks[ser];
-    if (t0 >= K) continue;  // past the series' last row (block-uniform)
-    const uint64_t sbase = (uint64_t)ser * SR + 2;
-    const int64_t r0 = (int64_t)(sbase + t0);
-    __syncthreads();
-    // frame row f = tid (FR <= NTC): its validity as one bit per row, by ballot
-    const int64_t vrow = r0 - FH + (int64_t)tid;
-    const bool v = tid < (uint32_t)FR && vrow >= 0 && row_valid((uint64_t)vrow, rows, SR, Ks);
-    const uint64_t vb = ballot(v);
-    if (lane == 0) sm.valid[w] = vb;  // read after the barrier below
-    for (uint32_t q = tid; q < 2u * FR; q += NTC) {
-      const uint32_t f = q >> 1, h = q & 1u;
-      const int64_t row = r0 - FH + (int64_t)f;
-      u32x4 v = u32x4{0u, 0u, 0u, 0u};
-      if (row >= 0 && (uint64_t)row < rows) v = *reinterpret_cast<const u32x4*>(x0 + (uint64_t)row * 16 + h * 8);
-      *reinterpret_cast<u32x4*>(&sm.x[(f + 2) * FXS + h * 8]) = v;
+  for (int q = 0; q < 10; ++q)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const uint32_t at = (ch + 16 * n + m) * 320 + q * 32 + kg * 8;
+      W1[q][n] = *reinterpret_cast<const u32x4*>(A.w[1] + at);
+      W2[q][n] = *reinterpret_cast<const u32x4*>(A.w[2] + at);
     }
+  for (uint32_t q = tid; q < 2u * FW3; q += NTC) sm.w3[q] = q < 320u ? A.w[3][q] : (uint16_t)0;
+  if (tid < 192u) sm.bias[tid] = A.b[tid / 64u][tid % 64u];
+  const float bias3 = A.b[3][0];
+  const uint64_t ntiles = (uint64_t)A.num_series * A.tiles_per_series;
+  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t ser = (uint32_t)(tile / A.tiles_per_series), f = (uint32_t)(tile - (uint64_t)ser * A.tiles_per_series);
+    ks_desc d;
+    uint32_t K;
+    if constexpr (FEAT) {
+      d = A.desc[ser];
+      K = feature_K(d, A.max_K, A.feat_rows);
+    } else {
+      K = A.Ks[ser];
+    }
+    const uint32_t nt = (K + FT - 1) / FT;
+    if (f >= nt) continue;  // block-uniform
+    const uint32_t len = (K + nt - 1) / nt, t0 = f * len, T = min(len, K - t0);
+    const uint64_t base = (uint64_t)ser * A.SR + 2;
     __syncthreads();
-    const uint64_t vw[3] = {sm.valid[0], sm.valid[1], sm.valid[2]};
-    const uint64_t lrows = fused_lane_rows(vw, kg);
-    u32x4 B0[3];
-    {
-      const uint16_t* w0p = w0;
-      asm volatile("" : "+v"(w0p));  // read per tile: keeps the compiler from pinning B0 in registers
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int j0 = q * 32 + (int)kg * 8;
-        B0[q] = j0 < 80 ? *reinterpret_cast<const u32x4*>(w0p + o * 80 + j0) : u32x4{0u, 0u, 0u, 0u};
+    if constexpr (FEAT) {  // one row per thread: nine features and the two position channels
+      static_assert(FT + 16 <= NTC, "a thread per input row");
+      if (tid < T + 16) {
+        const int32_t t = (int32_t)(t0 + tid) - 8;
+        u32x4 lo{0u, 0u, 0u, 0u}, hi{0u, 0u, 0u, 0u};
+        if ((uint32_t)t < K) {
+          const float* p = A.feat + (d.aux_offset + (uint32_t)t) * 9;
+          lo = u32x4{pack_bf(p[0], p[1]), pack_bf(p[2], p[3]), pack_bf(p[4], p[5]), pack_bf(p[6], p[7])};
+          hi = u32x4{pack_bf(p[8], pos_frac((uint32_t)t, K)), pack_bf(pos_centre((uint32_t)t, K), 0.0f), 0u, 0u};
+        }
+        *reinterpret_cast<u32x4*>(&sm.x[tid * FXS]) = lo;
+        *reinterpret_cast<u32x4*>(&sm.x[tid * FXS + 8]) = hi;
+      }
+    } else {
+      for (uint32_t q = tid; q < 2u * (T + 16); q += NTC) {
+        const uint32_t r = q >> 1, h = q & 1u;
+        const int32_t t = (int32_t)(t0 + r) - 8;
+        u32x4 v{0u, 0u, 0u, 0u};
+        if ((uint32_t)t < K) v = *reinterpret_cast<const u32x4*>(A.x0 + (base + (uint32_t)t) * 16 + h * 8);
+        *reinterpret_cast<u32x4*>(&sm.x[r * FXS + h * 8]) = v;
       }
     }
-    fused_layer<16, 3>(sm.x, FXS, B0, bias0, sm.act[0], lrows, w, m, kg);
     __syncthreads();
-    fused_layer<64, 10>(sm.act[0], FST, B1, bias1, sm.act[1], lrows, w, m, kg);
+    const int32_t tb = (int32_t)t0 - 6;
+    {
+      u32x4 W0[3][2];
+      const uint16_t* w0p = A.w[0];
+      asm volatile("" : "+v"(w0p));  // read per tile: keeps the compiler from pinning W0 in registers
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const int j0 = q * 32 + (int)kg * 8;
+          W0[q][n] = j0 < 80 ? *reinterpret_cast<const u32x4*>(w0p + (ch + 16 * n + m) * 80 + j0) : u32x4{0u, 0u, 0u, 0u};
+        }
+      fused_layer<16, 3>(sm.x, W0, sm.bias, sm.act[0], tb, K, (T + 12 + 15) / 16, rh, ch, m, kg);
+    }
     __syncthreads();
-    fused_layer<64, 10>(sm.act[1], FST, B2, bias2, sm.act[0], lrows, w, m, kg);
+    fused_layer<64, 10>(sm.act[0], W1, sm.bias + 64, sm.act[1], tb + 2, K, (T + 8 + 15) / 16, rh, ch, m, kg);
     __syncthreads();
-    // last layer (one output channel): wave w takes row blocks w, w + 4, w + 8
-    const uint16_t* w3row = &sm.w3[m == 0 ? 0 : FW3];
-    for (int blk = (int)w; blk < FBLK; blk += 4) {
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-      auto load_ab = [&](int q, u32x4& a, u32x4& b) {
-        const int j0 = q * 32 + (int)kg * 8;
-        const int k = j0 / 64, i0 = j0 - k * 64;
-        a = *reinterpret_cast<const u32x4*>(&sm.act[0][(blk * 16 + (int)m + k) * FST + i0]);
-        b = *reinterpret_cast<const u32x4*>(&w3row[j0]);
-      };
-      u32x4 a0, b0, a1, b1;
-      load_ab(0, a0, b0);
+    fused_layer<64, 10>(sm.act[1], W2, sm.bias + 128, sm.act[0], tb + 4, K, (T + 4 + 15) / 16, rh, ch, m, kg);
+    __syncthreads();
+    // last layer (one output channel, of 16): wave w takes row blocks w and w + 4
+    const uint32_t nb = (T + 15) / 16;
+    if (w < nb) {
+      const uint16_t* w3row = &sm.w3[m == 0 ? 0 : FW3];
+      const bool two = w + 4 < nb;
+      const uint16_t* in = &sm.act[0][(16 * w + m) * FST];
+      f32x4 acc[2];
+      acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int q = 0; q < 10; ++q) {
-        u32x4& ca = (q & 1) ? a1 : a0;
-        u32x4& cb = (q & 1) ? b1 : b0;
-        if (q + 1 < 10) load_ab(q + 1, (q & 1) ? a0 : a1, (q & 1) ? b0 : b1);
-        acc = mfma16(ca, cb, acc);
-        __builtin_amdgcn_sched_barrier(0);
+        const int at = (q / 2) * FST + (q & 1) * 32 + (int)kg * 8;
+        const u32x4 a = *reinterpret_cast<const u32x4*>(&w3row[q * 32 + kg * 8]);
+        acc[0] = mfma16(a, *reinterpret_cast<const u32x4*>(&in[at]), acc[0]);
+        if (two) acc[1] = mfma16(a, *reinterpret_cast<const u32x4*>(&in[at + 64 * FST]), acc[1]);
       }
-      if (m == 0) {
+      if (kg == 0) {  // channel 0 of row m of each block
+        float* dst = A.logits + base;
+        if (FEAT && A.out)
+          dst = d.aux_offset <= A.out_rows && K <= A.out_rows - d.aux_offset ? A.out + d.aux_offset : nullptr;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int f = blk * 16 + (int)kg * 4 + e;
-          const int64_t row = r0 - FH + f;
-          if (f >= FH && f < FH + FT && (uint64_t)row - sbase < K) logits[row] = acc[e] + bias3;
+        for (int g = 0; g < 2; ++g) {
+          const uint32_t r = 16 * w + 64 * g + m;
+          if (r < T && dst) dst[t0 + r] = acc[g][0] + bias3;
         }
       }
     }
@@ -441,14 +503,6 @@ __device__ __host__ inline Layer layer_info(int l) {
   }
 }
 constexpr uint32_t kNumParams = 44993;
-
-// Position channels of row t of a K-row series (double, rounded to float).
-__device__ __forceinline__ float pos_frac(uint32_t t, uint32_t K) {
-  return (float)((double)t / (double)(K > 1 ? K - 1 : 1));
-}
-__device__ __forceinline__ float pos_centre(uint32_t t, uint32_t K) {
-  return (float)(4.0 * (double)t * (double)(K - t) / ((double)K * (double)K));
-}
 
 // Entries of all shadow copies (forward weights and biases of every layer).
 constexpr uint32_t kShadowEntries = (64 * 5 * 16 + 64) + 2 * (64 * 5 * 64 + 64) + (16 * 5 * 64 + 16);
@@ -756,19 +810,6 @@ __global__ __launch_bounds__(NTC) void trace_copy_kernel(const ks_desc* __restri
     else v = dyf2[row * 64 + (c - 129)];
     gin[(d.aux_offset + t) * NG + c] = v;
   }
-}
-
-// Logits in the slot layout -> caller rows (aux_offset + t), nullable output.
-__global__ __launch_bounds__(NTC) void unpack_logits_kernel(const float* __restrict__ lg, const ks_desc* __restrict__ desc,
-                                                            uint32_t num_series, uint32_t SR,
-                                                            const uint32_t* __restrict__ Ks, float* __restrict__ out,
-                                                            uint64_t out_rows) {
-  const uint32_t s = blockIdx.x;
-  if (s >= num_series) return;
-  const ks_desc d = desc[s];
-  const uint32_t K = Ks[s];
-  if (!(d.aux_offset <= out_rows && K <= out_rows - d.aux_offset)) return;
-  for (uint32_t t = threadIdx.x; t < K; t += NTC) out[d.aux_offset + t] = lg[(uint64_t)s * SR + 2 + t];
 }
 
 }  // namespace cnn

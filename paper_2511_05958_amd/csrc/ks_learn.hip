@@ -101,16 +101,29 @@ hipError_t forward(ks_ctx* c, const ks_model* m, uint64_t rows, uint32_t SR, hip
   return hipGetLastError();
 }
 
-// Inference: the whole network in one launch, activations kept in LDS.
-hipError_t forward_infer(ks_ctx* c, const ks_model* m, uint64_t rows, uint32_t SR, hipStream_t st) {
+C::ForwardArgs forward_args(ks_ctx* c, const ks_model* m, uint32_t num_series, uint32_t SR, uint32_t max_K) {
   LearnBuffers& b = c->learn;
-  const uint32_t num_series = (uint32_t)(rows / SR);
-  const uint32_t per = (SR - 4 + C::FT - 1) / C::FT;  // tiles covering a slot's K <= SR - 4 rows
-  const uint64_t tiles = (uint64_t)num_series * per;
-  const uint64_t cap = (uint64_t)c->num_cus * 3;  // three 51 KB workgroups per CU
-  const uint32_t g = (uint32_t)(tiles < cap ? (tiles ? tiles : 1) : cap);
-  hipLaunchKernelGGL(C::fused_forward_kernel, dim3(g), dim3(C::NTC), 0, st, b.x0, rows, SR, b.K, num_series, per,
-                     m->wf[0], m->wf[1], m->wf[2], m->wf[3], m->b[0], m->b[1], m->b[2], m->b[3], b.logits);
+  C::ForwardArgs A{};
+  A.x0 = b.x0;
+  A.Ks = b.K;
+  A.max_K = max_K;
+  A.SR = SR;
+  A.num_series = num_series;
+  A.tiles_per_series = (max_K + C::FT - 1) / C::FT;
+  for (int l = 0; l < 4; ++l) {
+    A.w[l] = m->wf[l];
+    A.b[l] = m->b[l];
+  }
+  A.logits = b.logits;
+  return A;
+}
+
+// The whole network in one launch, activations kept in LDS: persistent
+// workgroups, as many as are resident.
+template <bool FEAT>
+hipError_t forward_infer(ks_ctx* c, const C::ForwardArgs& A, hipStream_t st) {
+  const uint64_t tiles = (uint64_t)A.num_series * A.tiles_per_series, cap = (uint64_t)c->num_cus * C::FWGS;
+  hipLaunchKernelGGL(C::fused_forward_kernel<FEAT>, dim3((uint32_t)(tiles < cap ? tiles : cap)), dim3(C::NTC), 0, st, A);
   return hipGetLastError();
 }
 
@@ -405,20 +418,14 @@ int ks_cnn_forward(ks_ctx* ctx, const ks_model* model, const float* features, ui
   if (!features || !logits) return KS_E_INVALID;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  const uint32_t SR = slot_rows(max_K);
-  const uint64_t rows = (uint64_t)num_series * SR;
-  if (int rc = ensure_learn(ctx, rows, num_series, false)) return rc;
-  hipStream_t st = (hipStream_t)stream;
-  LearnBuffers& b = ctx->learn;
-  b.stamp_valid = false;  // the slot buffers no longer hold a proposal pass
-  hipLaunchKernelGGL(C::pack_features_kernel, dim3(num_series), dim3(C::NTC), 0, st, features, feature_rows, desc,
-                     num_series, max_K, SR, b.x0, b.K);
-  hipError_t e = forward_infer(ctx, model, rows, SR, st);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(C::unpack_logits_kernel, dim3(num_series), dim3(C::NTC), 0, st, b.logits, desc, num_series,
-                       SR, b.K, logits, logit_rows);
-    e = hipGetLastError();
-  }
+  ctx->learn.stamp_valid = false;  // a refine after this call needs its own proposal pass
+  C::ForwardArgs A = forward_args(ctx, model, num_series, slot_rows(max_K), max_K);
+  A.feat = features;
+  A.feat_rows = feature_rows;
+  A.desc = desc;
+  A.out = logits;
+  A.out_rows = logit_rows;
+  const hipError_t e = forward_infer<true>(ctx, A, (hipStream_t)stream);
   return e == hipSuccess ? KS_OK : hip_fail(e, "cnn forward");
 }
 
@@ -443,7 +450,7 @@ int ks_propose(ks_ctx* ctx, const ks_model* model, const uint32_t* samples, uint
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? KS_OK : hip_fail(e, "propose");
   }
-  hipError_t e = forward_infer(ctx, model, (uint64_t)num_series * SR, SR, st);
+  hipError_t e = forward_infer<false>(ctx, forward_args(ctx, model, num_series, SR, max_K), st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(C::softmax_kernel, dim3((num_series + per - 1) / per), dim3(C::NTC), 0, st, b.logits,
                        num_series, SR, b.K, (const int32_t*)nullptr, (const uint32_t*)nullptr, (float*)nullptr,
