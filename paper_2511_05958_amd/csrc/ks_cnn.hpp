@@ -2,17 +2,15 @@
 // accumulation, the weight-gradient reduction, softmax cross-entropy, the
 // proposal (argmax + window mass) and Adam.
 //
-// Row layout. A batch of B series is one long sequence of B * SR rows
-// (SR = roundup(max_K + 4, 16)); series s owns rows [s SR + 2, s SR + 2 + K_s)
-// and every other row of its slot is kept zero, so the zero padding of each
-// kernel-5 convolution at the series' ends is simply the neighbouring zero
-// rows and every layer is one convolution over the whole sequence.
+// Row layout. Series s owns rows [s SR + 2, s SR + 2 + K_s) of the row buffers
+// (SR = roundup(max_K + 4, 16)); kernels mask rows outside the series, the zero
+// padding of the kernel-5 convolutions.
 //
 // A layer y[t][o] = b[o] + sum_{k<5, i<CIN} W[o][i][k] x[t + k - 2][i] is an
-// implicit GEMM with M = rows (16 per MFMA tile), N = output channels and
+// implicit GEMM with M = output channels (16 per MFMA tile), N = rows (16) and
 // reduction index j = k * CIN + i (32 per v_mfma_f32_16x16x32_bf16). The
 // input gradient of a layer is the same convolution of the output gradient
-// with W'[i][o][k] = W[o][i][4 - k], so one kernel serves both directions.
+// with W'[i][o][k] = W[o][i][4 - k].
 #pragma once
 
 #include <type_traits>
@@ -27,7 +25,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KW = 5;
-constexpr int TM = 64;   // rows per tile: four waves of 16
 constexpr int NTC = 256;
 
 // float -> bfloat16 bits, round to nearest even (finite inputs)
@@ -37,14 +34,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 
 __device__ __forceinline__ float relu(float v) { return v > 0.0f ? v : 0.0f; }
-
-// Row `row` holds data iff it lies inside its series' rows.
-__device__ __forceinline__ bool row_valid(uint64_t row, uint64_t rows, uint32_t SR, const uint32_t* __restrict__ Ks) {
-  if (row >= rows) return false;
-  const uint64_t s = row / SR;
-  const uint32_t r = (uint32_t)(row - s * SR);
-  return r >= 2 && r - 2 < Ks[s];
-}
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
@@ -57,91 +46,6 @@ __device__ __forceinline__ float pos_frac(uint32_t t, uint32_t K) {
 }
 __device__ __forceinline__ float pos_centre(uint32_t t, uint32_t K) {
   return (float)(4.0 * (double)t * (double)(K - t) / ((double)K * (double)K));
-}
-
-enum Epi { EPI_RELU = 0, EPI_LOGIT = 1, EPI_BWD = 2 };
-
-template <int CIN, int COUT>
-struct ConvShape {
-  static constexpr int J = KW * CIN;             // reduction length
-  static constexpr int JP = (J + 31) / 32 * 32;  // padded to whole MFMA steps
-  static constexpr int WST = JP + 8;             // LDS row stride of weights (bf16)
-  static constexpr int XST = CIN + 8;            // LDS row stride of the input tile
-  static constexpr int XR = TM + 4;              // input rows per tile (2-row halo each side)
-  static constexpr int NQ = JP / 32;
-  static constexpr int NN = COUT / 16;
-};
-
-// One convolution over `rows` rows.
-//   X     [rows][CIN]  bf16 input
-//   Wg    [COUT][5 CIN] bf16 weights, j = k CIN + i
-//   bias  [COUT] fp32 (EPI_RELU / EPI_LOGIT)
-//   EPI_RELU   Y[row][o] = bf16(relu(acc + b)) on valid rows, 0 elsewhere
-//   EPI_LOGIT  Yf[row]   = acc[o=0] + b[0] on valid rows, 0 elsewhere
-//   EPI_BWD    d = acc where Mask[row][o] != 0 (the layer input was > 0) and the
-//              row is valid, else 0: Y[row][o] = bf16(d), Yf[row][o] = d
-template <int CIN, int COUT, int EPI>
-__global__ __launch_bounds__(NTC) void conv_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wg,
-                                                   const float* __restrict__ bias, uint64_t rows, uint32_t SR,
-                                                   const uint32_t* __restrict__ Ks, uint16_t* __restrict__ Y,
-                                                   float* __restrict__ Yf, const uint16_t* __restrict__ Mask) {
-  using S = ConvShape<CIN, COUT>;
-  __shared__ __align__(16) uint16_t wl[COUT * S::WST];
-  __shared__ __align__(16) uint16_t xl[S::XR * S::XST];
-  const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
-  for (uint32_t q = tid; q < (uint32_t)(COUT * S::JP); q += NTC) {
-    const uint32_t o = q / S::JP, j = q - o * S::JP;
-    wl[o * S::WST + j] = j < (uint32_t)S::J ? Wg[o * S::J + j] : (uint16_t)0;
-  }
-  const uint32_t m = lane & 15u, kg = lane >> 4;
-  const uint64_t ntiles = (rows + TM - 1) / TM;
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t r0 = (int64_t)(tile * TM);
-    __syncthreads();
-    for (uint32_t q = tid; q < (uint32_t)(S::XR * CIN); q += NTC) {
-      const uint32_t rr = q / CIN, i = q - rr * CIN;
-      const int64_t row = r0 - 2 + (int64_t)rr;
-      xl[rr * S::XST + i] = (row >= 0 && (uint64_t)row < rows) ? X[(uint64_t)row * CIN + i] : (uint16_t)0;
-    }
-    __syncthreads();
-    f32x4 acc[S::NN];
-#pragma unroll
-    for (int n = 0; n < S::NN; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < S::NQ; ++q) {
-      const int j0 = q * 32 + (int)kg * 8;
-      u32x4 a = u32x4{0u, 0u, 0u, 0u};
-      if (j0 < S::J) {
-        const int k = j0 / CIN, i0 = j0 - k * CIN;
-        // tile row w*16 + m sits at xl row w*16 + m + 2; tap k reads row + k - 2
-        a = *reinterpret_cast<const u32x4*>(&xl[(w * 16 + m + k) * S::XST + i0]);
-      }
-#pragma unroll
-      for (int n = 0; n < S::NN; ++n) {
-        const u32x4 b = *reinterpret_cast<const u32x4*>(&wl[(n * 16 + m) * S::WST + j0]);
-        acc[n] = mfma16(a, b, acc[n]);
-      }
-    }
-#pragma unroll
-    for (int n = 0; n < S::NN; ++n) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint64_t row = (uint64_t)r0 + w * 16 + kg * 4 + e;
-        if (row >= rows) continue;
-        const uint32_t o = n * 16 + m;
-        const bool valid = row_valid(row, rows, SR, Ks);
-        if (EPI == EPI_RELU) {
-          Y[row * COUT + o] = valid ? f2bf(relu(acc[n][e] + bias[o])) : (uint16_t)0;
-        } else if (EPI == EPI_LOGIT) {
-          if (o == 0) Yf[row] = valid ? acc[n][e] + bias[0] : 0.0f;
-        } else {
-          const float d = (valid && Mask[row * COUT + o] != 0) ? acc[n][e] : 0.0f;
-          Y[row * COUT + o] = f2bf(d);
-          Yf[row * COUT + o] = d;
-        }
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------ fused forward
@@ -176,6 +80,7 @@ struct FusedSmem {
   uint16_t x[FROWS * FXS];
   uint16_t w3[2 * FW3];  // row 0: W3[0][j]; row 1: zeros (output channels 1..15)
   float bias[3 * 64];
+  uint32_t count;
 };
 
 // Two floats as bf16 bits, rounded to nearest even (v_cvt_pk_bf16_f32; the same
@@ -280,6 +185,13 @@ struct ForwardArgs {
   float* logits;  // slot rows, or
   float* out;     // the caller's rows aux_offset + t (series that fit in out_rows)
   uint64_t out_rows;
+  // training: the input rows and activations kept for the backward pass (slot
+  // rows), each series' K written to Ks; the labels >= 1 counted into nsig and
+  // the loss cleared (labels given) by the first workgroup
+  uint16_t* keep[4];
+  const int32_t* labels;
+  uint32_t* nsig;
+  float* loss;
 };
 
 // K of series s under the caller's descriptor, 0 where it is skipped.
@@ -287,8 +199,9 @@ __device__ __forceinline__ uint32_t feature_K(const ks_desc& d, uint32_t max_K, 
   return d.K >= 2 && d.K <= max_K && d.aux_offset <= feat_rows && d.K <= feat_rows - d.aux_offset ? d.K : 0u;
 }
 
-template <bool FEAT>
+template <bool FEAT, bool TRAIN>
 __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS))) void fused_forward_kernel(ForwardArgs A) {
+  static_assert(FEAT || !TRAIN, "training starts from the caller's features");
   __shared__ __align__(16) FusedSmem sm;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t m = lane & 15u, kg = lane >> 4;
@@ -305,6 +218,18 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
   for (uint32_t q = tid; q < 2u * FW3; q += NTC) sm.w3[q] = q < 320u ? A.w[3][q] : (uint16_t)0;
   if (tid < 192u) sm.bias[tid] = A.b[tid / 64u][tid % 64u];
   const float bias3 = A.b[3][0];
+  if (TRAIN && A.labels && blockIdx.x == 0) {
+    if (tid == 0) sm.count = 0;
+    __syncthreads();
+    uint32_t local = 0;
+    for (uint32_t s = tid; s < A.num_series; s += NTC) local += A.labels[s] >= 1 ? 1u : 0u;
+    atomicAdd(&sm.count, local);
+    __syncthreads();
+    if (tid == 0) {
+      *A.nsig = sm.count;
+      *A.loss = 0.0f;
+    }
+  }
   const uint64_t ntiles = (uint64_t)A.num_series * A.tiles_per_series;
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const uint32_t ser = (uint32_t)(tile / A.tiles_per_series), f = (uint32_t)(tile - (uint64_t)ser * A.tiles_per_series);
@@ -316,10 +241,21 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
     } else {
       K = A.Ks[ser];
     }
+    if (TRAIN && f == 0 && tid == 0) A.Ks[ser] = K;
     const uint32_t nt = (K + FT - 1) / FT;
     if (f >= nt) continue;  // block-uniform
     const uint32_t len = (K + nt - 1) / nt, t0 = f * len, T = min(len, K - t0);
     const uint64_t base = (uint64_t)ser * A.SR + 2;
+    // the tile's own rows of a finished LDS buffer (from row `off`) to memory
+    auto keep = [&](int l, uint32_t off) {
+      if constexpr (TRAIN) {
+        const uint16_t* in = l == 0 ? sm.x : sm.act[(l + 1) & 1];
+        const uint32_t sh = l == 0 ? 1u : 3u, msk = (1u << sh) - 1u, st = l == 0 ? FXS : FST;
+        for (uint32_t q = tid; q < T << sh; q += NTC)
+          *reinterpret_cast<u32x4*>(A.keep[l] + (((base + t0) << sh) + q) * 8) =
+              *reinterpret_cast<const u32x4*>(&in[(off + (q >> sh)) * st + (q & msk) * 8]);
+      }
+    };
     __syncthreads();
     if constexpr (FEAT) {  // one row per thread: nine features and the two position channels
       static_assert(FT + 16 <= NTC, "a thread per input row");
@@ -344,6 +280,7 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
       }
     }
     __syncthreads();
+    keep(0, 8);
     const int32_t tb = (int32_t)t0 - 6;
     {
       u32x4 W0[3][2];
@@ -359,10 +296,13 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
       fused_layer<16, 3>(sm.x, W0, sm.bias, sm.act[0], tb, K, (T + 12 + 15) / 16, rh, ch, m, kg);
     }
     __syncthreads();
+    keep(1, 6);
     fused_layer<64, 10>(sm.act[0], W1, sm.bias + 64, sm.act[1], tb + 2, K, (T + 8 + 15) / 16, rh, ch, m, kg);
     __syncthreads();
+    keep(2, 4);
     fused_layer<64, 10>(sm.act[1], W2, sm.bias + 128, sm.act[0], tb + 4, K, (T + 4 + 15) / 16, rh, ch, m, kg);
     __syncthreads();
+    keep(3, 2);
     // last layer (one output channel, of 16): wave w takes row blocks w and w + 4
     const uint32_t nb = (T + 15) / 16;
     if (w < nb) {
@@ -392,97 +332,279 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
   }
 }
 
-// Weight gradient partials of one layer:
-//   dW[o][j] = sum_rows dY[row][o] X[row + k - 2][i]   (j = k CIN + i)
-//   db[o]    = sum_rows dYf[row][o]
-// as a GEMM with M = output channels, N = j, reduction over rows. Workgroup g
-// accumulates its tiles and writes part[g][o * J + j] and part[g][COUT*J + o].
-template <int CIN, int COUT>
-struct DwShape {
-  static constexpr int J = KW * CIN;
-  static constexpr int NM = COUT / 16;
-  static constexpr int NJ = J / 16;
-  static constexpr int TILES = NM * NJ;
-  static constexpr int PER_WAVE = (TILES + 3) / 4;
-  static constexpr int YST = TM + 8;   // LDS stride of dY^T rows (bf16)
-  static constexpr int XST = TM + 12;  // LDS stride of X^T rows (bf16): TM + 4 halo + pad
-  static constexpr int PART = COUT * J + COUT;
+// ------------------------------------------------------------ fused backward
+// The input gradients of layers 3, 2, 1 over tiles of at most BT rows of one
+// series, on the forward's plan (32 channels and half of the row blocks per
+// wave, both 64-channel layers' flipped weights in registers): dz -> dy2 -> dy1
+// -> dy0, the gradients at the pre-activations, masked where the layer input
+// (a3, a2, a1) is 0 and zero outside the series. The LDS buffers hold bf16 rows
+// for the next layer; the fp32 values of the tile's own rows go to memory for
+// the weight and bias gradients. (A launch per layer with element-wise 2-byte
+// loads took 27 + 52 + 51 us on 69632 rows, this one 33.)
+//
+// dz row r is series row t0 - 6 + r; dy2, dy1, dy0 row r is t0 - 4 + r, t0 - 2 +
+// r, t0 + r. BT + 8 = 128 rows of dy2 make eight blocks.
+constexpr int BT = 120;
+
+struct BackSmem {
+  uint16_t dy[2][FROWS * FST];
+  uint16_t dz[FROWS + 4];
+  uint16_t w3[64 * 8];    // flipped taps of layer 3: [input channel][tap]
 };
 
-template <int CIN, int COUT>
-__global__ __launch_bounds__(NTC) void dw_kernel(const uint16_t* __restrict__ dY, const float* __restrict__ dYf,
-                                                 const uint16_t* __restrict__ X, uint64_t rows,
-                                                 float* __restrict__ part) {
-  using S = DwShape<CIN, COUT>;
-  __shared__ __align__(16) uint16_t yt[COUT * S::YST];
-  __shared__ __align__(16) uint16_t xt[CIN * S::XST];
+struct BackwardArgs {
+  const float* dz;  // slot rows
+  const uint32_t* Ks;
+  uint32_t SR, num_series, tiles_per_series;
+  const uint16_t* a[3];   // a3, a2, a1, slot rows
+  const uint16_t* wb[3];  // layers 3, 2, 1: [cin][5 cout_pad], taps flipped
+  float* dy[3];           // dy2, dy1, dy0, slot rows
+};
+
+__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS))) void fused_backward_kernel(BackwardArgs A) {
+  __shared__ __align__(16) BackSmem sm;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t m = lane & 15u, kg = lane >> 4;
-  f32x4 acc[S::PER_WAVE];
+  const uint32_t ch = 32 * (w & 1u), rh = w >> 1;
+  u32x4 W2[10][2], W1[10][2];
 #pragma unroll
-  for (int t = 0; t < S::PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float db = 0.0f;  // thread tid < COUT: bias gradient of channel tid
-  const uint64_t ntiles = (rows + TM - 1) / TM;
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t r0 = (int64_t)(tile * TM);
-    __syncthreads();
-    for (uint32_t q = tid; q < (uint32_t)(TM * COUT); q += NTC) {
-      const uint32_t rr = q / COUT, o = q - rr * COUT;
-      const uint64_t row = (uint64_t)r0 + rr;
-      yt[o * S::YST + rr] = row < rows ? dY[row * COUT + o] : (uint16_t)0;
+  for (int q = 0; q < 10; ++q)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const uint32_t at = (ch + 16 * n + m) * 320 + q * 32 + kg * 8;
+      W2[q][n] = *reinterpret_cast<const u32x4*>(A.wb[1] + at);
+      W1[q][n] = *reinterpret_cast<const u32x4*>(A.wb[2] + at);
     }
-    for (uint32_t q = tid; q < (uint32_t)((TM + 4) * CIN); q += NTC) {
-      const uint32_t rr = q / CIN, i = q - rr * CIN;
-      const int64_t row = r0 - 2 + (int64_t)rr;
-      xt[i * S::XST + rr] = (row >= 0 && (uint64_t)row < rows) ? X[(uint64_t)row * CIN + i] : (uint16_t)0;
-    }
-    if (tid < (uint32_t)COUT)
-      for (uint32_t rr = 0; rr < (uint32_t)TM; ++rr) {
-        const uint64_t row = (uint64_t)r0 + rr;
-        if (row < rows) db += dYf[row * COUT + tid];
+  for (uint32_t q = tid; q < 64u * 8u; q += NTC) sm.w3[q] = (q & 7u) < 5u ? A.wb[0][(q >> 3) * 80 + (q & 7u) * 16] : (uint16_t)0;
+  const uint32_t ntiles = A.num_series * A.tiles_per_series;
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t ser = tile / A.tiles_per_series, f = tile - ser * A.tiles_per_series;
+    const uint32_t K = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.Ks[ser]);
+    const uint32_t nt = (K + BT - 1) / BT;
+    if (f >= nt) continue;  // block-uniform
+    const uint32_t len = (K + nt - 1) / nt, t0 = f * len, T = min(len, K - t0);
+    const uint64_t base = (uint64_t)ser * A.SR + 2;
+    // masks one layer's products and stores them as out rows; the tile's own
+    // rows (off .. off + T - 1) also in fp32
+    auto finish = [&](auto gtag, int l, const f32x4* acc, uint32_t r0, uint32_t off, uint16_t* out) {
+      constexpr int G = decltype(gtag)::value;
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const uint32_t c = ch + 16 * n + 4 * kg;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const uint32_t r = r0 + 32 * g;
+          const uint32_t t = t0 + r - off;  // wraps below row 0: not < K
+          const bool v = t < K;
+          const uint2 mk = v ? *reinterpret_cast<const uint2*>(A.a[l] + (base + t) * 64 + c) : make_uint2(0u, 0u);
+          f32x4 d = acc[g * 2 + n];
+          d[0] = (mk.x & 0xffffu) ? d[0] : 0.0f;
+          d[1] = (mk.x >> 16) ? d[1] : 0.0f;
+          d[2] = (mk.y & 0xffffu) ? d[2] : 0.0f;
+          d[3] = (mk.y >> 16) ? d[3] : 0.0f;
+          *reinterpret_cast<uint2*>(&out[r * FST + c]) = make_uint2(pack_bf(d[0], d[1]), pack_bf(d[2], d[3]));
+          if (v && r >= off && r < off + T) *reinterpret_cast<f32x4*>(A.dy[l] + (base + t) * 64 + c) = d;
+        }
       }
+    };
+    auto layer = [&](int l, const u32x4 (&Wt)[10][2], const uint16_t* in, uint32_t rows, uint32_t off, uint16_t* out) {
+      for_blocks<4>(((rows + 15) / 16 + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
+        constexpr int G = decltype(tag)::value;
+        const uint32_t r0 = 32 * b0 + 16 * rh + m;
+        f32x4 acc[G][2];
+        conv_blocks<64, 10, G>(in + r0 * FST, Wt, kg, acc);
+        finish(tag, l, &acc[0][0], r0, off, out);
+      });
+    };
     __syncthreads();
-#pragma unroll
-    for (int t = 0; t < S::PER_WAVE; ++t) {
-      const int tt = w * S::PER_WAVE + t;
-      if (tt >= S::TILES) break;
-      const int mt = tt / S::NJ, nt = tt - mt * S::NJ;
-      const uint32_t o = mt * 16 + m;
-      const uint32_t j = nt * 16 + m;
-      const uint32_t k = j / CIN, i = j - k * CIN;
-#pragma unroll
-      for (int q = 0; q < TM / 32; ++q) {
-        const uint32_t rr = q * 32 + kg * 8;
-        const u32x4 a = *reinterpret_cast<const u32x4*>(&yt[o * S::YST + rr]);
-        // X[r0 + rr + e + k - 2] = xt[i][rr + e + k]: 8 bf16 at an odd offset when k is odd
-        uint32_t bw[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          bw[e] = (uint32_t)xt[i * S::XST + rr + k + 2 * e] | ((uint32_t)xt[i * S::XST + rr + k + 2 * e + 1] << 16);
-        acc[t] = mfma16(a, u32x4{bw[0], bw[1], bw[2], bw[3]}, acc[t]);
-      }
+    for (uint32_t r = tid; r < (uint32_t)FROWS + 4; r += NTC) {
+      const uint32_t t = t0 + r - 6;
+      sm.dz[r] = t < K && r < T + 12 ? f2bf(A.dz[base + t]) : (uint16_t)0;
     }
-  }
-  float* out = part + (uint64_t)blockIdx.x * S::PART;
+    __syncthreads();
+    // layer 3: one channel, so of each 32-deep step only the first element of
+    // lane groups 0 and 2 (taps 2 q and 2 q + 1) is not 0
+    for_blocks<4>(((T + 8 + 15) / 16 + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
+      constexpr int G = decltype(tag)::value;
+      const uint32_t r0 = 32 * b0 + 16 * rh + m;
+      f32x4 acc[G][2];
 #pragma unroll
-  for (int t = 0; t < S::PER_WAVE; ++t) {
-    const int tt = w * S::PER_WAVE + t;
-    if (tt >= S::TILES) break;
-    const int mt = tt / S::NJ, nt = tt - mt * S::NJ;
+      for (int q = 0; q < 3; ++q) {
+        const uint32_t k = 2 * q + (kg >> 1);
+        const bool on = (kg & 1u) == 0 && k < 5u;
+        u32x4 a[2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) out[(mt * 16 + kg * 4 + e) * S::J + nt * 16 + m] = acc[t][e];
+        for (int n = 0; n < 2; ++n) a[n] = u32x4{on ? (uint32_t)sm.w3[(ch + 16 * n + m) * 8 + k] : 0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const u32x4 x{on ? (uint32_t)sm.dz[r0 + 32 * g + k] : 0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int n = 0; n < 2; ++n) acc[g][n] = mfma16(a[n], x, q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[g][n]);
+        }
+      }
+      finish(tag, 0, &acc[0][0], r0, 4, sm.dy[0]);
+    });
+    __syncthreads();
+    layer(1, W2, sm.dy[0], T + 4, 2, sm.dy[1]);
+    __syncthreads();
+    layer(2, W1, sm.dy[1], T, 0, sm.dy[0]);
   }
-  if (tid < (uint32_t)COUT) out[COUT * S::J + tid] = db;
 }
 
-// grad[p] = sum over g < G of part[g][p], p < n.
-__global__ __launch_bounds__(NTC) void reduce_parts_kernel(const float* __restrict__ part, uint32_t G, uint32_t n,
-                                                           float* __restrict__ grad) {
-  const uint32_t p = blockIdx.x * NTC + threadIdx.x;
-  if (p >= n) return;
-  float s = 0.0f;
-  for (uint32_t g = 0; g < G; ++g) s += part[(uint64_t)g * n + p];
-  grad[p] = s;
+// ------------------------------------------------------------ weight gradients
+//   dW[o][k][i] = sum over rows t of bf16(dY[t][o]) X[t + k - 2][i],
+//   db[o] = sum over rows t of dY[t][o]
+// as GEMMs reduced over rows, one launch for the four layers (blockIdx.y).
+// Workgroup g takes the 64-row tiles g, g + G, ... of the slot rows and keeps its
+// sums in registers; the partials are added in the order of g by finish_kernel.
+// The order of every sum is fixed, whatever tile shape would be faster (weights
+// in 32-row matrix steps, biases row after row in fp32): the first Adam step of
+// a parameter is the sign of its gradient, so one whose gradient is within
+// rounding of 0 moves by 2 lr when any order changes, and b3's gradient is
+// nothing but the rounding of all the others (a softmax gradient sums to 0).
+// Both operands need eight consecutive rows of one channel per lane: the tiles
+// lie in LDS as they do in memory (rows of channels, whole 16-byte copies) and
+// ds_read_b64_tr_b16 reads them transposed, four rows by 16 channels per 16
+// lanes, at any row, so a tap is a row offset. (Transposed copies in LDS cost a
+// 2-byte write per element and eight 2-byte reads per operand and tap: 154 us
+// for a 64 x 64 layer of 69632 rows.) A wave takes 16 input channels, all 64
+// output channels and the five taps: 18 operand reads for 20 MFMAs. Rows 160
+// bytes apart put the four rows of a read on different banks.
+constexpr int DT = 64;         // rows per tile
+constexpr int DST = 64 + 16;   // LDS row stride (bf16)
+constexpr uint32_t kDwGrid = 256;  // workgroups (partials) per layer at most
+constexpr uint32_t kBiasPart = 224;  // bias partials per workgroup (193, padded)
+constexpr uint32_t kDwN0 = 5 * 64 * 16, kDwN1 = 5 * 64 * 64, kDwN3 = 5 * 64;
+constexpr uint32_t kDwPart = kDwN0 + 2 * kDwN1 + kDwN3;  // partial sums of a workgroup, all layers
+__host__ __device__ constexpr uint32_t dw_base(int l) { return l == 0 ? 0u : l == 1 ? kDwN0 : l == 2 ? kDwN0 + kDwN1 : kDwN0 + 2 * kDwN1; }
+__host__ __device__ constexpr uint32_t dw_size(int l) { return l == 0 ? kDwN0 : l == 3 ? kDwN3 : kDwN1; }
+
+struct DwArgs {
+  const float* dz;
+  const float* dy[3];     // of layers 0, 1, 2
+  const uint16_t* x[4];   // inputs of layers 0 .. 3
+  const uint32_t* Ks;
+  uint32_t SR, num_series;
+  float* part;            // layer l, workgroup g at G dw_base(l) + g dw_size(l): [k][o][i] ([k][i] for layer 3)
+  float* bpart;           // [g][kBiasPart]: b0[64] b1[64] b2[64] b3
+};
+
+// Rows r .. r + 7 (r = 8 kg of a 32-row step) of 16 channels from c0, transposed:
+// lane (m, kg) gets channel c0 + m of them. tile: LDS rows of DST, or of 16
+// channels unpadded.
+template <int ST>
+__device__ __forceinline__ u32x4 read_rows(const uint16_t* tile, uint32_t r, uint32_t c0, uint32_t lane) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_p;
+  const uint16_t* p = tile + (r + ((lane & 15u) >> 2)) * ST + c0 + (lane & 3u) * 4;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p + 4 * ST));
+  const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+  return u32x4{ua.x, ua.y, ub.x, ub.y};
+}
+
+struct DwSmem {
+  uint16_t xs[(DT + 4) * DST];  // X rows r0 - 2 + r
+  uint16_t ys[DT * DST];        // dY rows r0 + r (layer 3: dz) in bf16
+  float yf[DT * 64];            // and in fp32
+};
+
+template <int L>
+__device__ __forceinline__ void dw_layer(DwSmem& sm, const DwArgs& A) {
+  constexpr int CX = L == 0 ? 16 : 64;       // input channels
+  constexpr int XST = L == 0 ? 16 : DST;
+  constexpr int NT = L == 1 || L == 2 ? 4 : 1;  // output-channel tiles per wave
+  const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  const uint32_t m = lane & 15u, kg = lane >> 4;
+  f32x4 acc[KW][NT];
+#pragma unroll
+  for (int k = 0; k < KW; ++k)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[k][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float db = 0.0f;  // bias gradient of channel tid
+  const uint64_t rows = (uint64_t)A.num_series * A.SR;
+  const uint64_t ntiles = (rows + DT - 1) / DT;
+  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint64_t r0 = tile * DT;
+    const uint32_t s0 = (uint32_t)(r0 / A.SR), rem = (uint32_t)(r0 - (uint64_t)s0 * A.SR);
+    // slot row r0 + r (r from -2 on) holds data; the last two rows of a slot never do
+    auto valid = [&](int32_t r) {
+      const int32_t p = (int32_t)rem + r;
+      if (p < 2) return false;
+      const uint32_t ds = (uint32_t)p / A.SR, t = (uint32_t)p - ds * A.SR;
+      return s0 + ds < A.num_series && t >= 2u && t - 2u < A.Ks[s0 + ds];
+    };
+    __syncthreads();
+    for (uint32_t q = tid; q < (DT + 4) * (CX / 8u); q += NTC) {
+      const int32_t r = (int32_t)(q / (CX / 8u)) - 2;
+      const uint32_t c = q % (CX / 8u) * 8;
+      u32x4 v{0u, 0u, 0u, 0u};
+      if (valid(r)) v = *reinterpret_cast<const u32x4*>(A.x[L] + (r0 + r) * CX + c);
+      *reinterpret_cast<u32x4*>(&sm.xs[(r + 2) * XST + c]) = v;
+    }
+    if constexpr (L == 3) {
+      if (tid < (uint32_t)DT) {
+        const float z = valid((int32_t)tid) ? A.dz[r0 + tid] : 0.0f;
+        sm.yf[tid] = z;
+        sm.ys[tid] = f2bf(z);
+      }
+    } else {
+      for (uint32_t q = tid; q < DT * 16u; q += NTC) {
+        const uint32_t r = q >> 4, c = (q & 15u) * 4;
+        f32x4 v{0.f, 0.f, 0.f, 0.f};
+        if (valid((int32_t)r)) v = *reinterpret_cast<const f32x4*>(A.dy[L] + (r0 + r) * 64 + c);
+        *reinterpret_cast<f32x4*>(&sm.yf[r * 64 + c]) = v;
+        *reinterpret_cast<uint2*>(&sm.ys[r * DST + c]) = make_uint2(pack_bf(v[0], v[1]), pack_bf(v[2], v[3]));
+      }
+    }
+    __syncthreads();
+    if (tid < (L == 3 ? 1u : 64u)) {
+#pragma unroll 16
+      for (int r = 0; r < DT; ++r) db += sm.yf[L == 3 ? r : r * 64 + (int)tid];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < DT / 32; ++q) {
+      const uint32_t r = 32 * q + 8 * kg;
+      u32x4 a[NT];
+      if constexpr (L == 3) {  // one output channel of 16
+        const u32x4 z = *reinterpret_cast<const u32x4*>(&sm.ys[r]);
+        a[0] = m == 0 ? z : u32x4{0u, 0u, 0u, 0u};
+      } else {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) a[t] = read_rows<DST>(sm.ys, r, 16 * (NT == 4 ? t : (int)w), lane);
+      }
+#pragma unroll
+      for (int k = 0; k < KW; ++k) {
+        const u32x4 x = read_rows<XST>(sm.xs, r + k, L == 0 ? 0 : 16 * w, lane);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[k][t] = mfma16(a[t], x, acc[k][t]);
+      }
+    }
+  }
+  float* out = A.part + (uint64_t)gridDim.x * dw_base(L) + (uint64_t)blockIdx.x * dw_size(L);
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    if constexpr (L == 3) {
+      if (kg == 0) out[k * 64 + 16 * w + m] = acc[k][0][0];
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          out[(k * 64 + 16 * (NT == 4 ? t : (int)w) + 4 * kg + e) * CX + (L == 0 ? 0 : 16 * w) + m] = acc[k][t][e];
+    }
+  }
+  if (tid < (L == 3 ? 1u : 64u)) A.bpart[blockIdx.x * kBiasPart + L * 64u + tid] = db;
+}
+
+__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(4))) void dw_kernel(DwArgs A) {
+  __shared__ __align__(16) DwSmem sm;
+  switch (blockIdx.y) {
+    case 0: dw_layer<0>(sm, A); break;
+    case 1: dw_layer<1>(sm, A); break;
+    case 2: dw_layer<2>(sm, A); break;
+    default: dw_layer<3>(sm, A);
+  }
 }
 
 // ---------------------------------------------------------------- parameters
@@ -541,32 +663,54 @@ __global__ __launch_bounds__(NTC) void shadow_kernel(const float* __restrict__ t
   }
 }
 
-// Adam (Kingma & Ba) on the master vector; gradients gathered from the
-// per-layer reduced partials ([cout_pad][5 cin_pad] then [cout_pad] biases).
-__global__ __launch_bounds__(NTC) void adam_kernel(float* __restrict__ theta, float* __restrict__ mom1,
-                                                   float* __restrict__ mom2, float* __restrict__ grad_out,
-                                                   const float* __restrict__ g0, const float* __restrict__ g1,
-                                                   const float* __restrict__ g2, const float* __restrict__ g3,
-                                                   float lr, float bc1, float bc2, int apply) {
-  const uint32_t p = blockIdx.x * NTC + threadIdx.x;
-  if (p >= kNumParams) return;
+// Adds the G <= kDwGrid partials of every parameter's gradient, in order, and, with `apply`, makes its Adam step (Kingma & Ba) and
+// rewrites the device copies that the kernels read. A workgroup takes kFinP
+// parameters (in the partials' order: weights of layers 0 .. 3, then the
+// biases): all its threads fetch their partials to LDS at once, and one thread
+// per parameter adds them there. (A thread walking its 256 partials in memory
+// took 61 us per layer on the latency of its loads.) The padding of the copies
+// stays as shadow_kernel left it (0).
+constexpr uint32_t kFinP = 32;  // parameters of a workgroup
+__global__ __launch_bounds__(NTC) void finish_kernel(const float* __restrict__ part, uint32_t G,
+                                                     const float* __restrict__ bpart,
+                                                     float* __restrict__ theta, float* __restrict__ mom1,
+                                                     float* __restrict__ mom2, float* __restrict__ grad_out, Shadow sh,
+                                                     float lr, float bc1, float bc2, int apply) {
+  __shared__ float red[kDwGrid][kFinP];
+  constexpr uint32_t GRP = NTC / kFinP;
+  const uint32_t c = threadIdx.x % kFinP, grp = threadIdx.x / kFinP;
+  const uint32_t q = blockIdx.x * kFinP + c;
+  const bool bias = q >= kDwPart;
   int l = 3;
-  for (int q = 0; q < 4; ++q) {
-    const Layer L = layer_info(q);
-    if (p < L.b_off + (uint32_t)L.cout) {
-      l = q;
-      break;
-    }
+  const float* src = bpart + (q - kDwPart);  // the padding past 193 is read and dropped
+  uint32_t stride = kBiasPart;
+  if (!bias) {
+    l = q < dw_base(1) ? 0 : q < dw_base(2) ? 1 : q < dw_base(3) ? 2 : 3;
+    src = part + (uint64_t)G * dw_base(l) + (q - dw_base(l));
+    stride = dw_size(l);
   }
-  const Layer L = layer_info(l);
-  const float* g = l == 0 ? g0 : (l == 1 ? g1 : (l == 2 ? g2 : g3));
-  const uint32_t J = KW * L.cin_pad;
-  float gv;
-  if (p < L.b_off) {
-    const uint32_t q = p - L.w_off, o = q / (L.cin * KW), r = q - o * (L.cin * KW), i = r / KW, k = r - i * KW;
-    gv = g[o * J + k * L.cin_pad + i];
+#pragma unroll 8
+  for (uint32_t g = grp; g < G; g += GRP) red[g][c] = src[(uint64_t)g * stride];
+  __syncthreads();
+  if (grp) return;
+  float gv = 0.0f;
+#pragma unroll 8
+  for (uint32_t g = 0; g < G; ++g) gv += red[g][c];
+  uint32_t p, o = 0, k = 0, i = 0;
+  if (!bias) {
+    const Layer L = layer_info(l);
+    const uint32_t r = q - dw_base(l), oi = (uint32_t)(L.cout * L.cin_pad);
+    k = r / oi;
+    o = (r - k * oi) / (uint32_t)L.cin_pad;
+    i = r - k * oi - o * (uint32_t)L.cin_pad;
+    if (i >= (uint32_t)L.cin) return;
+    p = L.w_off + (o * L.cin + i) * KW + k;
   } else {
-    gv = g[L.cout_pad * J + (p - L.b_off)];
+    const uint32_t r = q - kDwPart;
+    if (r > 192u) return;
+    l = (int)(r / 64u);
+    o = r % 64u;
+    p = layer_info(l).b_off + o;
   }
   grad_out[p] = gv;
   if (!apply) return;
@@ -574,8 +718,20 @@ __global__ __launch_bounds__(NTC) void adam_kernel(float* __restrict__ theta, fl
   const float v = 0.999f * mom2[p] + 0.001f * gv * gv;
   mom1[p] = m;
   mom2[p] = v;
-  theta[p] -= lr * (m / bc1) / (sqrtf(v / bc2) + 1e-8f);
+  const float th = theta[p] - lr * (m / bc1) / (sqrtf(v / bc2) + 1e-8f);
+  theta[p] = th;
+  const Layer L = layer_info(l);
+  if (bias) {
+    sh.b[l][o] = th;
+  } else {
+    sh.wf[l][(o * KW + k) * L.cin_pad + i] = f2bf(th);
+    if (l >= 1) sh.wb[l][(i * KW + KW - 1 - k) * L.cout_pad + o] = f2bf(th);
+  }
 }
+constexpr uint32_t kFinishGrid = (kDwPart + kBiasPart) / kFinP;
+static_assert(dw_base(1) % kFinP == 0 && dw_base(2) % kFinP == 0 && dw_base(3) % kFinP == 0 && kDwPart % kFinP == 0 &&
+                  kBiasPart % kFinP == 0,
+              "whole workgroups, each of one kind");
 
 // p[i] = 0 for i < n (a plain fill kernel rather than a memset node, so that a
 // captured graph replays it like any other kernel).
@@ -586,30 +742,17 @@ __global__ __launch_bounds__(NTC) void zero_kernel(float* __restrict__ p, uint32
 
 // ---------------------------------------------------------------- series heads
 
-// Number of labels >= 1 in the batch (the series that enter the loss).
-__global__ __launch_bounds__(NTC) void count_labels_kernel(const int32_t* __restrict__ labels, uint32_t n,
-                                                           uint32_t* __restrict__ count) {
-  __shared__ uint32_t c;
-  if (threadIdx.x == 0) c = 0;
-  __syncthreads();
-  uint32_t local = 0;
-  for (uint32_t s = threadIdx.x; s < n; s += NTC) local += labels[s] >= 1 ? 1u : 0u;
-  atomicAdd(&c, local);
-  __syncthreads();
-  if (threadIdx.x == 0) *count = c;
-}
-
 // Softmax over rows t = 1..K-1 of each series (one wave per series).
-// Training (labels != null): loss += -log p[label] / B_sig and dlogit rows
-// (bf16 + fp32, 16 channels, channel 0 used) = (p - onehot) / B_sig on rows
-// 1..K-1 of series with label >= 1, zero elsewhere. Inference: proposal =
+// Training (labels != null): loss += -log p[label] / B_sig and dlogit rows (fp32)
+// = (p - onehot) / B_sig on rows 1..K-1 of series with label >= 1, zero on the
+// series' other rows. Inference: proposal =
 // argmax (smallest row on ties), confidence = softmax mass of rows within
 // +-w of it.
 __global__ __launch_bounds__(NTC) void softmax_kernel(const float* __restrict__ logits, uint32_t num_series,
                                                       uint32_t SR, const uint32_t* __restrict__ Ks,
                                                       const int32_t* __restrict__ labels,
                                                       const uint32_t* __restrict__ nsig, float* __restrict__ loss,
-                                                      uint16_t* __restrict__ dY, float* __restrict__ dYf, uint32_t w,
+                                                      float* __restrict__ dz, uint32_t w,
                                                       int32_t* __restrict__ proposal, float* __restrict__ conf) {
   const uint32_t lane = lane_id();
   const uint32_t s = blockIdx.x * (NTC / kWave) + wave_id();
@@ -621,12 +764,6 @@ __global__ __launch_bounds__(NTC) void softmax_kernel(const float* __restrict__ 
       proposal[s] = 0;
       conf[s] = 0.0f;
     }
-    if (dY)
-      for (uint32_t r = lane; r < SR; r += kWave)
-        for (int c = 0; c < 16; ++c) {
-          dY[((uint64_t)s * SR + r) * 16 + c] = 0;
-          dYf[((uint64_t)s * SR + r) * 16 + c] = 0.0f;
-        }
     return;
   }
   // max and argmax over t = 1..K-1
@@ -660,23 +797,14 @@ __global__ __launch_bounds__(NTC) void softmax_kernel(const float* __restrict__ 
       conf[s] = part / sum;
     }
   }
-  if (dY) {
+  if (dz) {
     const int32_t lab = labels[s];
     const bool use = lab >= 1 && (uint32_t)lab < K;
     const float inv = 1.0f / (float)max(*nsig, 1u);
-    for (uint32_t r = lane; r < SR; r += kWave) {
-      const uint64_t row = (uint64_t)s * SR + r;
+    for (uint32_t t = lane; t < K; t += kWave) {
       float d = 0.0f;
-      if (use && r >= 3 && r - 2 < K) {
-        const uint32_t t = r - 2;
-        d = (__expf(logits[base + t] - mx) / sum - (t == (uint32_t)lab ? 1.0f : 0.0f)) * inv;
-      }
-      dY[row * 16] = f2bf(d);
-      dYf[row * 16] = d;
-      for (int c = 1; c < 16; ++c) {
-        dY[row * 16 + c] = 0;
-        dYf[row * 16 + c] = 0.0f;
-      }
+      if (use && t >= 1) d = (__expf(logits[base + t] - mx) / sum - (t == (uint32_t)lab ? 1.0f : 0.0f)) * inv;
+      dz[base + t] = d;
     }
     if (use && lane == 0) atomicAdd(loss, (logf(sum) - (logits[base + lab] - mx)) * inv);
   }
@@ -718,52 +846,18 @@ __global__ __launch_bounds__(NTC) void median_jump_kernel(const float* __restric
   }
 }
 
-// Caller features (fp32 [rows at aux_offset][9]) -> network input rows
-// (bf16, 16 channels) in the slot layout, plus each series' K (0 if invalid).
-__global__ __launch_bounds__(NTC) void pack_features_kernel(const float* __restrict__ feat, uint64_t feat_rows,
-                                                            const ks_desc* __restrict__ desc, uint32_t num_series,
-                                                            uint32_t max_K, uint32_t SR,
-                                                            uint16_t* __restrict__ x0,
-                                                            uint32_t* __restrict__ Ks) {
-  const uint32_t s = blockIdx.x;
-  if (s >= num_series) return;
-  const ks_desc d = desc[s];
-  const bool ok = d.K >= 2 && d.K <= max_K && d.aux_offset <= feat_rows && d.K <= feat_rows - d.aux_offset;
-  const uint32_t K = ok ? d.K : 0u;
-  for (uint32_t q = threadIdx.x; q < SR * 16; q += NTC) {
-    const uint32_t r = q / 16, k = q - r * 16;
-    uint16_t b = 0;
-    if (r >= 2 && r - 2 < K) {
-      if (k < 9)
-        b = f2bf(feat[(d.aux_offset + r - 2) * 9 + k]);
-      else if (k == 9)
-        b = f2bf(pos_frac(r - 2, K));
-      else if (k == 10)
-        b = f2bf(pos_centre(r - 2, K));
-    }
-    x0[((uint64_t)s * SR + r) * 16 + k] = b;
-  }
-  if (threadIdx.x == 0) Ks[s] = K;
-}
-
-// Caller logit gradients (fp32 rows aux_offset + t) -> the backward pass's
-// input in the slot layout: bf16 and fp32 copies of channel 0 (16 channels, the
-// others zero), zero on rows outside every series.
-__global__ __launch_bounds__(NTC) void pack_dlogits_kernel(const float* __restrict__ dz, uint64_t dz_rows,
+// Caller logit gradients (fp32 rows aux_offset + t) -> slot rows; zero for a
+// series that does not fit.
+__global__ __launch_bounds__(NTC) void pack_dlogits_kernel(const float* __restrict__ src, uint64_t src_rows,
                                                            const ks_desc* __restrict__ desc, uint32_t num_series,
                                                            uint32_t SR, const uint32_t* __restrict__ Ks,
-                                                           uint16_t* __restrict__ dY, float* __restrict__ dYf) {
+                                                           float* __restrict__ dz) {
   const uint32_t s = blockIdx.x;
   if (s >= num_series) return;
   const ks_desc d = desc[s];
-  uint32_t K = Ks[s];
-  if (!(d.aux_offset <= dz_rows && K <= dz_rows - d.aux_offset)) K = 0;
-  for (uint32_t q = threadIdx.x; q < SR * 16; q += NTC) {
-    const uint32_t r = q / 16, c = q - r * 16;
-    const float v = (c == 0 && r >= 2 && r - 2 < K) ? dz[d.aux_offset + r - 2] : 0.0f;
-    dY[((uint64_t)s * SR + r) * 16 + c] = f2bf(v);
-    dYf[((uint64_t)s * SR + r) * 16 + c] = v;
-  }
+  const uint32_t K = Ks[s];
+  const bool fits = d.aux_offset <= src_rows && K <= src_rows - d.aux_offset;
+  for (uint32_t t = threadIdx.x; t < K; t += NTC) dz[(uint64_t)s * SR + 2 + t] = fits ? src[d.aux_offset + t] : 0.0f;
 }
 
 // Per-layer values of one forward (and backward) pass -> caller rows
@@ -804,7 +898,7 @@ __global__ __launch_bounds__(NTC) void trace_copy_kernel(const ks_desc* __restri
     const uint32_t t = q / NG, c = q - t * NG;
     const uint64_t row = (uint64_t)s * SR + 2 + t;
     float v;
-    if (c == 0) v = dz[row * 16];
+    if (c == 0) v = dz[row];
     else if (c < 65) v = dyf0[row * 64 + (c - 1)];
     else if (c < 129) v = dyf1[row * 64 + (c - 65)];
     else v = dyf2[row * 64 + (c - 129)];

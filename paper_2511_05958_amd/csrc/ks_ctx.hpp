@@ -84,14 +84,12 @@ struct LearnBuffers {
   uint16_t* act[3] = {nullptr, nullptr, nullptr};  // [rows][64] bf16 (a1, a2, a3)
   float* logits = nullptr;    // [rows]
   // training
-  uint16_t* dy16 = nullptr;   // [rows][16] bf16: logit gradient
-  float* dy16f = nullptr;
-  uint16_t* dy[3] = {nullptr, nullptr, nullptr};  // [rows][64] bf16: gradients at y2, y1, y0
-  float* dyf[3] = {nullptr, nullptr, nullptr};     // the same in fp32 (before the bf16 rounding)
-  float* part = nullptr;      // weight-gradient partials
-  float* grad[4] = {nullptr, nullptr, nullptr, nullptr};  // reduced, per layer
+  float* dz = nullptr;        // [rows]: logit gradient
+  float* dy[3] = {nullptr, nullptr, nullptr};     // [rows][64]: gradients at y2, y1, y0
+  float* part = nullptr;      // weight-gradient partials of the workgroups
+  float* bpart = nullptr;     // bias-gradient partials
   uint32_t* nsig = nullptr;
-  uint64_t cap_rows = 0, cap_series = 0, cap_part = 0;
+  uint64_t cap_rows = 0, cap_series = 0;
   // the last proposal / feature pass (ks_refine checks it)
   const void* stamp_desc = nullptr;
   uint32_t stamp_series = 0, stamp_SR = 0, stamp_maxK = 0;

@@ -21,8 +21,8 @@ namespace ks_host {
 
 void free_learn(LearnBuffers& b) {
   void* ptrs[] = {b.s1, b.s2lo, b.s2hi, b.smin, b.cmin, b.K, b.feat, b.x0, b.act[0], b.act[1], b.act[2], b.logits,
-                  b.dy16, b.dy16f, b.dy[0], b.dy[1], b.dy[2], b.dyf[0], b.dyf[1], b.dyf[2], b.part, b.grad[0], b.grad[1],
-                  b.grad[2], b.grad[3], b.nsig};
+                  b.dz, b.dy[0], b.dy[1], b.dy[2], b.part, b.bpart,
+                  b.nsig};
   for (void* p : ptrs) (void)hipFree(p);
   b = LearnBuffers{};
 }
@@ -30,8 +30,6 @@ void free_learn(LearnBuffers& b) {
 }  // namespace ks_host
 
 namespace {
-
-constexpr uint32_t kDwGrid = 256;     // workgroups of a weight-gradient reduction
 
 uint32_t slot_rows(uint32_t max_K) { return (max_K + 4 + 15) / 16 * 16; }
 
@@ -44,7 +42,7 @@ bool alloc(T*& p, uint64_t n) {
 // (training buffers too when `train`).
 int ensure_learn(ks_ctx* c, uint64_t rows, uint64_t series, bool train) {
   LearnBuffers& b = c->learn;
-  const bool have_train = b.dy16 != nullptr;
+  const bool have_train = b.dz != nullptr;
   if (rows <= b.cap_rows && series <= b.cap_series && (!train || have_train)) return KS_OK;
   const uint64_t R = rows > b.cap_rows ? rows : b.cap_rows;
   const uint64_t S = series > b.cap_series ? series : b.cap_series;
@@ -57,13 +55,9 @@ int ensure_learn(ks_ctx* c, uint64_t rows, uint64_t series, bool train) {
             alloc(b.feat, R * 9) && alloc(b.x0, R * 16) && alloc(b.act[0], R * 64) && alloc(b.act[1], R * 64) &&
             alloc(b.act[2], R * 64) && alloc(b.logits, R);
   if (ok && T) {
-    const uint64_t part = (uint64_t)kDwGrid * (64 * 320 + 64);
-    ok = alloc(b.dy16, R * 16) && alloc(b.dy16f, R * 16) && alloc(b.dy[0], R * 64) && alloc(b.dy[1], R * 64) &&
-         alloc(b.dy[2], R * 64) && alloc(b.dyf[0], R * 64) && alloc(b.dyf[1], R * 64) && alloc(b.dyf[2], R * 64) &&
-         alloc(b.part, part) && alloc(b.grad[0], 64 * 80 + 64) &&
-         alloc(b.grad[1], 64 * 320 + 64) && alloc(b.grad[2], 64 * 320 + 64) && alloc(b.grad[3], 16 * 320 + 16) &&
-         alloc(b.nsig, 4);
-    b.cap_part = part;
+    ok = alloc(b.dz, R) && alloc(b.dy[0], R * 64) && alloc(b.dy[1], R * 64) && alloc(b.dy[2], R * 64) &&
+         alloc(b.part, (uint64_t)C::kDwGrid * C::kDwPart) &&
+         alloc(b.bpart, (uint64_t)C::kDwGrid * C::kBiasPart) && alloc(b.nsig, 4);
   }
   if (!ok) {
     free_learn(b);
@@ -79,26 +73,14 @@ ks::LearnWs learn_ws(ks_ctx* c) {
   return ks::LearnWs{c->learn.s1, c->learn.s2lo, c->learn.s2hi, c->learn.smin, c->learn.cmin, c->learn.K};
 }
 
-uint32_t conv_grid(const ks_ctx* c, uint64_t rows) {
-  const uint64_t tiles = (rows + C::TM - 1) / C::TM;
-  const uint64_t cap = (uint64_t)c->num_cus * 3;
-  return (uint32_t)(tiles < cap ? (tiles ? tiles : 1) : cap);
-}
-
-// The network forward over the slot rows, one launch per layer, keeping the
-// activations a1..a3 for the backward pass: x0 -> a1 -> a2 -> a3 -> logits.
-hipError_t forward(ks_ctx* c, const ks_model* m, uint64_t rows, uint32_t SR, hipStream_t st) {
-  LearnBuffers& b = c->learn;
-  const uint32_t g = conv_grid(c, rows);
-  hipLaunchKernelGGL((C::conv_kernel<16, 64, C::EPI_RELU>), dim3(g), dim3(C::NTC), 0, st, b.x0, m->wf[0], m->b[0],
-                     rows, SR, b.K, b.act[0], (float*)nullptr, (const uint16_t*)nullptr);
-  hipLaunchKernelGGL((C::conv_kernel<64, 64, C::EPI_RELU>), dim3(g), dim3(C::NTC), 0, st, b.act[0], m->wf[1],
-                     m->b[1], rows, SR, b.K, b.act[1], (float*)nullptr, (const uint16_t*)nullptr);
-  hipLaunchKernelGGL((C::conv_kernel<64, 64, C::EPI_RELU>), dim3(g), dim3(C::NTC), 0, st, b.act[1], m->wf[2],
-                     m->b[2], rows, SR, b.K, b.act[2], (float*)nullptr, (const uint16_t*)nullptr);
-  hipLaunchKernelGGL((C::conv_kernel<64, 16, C::EPI_LOGIT>), dim3(g), dim3(C::NTC), 0, st, b.act[2], m->wf[3],
-                     m->b[3], rows, SR, b.K, (uint16_t*)nullptr, b.logits, (const uint16_t*)nullptr);
-  return hipGetLastError();
+C::Shadow shadow_of(const ks_model* m) {
+  C::Shadow sh;
+  for (int l = 0; l < 4; ++l) {
+    sh.wf[l] = m->wf[l];
+    sh.wb[l] = m->wb[l];
+    sh.b[l] = m->b[l];
+  }
+  return sh;
 }
 
 C::ForwardArgs forward_args(ks_ctx* c, const ks_model* m, uint32_t num_series, uint32_t SR, uint32_t max_K) {
@@ -118,43 +100,78 @@ C::ForwardArgs forward_args(ks_ctx* c, const ks_model* m, uint32_t num_series, u
   return A;
 }
 
-// The whole network in one launch, activations kept in LDS: persistent
-// workgroups, as many as are resident.
-template <bool FEAT>
-hipError_t forward_infer(ks_ctx* c, const C::ForwardArgs& A, hipStream_t st) {
-  const uint64_t tiles = (uint64_t)A.num_series * A.tiles_per_series, cap = (uint64_t)c->num_cus * C::FWGS;
-  hipLaunchKernelGGL(C::fused_forward_kernel<FEAT>, dim3((uint32_t)(tiles < cap ? tiles : cap)), dim3(C::NTC), 0, st, A);
+// Resident workgroups of the fused network kernels, at most one per tile.
+uint32_t fused_grid(const ks_ctx* c, uint32_t num_series, uint32_t tiles_per_series) {
+  const uint64_t tiles = (uint64_t)num_series * tiles_per_series, cap = (uint64_t)c->num_cus * C::FWGS;
+  return (uint32_t)(tiles < cap ? tiles : cap);
+}
+
+// The whole network in one launch, activations kept in LDS.
+template <bool FEAT, bool TRAIN = false>
+hipError_t launch_forward(ks_ctx* c, const C::ForwardArgs& A, hipStream_t st) {
+  auto kernel = C::fused_forward_kernel<FEAT, TRAIN>;
+  hipLaunchKernelGGL(kernel, dim3(fused_grid(c, A.num_series, A.tiles_per_series)), dim3(C::NTC), 0, st, A);
   return hipGetLastError();
 }
 
-// Backward pass over the slot rows from the logit gradient in dy16 / dy16f
-// (bf16 / fp32, channel 0), with the activations of the last forward():
-// the gradients at the pre-activations y2, y1, y0 in dy / dyf[0..2] and the
-// per-layer weight and bias gradients reduced into grad[0..3].
-hipError_t backward(ks_ctx* c, const ks_model* model, uint64_t rows, uint32_t SR, hipStream_t st) {
+// The training forward from the caller's features: activations a1..a3, input
+// rows, logits and each series' K kept for the backward pass; with labels their
+// count in nsig and *loss cleared.
+hipError_t forward_train(ks_ctx* c, const ks_model* m, const float* features, uint64_t feature_rows,
+                         const ks_desc* desc, uint32_t num_series, uint32_t max_K, const int32_t* labels, float* loss,
+                         hipStream_t st) {
   LearnBuffers& b = c->learn;
-  const uint64_t tiles = (rows + C::TM - 1) / C::TM;
-  const uint32_t G = (uint32_t)(tiles < kDwGrid ? tiles : kDwGrid);
-  const uint32_t gc = conv_grid(c, rows);
-  auto reduce = [&](float* dst, uint32_t n) {
-    hipLaunchKernelGGL(C::reduce_parts_kernel, dim3((n + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st, b.part, G, n,
-                       dst);
-  };
-  // layer 3 (64 -> 1), then 2, 1 (64 -> 64), then 0 (11 -> 64)
-  hipLaunchKernelGGL((C::dw_kernel<64, 16>), dim3(G), dim3(C::NTC), 0, st, b.dy16, b.dy16f, b.act[2], rows, b.part);
-  reduce(b.grad[3], C::DwShape<64, 16>::PART);
-  hipLaunchKernelGGL((C::conv_kernel<16, 64, C::EPI_BWD>), dim3(gc), dim3(C::NTC), 0, st, b.dy16, model->wb[3],
-                     (const float*)nullptr, rows, SR, b.K, b.dy[0], b.dyf[0], b.act[2]);
-  hipLaunchKernelGGL((C::dw_kernel<64, 64>), dim3(G), dim3(C::NTC), 0, st, b.dy[0], b.dyf[0], b.act[1], rows, b.part);
-  reduce(b.grad[2], C::DwShape<64, 64>::PART);
-  hipLaunchKernelGGL((C::conv_kernel<64, 64, C::EPI_BWD>), dim3(gc), dim3(C::NTC), 0, st, b.dy[0], model->wb[2],
-                     (const float*)nullptr, rows, SR, b.K, b.dy[1], b.dyf[1], b.act[1]);
-  hipLaunchKernelGGL((C::dw_kernel<64, 64>), dim3(G), dim3(C::NTC), 0, st, b.dy[1], b.dyf[1], b.act[0], rows, b.part);
-  reduce(b.grad[1], C::DwShape<64, 64>::PART);
-  hipLaunchKernelGGL((C::conv_kernel<64, 64, C::EPI_BWD>), dim3(gc), dim3(C::NTC), 0, st, b.dy[1], model->wb[1],
-                     (const float*)nullptr, rows, SR, b.K, b.dy[2], b.dyf[2], b.act[0]);
-  hipLaunchKernelGGL((C::dw_kernel<16, 64>), dim3(G), dim3(C::NTC), 0, st, b.dy[2], b.dyf[2], b.x0, rows, b.part);
-  reduce(b.grad[0], C::DwShape<16, 64>::PART);
+  C::ForwardArgs A = forward_args(c, m, num_series, slot_rows(max_K), max_K);
+  A.feat = features;
+  A.feat_rows = feature_rows;
+  A.desc = desc;
+  A.keep[0] = b.x0;
+  for (int l = 0; l < 3; ++l) A.keep[l + 1] = b.act[l];
+  A.labels = labels;
+  A.nsig = b.nsig;
+  A.loss = loss;
+  return launch_forward<true, true>(c, A, st);
+}
+
+// Backward pass from the logit gradient in dz, with the activations of the last
+// forward_train: the gradients at y2, y1, y0 in dy[0..2] and, into `grads`
+// (nullable), the parameters' gradient; with `step` also the Adam step.
+hipError_t backward(ks_ctx* c, const ks_model* model, uint32_t num_series, uint32_t max_K, float* grads,
+                    const float* step, hipStream_t st) {
+  LearnBuffers& b = c->learn;
+  const uint32_t SR = slot_rows(max_K);
+  C::BackwardArgs A{};
+  A.dz = b.dz;
+  A.Ks = b.K;
+  A.SR = SR;
+  A.num_series = num_series;
+  A.tiles_per_series = (max_K + C::BT - 1) / C::BT;
+  for (int l = 0; l < 3; ++l) {
+    A.a[l] = b.act[2 - l];
+    A.wb[l] = model->wb[3 - l];
+    A.dy[l] = b.dy[l];
+  }
+  hipLaunchKernelGGL(C::fused_backward_kernel, dim3(fused_grid(c, num_series, A.tiles_per_series)), dim3(C::NTC), 0, st,
+                     A);
+  if (!grads) return hipGetLastError();
+  C::DwArgs D{};
+  D.dz = b.dz;
+  D.x[0] = b.x0;
+  for (int l = 0; l < 3; ++l) {
+    D.dy[l] = b.dy[2 - l];
+    D.x[l + 1] = b.act[l];
+  }
+  D.Ks = b.K;
+  D.SR = SR;
+  D.num_series = num_series;
+  D.part = b.part;
+  D.bpart = b.bpart;
+  const uint64_t tiles = ((uint64_t)num_series * SR + C::DT - 1) / C::DT;
+  const uint32_t G = (uint32_t)(tiles < C::kDwGrid ? tiles : C::kDwGrid);
+  hipLaunchKernelGGL(C::dw_kernel, dim3(G, 4), dim3(C::NTC), 0, st, D);
+  hipLaunchKernelGGL(C::finish_kernel, dim3(C::kFinishGrid), dim3(C::NTC), 0, st, b.part, G, b.bpart, model->theta,
+                     model->m1, model->m2, grads, shadow_of(model), step ? step[0] : 0.0f, step ? step[1] : 1.0f,
+                     step ? step[2] : 1.0f, step ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -172,13 +189,8 @@ void launch_refine(const ks_desc* desc, uint32_t n, uint64_t num_samples, uint32
 }
 
 hipError_t shadow(ks_model* m, hipStream_t st) {
-  C::Shadow sh;
-  for (int l = 0; l < 4; ++l) {
-    sh.wf[l] = m->wf[l];
-    sh.wb[l] = m->wb[l];
-    sh.b[l] = m->b[l];
-  }
-  hipLaunchKernelGGL(C::shadow_kernel, dim3((C::kShadowEntries + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st, m->theta, sh);
+  hipLaunchKernelGGL(C::shadow_kernel, dim3((C::kShadowEntries + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st, m->theta,
+                     shadow_of(m));
   return hipGetLastError();
 }
 
@@ -425,7 +437,7 @@ int ks_cnn_forward(ks_ctx* ctx, const ks_model* model, const float* features, ui
   A.desc = desc;
   A.out = logits;
   A.out_rows = logit_rows;
-  const hipError_t e = forward_infer<true>(ctx, A, (hipStream_t)stream);
+  const hipError_t e = launch_forward<true>(ctx, A, (hipStream_t)stream);
   return e == hipSuccess ? KS_OK : hip_fail(e, "cnn forward");
 }
 
@@ -450,11 +462,11 @@ int ks_propose(ks_ctx* ctx, const ks_model* model, const uint32_t* samples, uint
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? KS_OK : hip_fail(e, "propose");
   }
-  hipError_t e = forward_infer<false>(ctx, forward_args(ctx, model, num_series, SR, max_K), st);
+  hipError_t e = launch_forward<false>(ctx, forward_args(ctx, model, num_series, SR, max_K), st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(C::softmax_kernel, dim3((num_series + per - 1) / per), dim3(C::NTC), 0, st, b.logits,
                        num_series, SR, b.K, (const int32_t*)nullptr, (const uint32_t*)nullptr, (float*)nullptr,
-                       (uint16_t*)nullptr, (float*)nullptr, params->w, proposal, confidence);
+                       (float*)nullptr, params->w, proposal, confidence);
     e = hipGetLastError();
   }
   return e == hipSuccess ? KS_OK : hip_fail(e, "propose");
@@ -501,29 +513,18 @@ int ks_train_step(ks_ctx* ctx, ks_model* model, const float* features, uint64_t 
   hipStream_t st = (hipStream_t)stream;
   LearnBuffers& b = ctx->learn;
   b.stamp_valid = false;
-  hipLaunchKernelGGL(C::pack_features_kernel, dim3(num_series), dim3(C::NTC), 0, st, features, feature_rows, desc,
-                     num_series, max_K, SR, b.x0, b.K);
-  hipError_t e = forward(ctx, model, rows, SR, st);
+  float* loss_acc = loss ? loss : reinterpret_cast<float*>(b.nsig + 1);  // discarded when the caller wants no loss
+  hipError_t e = forward_train(ctx, model, features, feature_rows, desc, num_series, max_K, labels, loss_acc, st);
   if (e != hipSuccess) return hip_fail(e, "train forward");
   // loss and logit gradient
-  hipLaunchKernelGGL(C::count_labels_kernel, dim3(1), dim3(C::NTC), 0, st, labels, num_series, b.nsig);
-  float* loss_acc = reinterpret_cast<float*>(b.nsig + 1);  // discarded when the caller wants no loss
-  if (loss) {
-    hipLaunchKernelGGL(C::zero_kernel, dim3(1), dim3(C::NTC), 0, st, loss, 1u);
-    loss_acc = loss;
-  }
   const uint32_t per = C::NTC / 64;
   hipLaunchKernelGGL(C::softmax_kernel, dim3((num_series + per - 1) / per), dim3(C::NTC), 0, st, b.logits, num_series,
-                     SR, b.K, labels, b.nsig, loss_acc, b.dy16, b.dy16f, 0u, (int32_t*)nullptr, (float*)nullptr);
-  if ((e = backward(ctx, model, rows, SR, st)) != hipSuccess) return hip_fail(e, "train backward");
-  // Adam
+                     SR, b.K, labels, b.nsig, loss_acc, b.dz, 0u, (int32_t*)nullptr, (float*)nullptr);
+  // gradients and Adam
   model->step += 1;
-  const float bc1 = (float)(1.0 - std::pow(0.9, (double)model->step));
-  const float bc2 = (float)(1.0 - std::pow(0.999, (double)model->step));
-  hipLaunchKernelGGL(C::adam_kernel, dim3((C::kNumParams + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st, model->theta,
-                     model->m1, model->m2, model->grad, b.grad[0], b.grad[1], b.grad[2], b.grad[3], lr, bc1, bc2,
-                     1);
-  e = shadow(model, st);
+  const float step[3] = {lr, (float)(1.0 - std::pow(0.9, (double)model->step)),
+                         (float)(1.0 - std::pow(0.999, (double)model->step))};
+  e = backward(ctx, model, num_series, max_K, model->grad, step, st);
   return e == hipSuccess ? KS_OK : hip_fail(e, "train step");
 }
 
@@ -550,18 +551,12 @@ int ks_cnn_backward(ks_ctx* ctx, const ks_model* model, const float* features, u
     e = hipGetLastError();
     return e == hipSuccess ? KS_OK : hip_fail(e, "gradient reset");
   }
-  hipLaunchKernelGGL(C::pack_features_kernel, dim3(num_series), dim3(C::NTC), 0, st, features, feature_rows, desc,
-                     num_series, max_K, SR, b.x0, b.K);
-  if ((e = forward(ctx, model, rows, SR, st)) != hipSuccess) return hip_fail(e, "backward: forward");
+  if ((e = forward_train(ctx, model, features, feature_rows, desc, num_series, max_K, nullptr, nullptr, st)) != hipSuccess)
+    return hip_fail(e, "backward: forward");
   hipLaunchKernelGGL(C::pack_dlogits_kernel, dim3(num_series), dim3(C::NTC), 0, st, dlogits, dlogit_rows, desc,
-                     num_series, SR, b.K, b.dy16, b.dy16f);
-  if ((e = backward(ctx, model, rows, SR, st)) != hipSuccess) return hip_fail(e, "backward");
-  // gather into the parameter layout (the optimizer kernel with its update off)
-  hipLaunchKernelGGL(C::adam_kernel, dim3((C::kNumParams + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st,
-                     (float*)nullptr, (float*)nullptr, (float*)nullptr, grads, b.grad[0], b.grad[1], b.grad[2],
-                     b.grad[3], 0.0f, 1.0f, 1.0f, 0);
-  e = hipGetLastError();
-  return e == hipSuccess ? KS_OK : hip_fail(e, "backward gather");
+                     num_series, SR, b.K, b.dz);
+  e = backward(ctx, model, num_series, max_K, grads, nullptr, st);
+  return e == hipSuccess ? KS_OK : hip_fail(e, "backward");
 }
 
 int ks_cnn_trace(ks_ctx* ctx, const ks_model* model, const float* features, uint64_t feature_rows,
@@ -583,30 +578,22 @@ int ks_cnn_trace(ks_ctx* ctx, const ks_model* model, const float* features, uint
   if (int rc = ensure_learn(ctx, rows, num_series, true)) return rc;
   LearnBuffers& b = ctx->learn;
   b.stamp_valid = false;
-  hipLaunchKernelGGL(C::pack_features_kernel, dim3(num_series), dim3(C::NTC), 0, st, features, feature_rows, desc,
-                     num_series, max_K, SR, b.x0, b.K);
-  hipError_t e = forward(ctx, model, rows, SR, st);
+  float* loss_acc = reinterpret_cast<float*>(b.nsig + 1);  // the training step's loss goes to a scratch word
+  hipError_t e = forward_train(ctx, model, features, feature_rows, desc, num_series, max_K, labels, loss_acc, st);
   if (e != hipSuccess) return hip_fail(e, "trace forward");
-  if (labels) {  // the training step's logit gradient (its loss goes to a scratch word)
-    hipLaunchKernelGGL(C::count_labels_kernel, dim3(1), dim3(C::NTC), 0, st, labels, num_series, b.nsig);
+  if (labels) {  // the training step's logit gradient
     const uint32_t per = C::NTC / 64;
     hipLaunchKernelGGL(C::softmax_kernel, dim3((num_series + per - 1) / per), dim3(C::NTC), 0, st, b.logits,
-                       num_series, SR, b.K, labels, b.nsig, reinterpret_cast<float*>(b.nsig + 1), b.dy16, b.dy16f, 0u,
-                       (int32_t*)nullptr, (float*)nullptr);
+                       num_series, SR, b.K, labels, b.nsig, loss_acc, b.dz, 0u, (int32_t*)nullptr, (float*)nullptr);
   } else if (dlogits) {
     hipLaunchKernelGGL(C::pack_dlogits_kernel, dim3(num_series), dim3(C::NTC), 0, st, dlogits, dlogit_rows, desc,
-                       num_series, SR, b.K, b.dy16, b.dy16f);
+                       num_series, SR, b.K, b.dz);
   }
-  if (bwd) {
-    if ((e = backward(ctx, model, rows, SR, st)) != hipSuccess) return hip_fail(e, "trace backward");
-    if (grads)
-      hipLaunchKernelGGL(C::adam_kernel, dim3((C::kNumParams + C::NTC - 1) / C::NTC), dim3(C::NTC), 0, st,
-                         (float*)nullptr, (float*)nullptr, (float*)nullptr, grads, b.grad[0], b.grad[1], b.grad[2],
-                         b.grad[3], 0.0f, 1.0f, 1.0f, 0);
-  }
+  if (bwd && (e = backward(ctx, model, num_series, max_K, grads, nullptr, st)) != hipSuccess)
+    return hip_fail(e, "trace backward");
   if (acts || grads_in)
     hipLaunchKernelGGL(C::trace_copy_kernel, dim3(num_series), dim3(C::NTC), 0, st, desc, num_series, SR, b.K, b.x0,
-                       b.act[0], b.act[1], b.act[2], b.logits, b.dy16f, bwd ? b.dyf[0] : nullptr, b.dyf[1], b.dyf[2],
+                       b.act[0], b.act[1], b.act[2], b.logits, b.dz, bwd ? b.dy[0] : nullptr, b.dy[1], b.dy[2],
                        acts, grads_in, trace_rows);
   e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "trace");
