@@ -414,11 +414,11 @@ int ks_cnn_trace(ks_ctx *ctx, const ks_model *model, const float *features, uint
  *               Above max_cp only max_cp of them are stored (which ones is
  *               unspecified). 0xffffffff for a series whose descriptor
  *               ks_scan_batch would flag KS_BAD_SHAPE or KS_OUT_OF_RANGE.
- * The depths run breadth-first: one ks_scan_batch over all open windows per
- * depth. Between depths the call reads back the next depth's window count
- * and largest K, which synchronizes `stream` once per depth. The window
- * workspace (num_series * max(1, max_K / 2) windows, 80 B each) grows on
- * demand. KS_E_INVALID on a NULL pointer, max_cp == 0 or a bad parameter,
+ * One launch does the whole segmentation of a series in one workgroup (batches
+ * of few series spread the reading of their rows over the device first, in a
+ * second launch whose per-row moments, 24 B each, are kept in a workspace that
+ * grows on demand); nothing is read back, the call does not wait for the
+ * device. KS_E_INVALID on a NULL pointer, max_cp == 0 or a bad parameter,
  * KS_E_RANGE / KS_E_NOMEM as ks_scan_batch. */
 int ks_segment_batch(ks_ctx *ctx, const uint32_t *samples, uint64_t num_samples, const ks_desc *desc,
                      uint32_t num_series, const ks_params *params, uint32_t max_levels, uint32_t max_cp,

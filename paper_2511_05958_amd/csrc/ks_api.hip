@@ -93,7 +93,6 @@ unsigned char* scratch_of(int device) {
 // 109; a series of more than 256 KB keeps its one workgroup busy for longer than
 // the spread scan's two more launches take.
 constexpr uint32_t kSplitMaxSeries = 384;
-constexpr uint32_t kSplitWGs = 2048;             // eight workgroups per CU stream the rows
 constexpr uint32_t kTinyMaxSeries = 1024;
 constexpr int kTinyMaxClass = 2;                 // K <= 256
 constexpr uint64_t kTinyMaxSamples = 1u << 16;   // 256 KB a series
@@ -281,10 +280,7 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
   } else {
     if (int rc = ensure_workspace(c, a.num_series, 0)) return rc;
     const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
-    const uint32_t chunks = (kSplitWGs + a.num_series - 1) / a.num_series;
-    const uint32_t C = chunks < a.max_K ? chunks : a.max_K;
-    hipLaunchKernelGGL(ks::split_moments_kernel, dim3(C, a.num_series), dim3(ks::kSplitNT), 0, st, a.samples,
-                       a.num_samples, a.desc, a.max_K, a.out, ws);
+    ks::launch_split_moments(a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
     hipLaunchKernelGGL(ks::split_rank_kernel, dim3((a.max_K + ks::kWave - 1) / ks::kWave, a.num_series),
                        dim3(ks::kSplitNT), 0, st, a.num_samples, a.desc, a.max_K, ws);
     hipLaunchKernelGGL(ks::split_walk_kernel, dim3((a.max_K - 1 + ks::kWave - 1) / ks::kWave, a.num_series),

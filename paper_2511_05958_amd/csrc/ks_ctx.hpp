@@ -96,17 +96,11 @@ struct LearnBuffers {
   bool stamp_valid = false;
 };
 
-// Window workspace of the binary segmentation (ks_segment_batch), grown on demand.
+// Workspace of the binary segmentation (ks_segment_batch), grown on demand.
 struct SegBuffers {
-  ks_desc* win[2] = {nullptr, nullptr};    // open windows of this / the next depth
-  uint32_t* wser[2] = {nullptr, nullptr};  // their series
-  uint32_t* wstart[2] = {nullptr, nullptr};  // their first row within the series
-  ks_result* res = nullptr;                // scan results of the open windows
-  uint32_t* ctr = nullptr;                 // device: per depth d, [2 d] its window count, [2 d + 1] their largest K
-  uint32_t* host_ctr = nullptr;            // pinned host copy of ctr
-  ks::RowMom* rows = nullptr;              // per-row moments and minimum of depth 0 (s * max_K + i)
-  uint64_t cap = 0;                        // windows per buffer
-  uint64_t cap_rows = 0;
+  ks::RowMom* rows = nullptr;  // per-row moments and minimum (s * max_K + i)
+  uint32_t* ticket = nullptr;
+  uint64_t cap_rows = 0, cap_series = 0;
 };
 
 int hip_fail(hipError_t e, const char* what);

@@ -132,6 +132,11 @@ __device__ __forceinline__ void write_result(ks_result* o, uint32_t cp, uint32_t
   o->pad = 0;
 }
 
+// Eq. 1: H0 is denied for the split c with statistic U.
+__device__ __forceinline__ bool significant(uint32_t U, uint32_t c, uint32_t K, double c_alpha) {
+  return (double)((uint64_t)U * U) > c_alpha * (double)((uint64_t)c * (K - c) * K);
+}
+
 // The result of a series whose most significant split is c (statistic U).
 __device__ __forceinline__ void write_choice(ks_result* out, uint32_t U, uint32_t c, uint32_t K, const ks_params& prm,
                                              uint32_t extra_flags) {
@@ -140,7 +145,7 @@ __device__ __forceinline__ void write_choice(ks_result* out, uint32_t U, uint32_
   const double nmK = (double)((uint64_t)n * m * K);
   const double lambda2 = U2 / nmK;
   const double p = U == 0 ? 1.0 : kolmogorov_q(lambda2);
-  const uint32_t flags = ((U2 > prm.c_alpha * nmK) ? KS_SIGNIFICANT : 0u) | extra_flags;
+  const uint32_t flags = (significant(U, c, K, prm.c_alpha) ? KS_SIGNIFICANT : 0u) | extra_flags;
   write_result(out, c, n, m, U, (double)U / (double)((uint64_t)n * m), sqrt(lambda2), p, flags);
 }
 

@@ -1,14 +1,22 @@
-// Binary segmentation over a batch: every level boundary of each series.
-// Depth 0 scans the whole series like ks_scan_batch and also keeps every
-// row's moments and minimum (24 B per row). A window [a, b) of a later depth
-// is a series of its own, but its eq. 2 keys need only its rows' sum r and
-// sum r^2 and the window's minimum (the least row minimum), so depths >= 1
-// read that workspace and never the samples. After each depth a split kernel
-// records the significant splits and opens both sides of each as windows of
-// the next depth; a final kernel sorts each series' boundaries by position.
-// Window and split kernels run on fixed grids that stride over the depth's
-// window count in device memory, so the host enqueues several depths between
-// read-backs of those counts.
+// Binary segmentation over a batch: every level boundary of each series, in one
+// launch with one workgroup per series.
+//
+// The row moments (sum r, sum r^2) and minima of a series are kept in LDS. A
+// window [a, b) of rows is a series of its own, but its eq. 2 keys need only its
+// rows' moments and the window's minimum (the least row minimum), so the samples
+// are read once. The workgroup takes windows from a stack: keys, ranks by
+// counting smaller keys, the walk shared by all waves, the choice; a significant
+// split is recorded and opens both sides. At the end one thread per boundary
+// finds its place and its p-value.
+//
+// (One launch per depth for all open windows, with a split kernel after each, a
+// read-back of the window counts every few depths and a sort at the end took 14
+// depths x 10 - 25 us after a root pass of 107 us on 512 series of 256 rows of
+// 1024 samples, 331 us a call, most depths with a handful of windows.)
+//
+// A workgroup streams its own series' rows when there are enough series to keep
+// HBM busy that way; with fewer, split_moments_kernel has spread the rows over
+// the device and left the moments in the workspace.
 #include <hip/hip_runtime.h>
 
 #include <new>
@@ -16,6 +24,8 @@
 #include "ks.h"
 #include "ks_ctx.hpp"
 #include "ks_scan.hpp"
+#include "ks_select.hpp"
+#include "ks_split.hpp"
 #include "ks_wave.hpp"
 
 using namespace ks_host;
@@ -23,9 +33,8 @@ using namespace ks_host;
 namespace ks_host {
 
 void free_seg(SegBuffers& b) {
-  void* dev[] = {b.win[0], b.win[1], b.wser[0], b.wser[1], b.wstart[0], b.wstart[1], b.res, b.ctr, b.rows};
-  for (void* p : dev) (void)hipFree(p);
-  if (b.host_ctr) (void)hipHostFree(b.host_ctr);
+  (void)hipFree(b.rows);
+  (void)hipFree(b.ticket);
   b = SegBuffers{};
 }
 
@@ -33,206 +42,315 @@ void free_seg(SegBuffers& b) {
 
 namespace {
 
-constexpr uint32_t kSegNT = 256;
-constexpr uint32_t kSegGrid = 2048;      // workgroups of a window-scan launch (grid-stride over the windows)
-constexpr uint32_t kSegSplitGrid = 256;  // workgroups of a split launch
-constexpr uint32_t kSegDepths = KS_MAX_K + 1;  // counter pairs: a window of a later depth is a part of one before it
+constexpr int kTreeNT = 1024;
+constexpr uint32_t kTreeW = kTreeNT / ks::kWave;
 
-// Depth 0: the full scan of series blockIdx.x (as scan_kernel, in workgroups
-// of kSegRootNT threads: the streaming depth is HBM-bound like the plain
-// scan), also storing each row's moments and minimum at rows[s * row_stride + i].
-// The rows' minima wait in the key buffer (free until the keys are made) and
-// the records are written once the series is streamed, consecutive threads
-// taking consecutive rows, rather than one 24-byte store per row as it ends.
-constexpr int kSegRootNT = 512;
+constexpr uint32_t kSmall = ks::kWave;  // windows of up to this many rows are a wave's work
 
 template <int KMAX>
-__global__ __launch_bounds__(kSegRootNT) void seg_root_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
-                                                       const ks_desc* __restrict__ desc, uint32_t num_series,
-                                                       ks_params prm, uint32_t max_K, ks_result* __restrict__ out,
-                                                       ks::RowMom* __restrict__ rows, uint32_t row_stride) {
-  using S = ks::ScanShape<KMAX, kSegRootNT, kRB>;
-  __shared__ ks::ScanSmem<KMAX, kSegRootNT, kRB> sm;
-  const uint32_t s = blockIdx.x;
-  if (s >= num_series) return;
+struct TreeSmem {
+  uint64_t s1[KMAX], s2lo[KMAX];  // the series' rows
+  uint32_t s2hi[KMAX], rmin[KMAX];
+  union {
+    struct {  // a window that the workgroup shares
+      uint64_t lo[KMAX], hi[KMAX];
+      uint32_t rank[KMAX];
+      __align__(16) uint16_t is[KMAX];
+      uint16_t pos[KMAX];
+      uint64_t tie[(KMAX + ks::kWave - 1) / ks::kWave];
+      uint32_t partU[kTreeNT], bestU[kTreeW], bestC[kTreeW], red[kTreeW];
+    };
+    struct {  // a wave's window
+      uint64_t lo[kSmall], hi[kSmall];
+      uint64_t stack[kSmall / 2];
+      uint32_t order[kSmall];
+    } wave[kTreeW];
+  };
+  // open windows, a | b << 16 | depth << 32, disjoint: those of more than
+  // kSmall rows (the workgroup's stack), and the others (the waves' list)
+  uint64_t stack[KMAX / kSmall + 1], small[KMAX / 2];
+  uint32_t fU[KMAX];              // boundaries found: statistic, window, split, depth
+  uint16_t fa[KMAX], fb[KMAX], fc[KMAX], fd[KMAX];
+  uint32_t split;                 // the window's split if significant, else 0
+  uint32_t found, next;           // the waves' counters
+};
+
+__device__ __forceinline__ uint64_t pack_window(uint32_t a, uint32_t b, uint32_t depth) {
+  return (uint64_t)depth << 32 | (uint64_t)b << 16 | a;
+}
+
+// A window of at most kSmall rows and every window that opens inside it, by the
+// calling wave: a row per lane, keys and order in the wave's own LDS, no
+// workgroup barrier.
+template <int KMAX>
+__device__ __forceinline__ void tree_small(TreeSmem<KMAX>& sm, uint64_t window, uint32_t N, double c_alpha,
+                                           uint32_t max_levels, uint32_t w, uint32_t lane) {
+  auto& S = sm.wave[w];
+  uint32_t top = 0;
+  for (;;) {
+    const uint32_t a = (uint32_t)window & 0xffffu, b = (uint32_t)(window >> 16) & 0xffffu;
+    const uint32_t depth = (uint32_t)(window >> 32), K = b - a;
+    const bool row = lane < K;
+    const uint32_t at = a + (row ? lane : 0u);
+    const uint32_t gmin = ks::wave_min_u32(sm.rmin[at]);
+    const ks::SortKey k = ks::sort_key(sm.s1[at], sm.s2lo[at], sm.s2hi[at], lane, N, gmin);
+    const bool wide = ks::ballot(row && k.hi != 0) != 0;
+    S.lo[lane] = k.lo;
+    S.hi[lane] = k.hi;
+    ks::wave_lds_sync();
+    const uint32_t rank = ks::count_below(S.lo, S.hi, 0, K, k.lo, k.hi, wide);
+    if (row) S.order[rank] = lane;
+    ks::wave_lds_sync();
+    // lane p: the row at sorted position p
+    const uint32_t mine = S.order[row ? lane : 0u], after = S.order[lane + 1 < K ? lane + 1 : 0u];
+    const bool end = row && (lane + 1 == K || ks::group_end(ks::SortKey{S.lo[mine], S.hi[mine]},
+                                                            ks::SortKey{S.lo[after], S.hi[after]}));
+    const uint64_t tie = ks::ballot(end);
+    const int32_t c = (int32_t)lane + 1, up = (int32_t)K - c;
+    int32_t D = 0, mx = 0, mn = 0;
+    for (uint32_t p = 0; p < K; ++p) {
+      const int32_t r = __builtin_amdgcn_readlane((int)mine, (int)p);
+      D += r < c ? up : -c;
+      if ((tie >> p) & 1u) {
+        mx = max(mx, D);
+        mn = min(mn, D);
+      }
+    }
+    uint32_t bU = (uint32_t)c < K ? (uint32_t)max(mx, -mn) : 0u, bC = (uint32_t)c < K ? (uint32_t)c : 0u;
+    ks::wave_best(bU, bC, K);
+    if (ks::significant(bU, bC, K, c_alpha)) {
+      if (lane == 0) {
+        const uint32_t n = atomicAdd(&sm.found, 1u);
+        sm.fU[n] = bU;
+        sm.fa[n] = (uint16_t)a;
+        sm.fb[n] = (uint16_t)b;
+        sm.fc[n] = (uint16_t)(a + bC);
+        sm.fd[n] = (uint16_t)depth;
+      }
+      if (max_levels == 0 || depth + 1 < max_levels) {
+        if (K - bC >= 2) S.stack[top++] = pack_window(a + bC, b, depth + 1);  // every lane the same value
+        if (bC >= 2) S.stack[top++] = pack_window(a, a + bC, depth + 1);
+      }
+    }
+    ks::wave_lds_sync();
+    if (top == 0) return;
+    window = S.stack[--top];
+    window = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(window >> 32)) << 32 |
+             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)window);
+    ks::wave_lds_sync();
+  }
+}
+
+// The most significant split of the window of rows a .. a + K - 1; sm.split gets
+// it if it is significant, and record n of the boundaries is written then.
+template <int KMAX>
+__device__ __forceinline__ void tree_window(TreeSmem<KMAX>& sm, uint32_t a, uint32_t K, uint32_t depth, uint32_t N,
+                                            double c_alpha, uint32_t n) {
+  const uint32_t tid = threadIdx.x, lane = ks::lane_id(), w = ks::wave_id();
+  uint32_t mn = 0xffffffffu;
+  for (uint32_t i = tid; i < K; i += kTreeNT) mn = min(mn, sm.rmin[a + i]);
+  const uint32_t gmin = ks::block_min_u32<kTreeNT>(mn, sm.red);
+  bool w53 = false;
+  for (uint32_t i = tid; i < K; i += kTreeNT) {
+    const ks::SortKey k = ks::sort_key(sm.s1[a + i], sm.s2lo[a + i], sm.s2hi[a + i], i, N, gmin);
+    sm.lo[i] = k.lo;
+    sm.hi[i] = k.hi;
+    sm.rank[i] = 0;
+    w53 |= k.hi != 0;
+  }
+  const bool wide = ks::block_any<kTreeNT>(w53, sm.red);
+  {  // several threads count for one row where there are fewer rows than threads
+    const uint32_t KR = min((K + ks::kWave - 1u) & ~(uint32_t)(ks::kWave - 1), (uint32_t)kTreeNT), P = kTreeNT / KR;
+    const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
+    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
+    if (q < P)
+      for (uint32_t i = i0; i < K; i += KR)
+        atomicAdd(&sm.rank[i], ks::count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < K; i += kTreeNT) {
+    const uint32_t p = sm.rank[i];
+    sm.is[p] = (uint16_t)i;
+    sm.pos[i] = (uint16_t)p;
+  }
+  __syncthreads();
+  bool tied = false;
+  for (uint32_t p0 = w * ks::kWave; p0 < K; p0 += kTreeNT) {
+    const uint32_t p = p0 + lane;
+    bool end = false;
+    if (p < K) {
+      const uint32_t i = sm.is[p], j = sm.is[min(p + 1, K - 1)];
+      end = p + 1 == K || ks::group_end(ks::SortKey{sm.lo[i], sm.hi[i]}, ks::SortKey{sm.lo[j], sm.hi[j]});
+    }
+    const uint64_t m = ks::ballot(end);
+    if (lane == 0) sm.tie[p0 / ks::kWave] = m;
+    tied |= m != ks::ballot(p < K);
+  }
+  const bool ties = ks::block_any<kTreeNT>(tied, sm.red);
+  // 64-candidate slots: the waves of a slot share the positions (shares of a
+  // multiple of 8), or a wave walks its slots one after the other
+  const uint32_t ns = (K - 1u + ks::kWave - 1u) / ks::kWave;
+  uint32_t bU = 0, bC = 0;
+  if (ns < kTreeW) {
+    const uint32_t Q = kTreeW / ns, slot = w / Q, share = w % Q;
+    const uint32_t len = ((K + Q - 1) / Q + 7u) & ~7u;
+    uint32_t c[1] = {1u + slot * ks::kWave + lane}, U[1] = {0};
+    if (slot < ns) {
+      const uint32_t pa = min(K, share * len), pb = min(K, pa + len);
+      if (pa < pb) ks::walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, pa, pb, c, U);
+    }
+    sm.partU[tid] = U[0];
+    __syncthreads();
+    if (slot < ns && share == 0) {
+      for (uint32_t q = 1; q < Q; ++q) U[0] = max(U[0], sm.partU[tid + q * ks::kWave]);
+      if (c[0] < K) {
+        bU = U[0];
+        bC = c[0];
+      }
+    }
+  } else {
+    for (uint32_t slot = w; slot < ns; slot += kTreeW) {
+      uint32_t c[1] = {1u + slot * ks::kWave + lane}, U[1];
+      ks::walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, 0, K, c, U);
+      if (c[0] < K && (bC == 0 || ks::more_significant(U[0], c[0], bU, bC, K))) {
+        bU = U[0];
+        bC = c[0];
+      }
+    }
+  }
+  ks::wave_best(bU, bC, K);
+  if (lane == 0) {
+    sm.bestU[w] = bU;
+    sm.bestC[w] = bC;
+  }
+  __syncthreads();
+  if (w == 0) {
+    bU = lane < kTreeW ? sm.bestU[lane] : 0u;
+    bC = lane < kTreeW ? sm.bestC[lane] : 0u;
+    ks::wave_best(bU, bC, K);
+    if (lane == 0) {
+      const bool sig = ks::significant(bU, bC, K, c_alpha);
+      sm.split = sig ? bC : 0u;
+      if (sig) {
+        sm.fU[n] = bU;
+        sm.fa[n] = (uint16_t)a;
+        sm.fb[n] = (uint16_t)(a + K);
+        sm.fc[n] = (uint16_t)(a + bC);
+        sm.fd[n] = (uint16_t)depth;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// rows: the moments of series s at s * max_K (nullptr: streamed here).
+template <int KMAX>
+__global__ __launch_bounds__(kTreeNT) void seg_tree_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
+                                                           const ks_desc* __restrict__ desc, ks_params prm,
+                                                           uint32_t max_K, const ks::RowMom* __restrict__ rows,
+                                                           uint32_t max_levels, uint32_t max_cp,
+                                                           ks_result* __restrict__ cps, uint32_t* __restrict__ counts) {
+  __shared__ TreeSmem<KMAX> sm;
+  const uint32_t s = blockIdx.x, tid = threadIdx.x, lane = ks::lane_id();
   const ks_desc d = desc[s];
-  const uint32_t bad = ks::check_desc(d, num_samples, max_K);
-  if (bad) {
-    if (threadIdx.x == 0) ks::write_result(out + s, 0, 0, 0, 0, 0.0, 0.0, 1.0, bad);
+  if (ks::check_desc(d, num_samples, max_K)) {
+    if (tid == 0) counts[s] = KS_SEGMENT_BAD;
     return;
   }
-  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
-  ks::RowMom* rm = rows + (uint64_t)s * row_stride;
-  const uint32_t mn = ks::stream_rows<true>(samples, d.offset, d.N, w, d.K, S::W, lane,
-                                            [&](uint32_t i, uint64_t s1, uint64_t s2, uint32_t s2h, uint32_t rmin) {
-                                              if (lane == 0) {
-                                                sm.u.mom.s1[i] = s1;
-                                                sm.u.mom.s2lo[i] = s2;
-                                                sm.u.mom.s2hi[i] = s2h;
-                                                sm.key[0][i] = rmin;
-                                              }
-                                            });
-  const uint32_t gmin = ks::block_min_u32<kSegRootNT>(mn, sm.red);  // its barriers publish the rows
-  for (uint32_t i = threadIdx.x; i < d.K; i += kSegRootNT)
-    rm[i] = ks::RowMom{sm.u.mom.s1[i], sm.u.mom.s2lo[i], sm.u.mom.s2hi[i], sm.key[0][i]};
-  __syncthreads();  // the minima are read before the keys overwrite them
-  ks::finish_series(sm, d.K, d.N, gmin, prm, out + s, nullptr);
-}
-
-// Depth >= 1: windows t = blockIdx.x, + gridDim.x, ... below *count (series
-// wser[t], rows wstart[t] .. + win[t].K) from the stored row moments; a
-// window's eq. 2 minimum is the least of its rows' minima.
-template <int KMAX>
-__global__ __launch_bounds__(kNT) void seg_window_kernel(const ks_desc* __restrict__ win,
-                                                         const uint32_t* __restrict__ count,
-                                                         const uint32_t* __restrict__ wser,
-                                                         const uint32_t* __restrict__ wstart, ks_params prm,
-                                                         const ks::RowMom* __restrict__ rows, uint32_t row_stride,
-                                                         ks_result* __restrict__ out) {
-  __shared__ ks::ScanSmem<KMAX, kNT, kRB> sm;
-  const uint32_t n = *count;
-  for (uint32_t t = blockIdx.x; t < n; t += gridDim.x) {
-    __syncthreads();  // the previous window's reads of sm are done
-    const ks_desc d = win[t];
-    const uint32_t K = d.K;
-    if (K < 2 || K > (uint32_t)KMAX) {  // never opened by the split kernel
-      if (threadIdx.x == 0) ks::write_result(out + t, 0, 0, 0, 0, 0.0, 0.0, 1.0, KS_BAD_SHAPE);
-      continue;
-    }
-    const ks::RowMom* rm = rows + (uint64_t)wser[t] * row_stride + wstart[t];
-    uint32_t mn = 0xffffffffu;
-    for (uint32_t i = threadIdx.x; i < K; i += kNT) {
+  const uint32_t K = d.K, N = d.N;
+  if (rows) {
+    const ks::RowMom* rm = rows + (uint64_t)s * max_K;
+    for (uint32_t i = tid; i < K; i += kTreeNT) {
       const ks::RowMom r = rm[i];
-      sm.u.mom.s1[i] = r.s1;
-      sm.u.mom.s2lo[i] = r.s2lo;
-      sm.u.mom.s2hi[i] = r.s2hi;
-      mn = min(mn, r.pad);
+      sm.s1[i] = r.s1;
+      sm.s2lo[i] = r.s2lo;
+      sm.s2hi[i] = r.s2hi;
+      sm.rmin[i] = r.pad;
     }
-    const uint32_t gmin = ks::block_min_u32<kNT>(mn, sm.red);  // its barriers also publish the moments
-    ks::finish_series(sm, K, d.N, gmin, prm, out + t, nullptr);
+  } else {
+    ks::stream_rows<true>(samples, d.offset, N, ks::wave_id(), K, kTreeW, lane,
+                          [&](uint32_t i, uint64_t s1, uint64_t s2, uint32_t s2h, uint32_t rmin) {
+                            if (lane == 0) {
+                              sm.s1[i] = s1;
+                              sm.s2lo[i] = s2;
+                              sm.s2hi[i] = s2h;
+                              sm.rmin[i] = rmin;
+                            }
+                          });
+  }
+  uint32_t top = 0, small = 0, found = 0;  // every thread keeps the same
+  auto open = [&](uint32_t a, uint32_t b, uint32_t depth) {
+    const bool big = b - a > kSmall;
+    if (tid == 0) (big ? sm.stack[top] : sm.small[small]) = pack_window(a, b, depth);
+    big ? ++top : ++small;
+  };
+  open(0, K, 0);
+  while (top > 0) {
+    __syncthreads();
+    const uint64_t e = sm.stack[--top];
+    const uint32_t a = (uint32_t)e & 0xffffu, b = (uint32_t)(e >> 16) & 0xffffu, depth = (uint32_t)(e >> 32);
+    tree_window<KMAX>(sm, a, b - a, depth, N, prm.c_alpha, found);
+    const uint32_t c = sm.split;
+    if (c == 0) continue;
+    ++found;
+    if (max_levels != 0 && depth + 1 >= max_levels) continue;
+    if (b - a - c >= 2) open(a + c, b, depth + 1);
+    if (c >= 2) open(a, a + c, depth + 1);
+  }
+  if (tid == 0) {
+    sm.found = found;
+    sm.next = 0;
+  }
+  __syncthreads();
+  for (;;) {  // the small windows, a wave each
+    uint32_t j = 0;
+    if (lane == 0) j = atomicAdd(&sm.next, 1u);
+    j = (uint32_t)__builtin_amdgcn_readfirstlane((int)j);
+    if (j >= small) break;
+    tree_small<KMAX>(sm, sm.small[j], N, prm.c_alpha, max_levels, ks::wave_id(), lane);
+  }
+  __syncthreads();
+  found = sm.found;
+  if (tid == 0) counts[s] = found;
+  ks_result* out = cps + (uint64_t)s * max_cp;
+  for (uint32_t j = tid; j < found; j += kTreeNT) {
+    const uint32_t cp = sm.fc[j];
+    uint32_t at = 0;
+    for (uint32_t q = 0; q < found; ++q) at += sm.fc[q] < cp ? 1u : 0u;
+    if (at >= max_cp) continue;
+    ks_result r;
+    const uint32_t a = sm.fa[j];
+    ks::write_choice(&r, sm.fU[j], cp - a, sm.fb[j] - a, prm, 0u);
+    r.cp = cp;
+    r.pad = sm.fd[j];
+    out[at] = r;
   }
 }
 
-template <template <int> class KERNEL, typename... Args>
-void launch_kc(int kc, uint32_t grid, hipStream_t st, Args... args) {
-  switch (kc) {
-    case 0: hipLaunchKernelGGL(KERNEL<64>::f, dim3(grid), dim3(KERNEL<64>::nt), 0, st, args...); break;
-    case 1: hipLaunchKernelGGL(KERNEL<128>::f, dim3(grid), dim3(KERNEL<128>::nt), 0, st, args...); break;
-    case 2: hipLaunchKernelGGL(KERNEL<256>::f, dim3(grid), dim3(KERNEL<256>::nt), 0, st, args...); break;
-    case 3: hipLaunchKernelGGL(KERNEL<512>::f, dim3(grid), dim3(KERNEL<512>::nt), 0, st, args...); break;
-    case 4: hipLaunchKernelGGL(KERNEL<1024>::f, dim3(grid), dim3(KERNEL<1024>::nt), 0, st, args...); break;
-    default: hipLaunchKernelGGL(KERNEL<2048>::f, dim3(grid), dim3(KERNEL<2048>::nt), 0, st, args...);
-  }
-}
 template <int KMAX>
-struct RootK {
-  static constexpr auto f = seg_root_kernel<KMAX>;
-  static constexpr int nt = kSegRootNT;
-};
-template <int KMAX>
-struct WindowK {
-  static constexpr auto f = seg_window_kernel<KMAX>;
-  static constexpr int nt = kNT;
-};
-
-// One thread per open window of depth `depth` (n of them, or *count when
-// count is given), grid-stride. Window t is series wser[t] (t itself at
-// depth 0) starting at row wstart[t] (0 at depth 0). ctr: the next depth's
-// window count and largest K.
-__global__ __launch_bounds__(kSegNT) void seg_split_kernel(
-    const ks_desc* __restrict__ win, const ks_result* __restrict__ res, uint32_t n, const uint32_t* __restrict__ count,
-    const uint32_t* __restrict__ wser, const uint32_t* __restrict__ wstart, uint32_t depth, int open_next,
-    ks_desc* __restrict__ next, uint32_t* __restrict__ nser, uint32_t* __restrict__ nstart, uint32_t* __restrict__ ctr,
-    uint64_t cap, ks_result* __restrict__ cps, uint32_t* __restrict__ counts, uint32_t max_cp) {
-  if (count) n = *count;
-  for (uint32_t t = blockIdx.x * kSegNT + threadIdx.x; t < n; t += gridDim.x * kSegNT) {
-  const ks_result r = res[t];
-  const uint32_t s = wser ? wser[t] : t;
-  const uint32_t a = wstart ? wstart[t] : 0u;
-  if (r.flags & (KS_BAD_SHAPE | KS_OUT_OF_RANGE)) {
-    // only a caller's descriptor can be malformed: every later window lies inside a valid series
-    if (depth == 0) counts[s] = KS_SEGMENT_BAD;
-    continue;
-  }
-  if (!(r.flags & KS_SIGNIFICANT)) continue;
-  const ks_desc d = win[t];
-  const uint32_t slot = atomicAdd(&counts[s], 1u);
-  if (slot < max_cp) {
-    ks_result o = r;
-    o.cp = a + r.cp;
-    o.pad = depth;
-    cps[(uint64_t)s * max_cp + slot] = o;
-  }
-  if (!open_next) continue;
-  const uint32_t kl = r.cp, kr = d.K - r.cp;
-  if (kl >= 2) {
-    const uint32_t i = atomicAdd(&ctr[0], 1u);
-    if (i < cap) {
-      next[i] = ks_desc{d.offset, kl, d.N, 0};
-      nser[i] = s;
-      nstart[i] = a;
-      atomicMax(&ctr[1], kl);
-    }
-  }
-  if (kr >= 2) {
-    const uint32_t i = atomicAdd(&ctr[0], 1u);
-    if (i < cap) {
-      next[i] = ks_desc{d.offset + (uint64_t)r.cp * d.N, kr, d.N, 0};
-      nser[i] = s;
-      nstart[i] = a + r.cp;
-      atomicMax(&ctr[1], kr);
-    }
-  }
-  }
+void launch_tree(uint32_t num_series, hipStream_t st, const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,
+                 const ks_params& prm, uint32_t max_K, const ks::RowMom* rows, uint32_t max_levels, uint32_t max_cp,
+                 ks_result* cps, uint32_t* counts) {
+  hipLaunchKernelGGL(seg_tree_kernel<KMAX>, dim3(num_series), dim3(kTreeNT), 0, st, samples, num_samples, desc, prm,
+                     max_K, rows, max_levels, max_cp, cps, counts);
 }
 
-// Sort each series' stored boundaries by cp (insertion sort; one thread per
-// series, positions are distinct).
-__global__ __launch_bounds__(kSegNT) void seg_sort_kernel(ks_result* __restrict__ cps,
-                                                          const uint32_t* __restrict__ counts, uint32_t num_series,
-                                                          uint32_t max_cp) {
-  const uint32_t s = blockIdx.x * kSegNT + threadIdx.x;
-  if (s >= num_series) return;
-  const uint32_t c = counts[s];
-  if (c == KS_SEGMENT_BAD) return;
-  const uint32_t k = c < max_cp ? c : max_cp;
-  ks_result* v = cps + (uint64_t)s * max_cp;
-  for (uint32_t i = 1; i < k; ++i) {
-    const ks_result x = v[i];
-    uint32_t j = i;
-    while (j > 0 && v[j - 1].cp > x.cp) {
-      v[j] = v[j - 1];
-      --j;
-    }
-    v[j] = x;
-  }
-}
-
-template <typename T>
-bool alloc(T*& p, uint64_t n) {
-  return hipMalloc(&p, sizeof(T) * (n ? n : 1)) == hipSuccess;
-}
-
-int ensure_seg(ks_ctx* c, uint64_t cap, uint64_t rows) {
+int ensure_seg(ks_ctx* c, uint64_t rows, uint64_t series) {
   SegBuffers& b = c->seg;
-  if (cap <= b.cap && rows <= b.cap_rows) return KS_OK;
-  if (cap < b.cap) cap = b.cap;
+  if (rows <= b.cap_rows && series <= b.cap_series) return KS_OK;
   if (rows < b.cap_rows) rows = b.cap_rows;
+  if (series < b.cap_series) series = b.cap_series;
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_seg(b);
-  bool ok = alloc(b.win[0], cap) && alloc(b.win[1], cap) && alloc(b.wser[0], cap) && alloc(b.wser[1], cap) &&
-            alloc(b.wstart[0], cap) && alloc(b.wstart[1], cap) && alloc(b.res, cap) &&
-            alloc(b.ctr, 2 * kSegDepths) && alloc(b.rows, rows) &&
-            hipHostMalloc(reinterpret_cast<void**>(&b.host_ctr), 2 * kSegDepths * sizeof(uint32_t),
-                          hipHostMallocDefault) == hipSuccess;
-  if (!ok) {
+  if (hipMalloc(&b.rows, sizeof(ks::RowMom) * rows) != hipSuccess ||
+      hipMalloc(&b.ticket, sizeof(uint32_t) * series) != hipSuccess) {
     free_seg(b);
     (void)hipGetLastError();
     return KS_E_NOMEM;
   }
-  b.cap = cap;
   b.cap_rows = rows;
+  b.cap_series = series;
   return KS_OK;
 }
 
@@ -249,61 +367,26 @@ extern "C" int ks_segment_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t n
   if (max_K < 2 || max_K > KS_MAX_K) return KS_E_RANGE;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  // the windows of one depth are disjoint row ranges of >= 2 rows of their series
-  const uint64_t cap = (uint64_t)num_series * (max_K / 2 > 1 ? max_K / 2 : 1);
-  if (int rc = ensure_seg(ctx, cap, (uint64_t)num_series * max_K)) return rc;
-  SegBuffers& b = ctx->seg;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = hipMemsetAsync(counts, 0, sizeof(uint32_t) * num_series, st);
-  if (e != hipSuccess) return hip_fail(e, "counts reset");
-  if ((e = hipMemsetAsync(b.ctr, 0, 2 * sizeof(uint32_t) * kSegDepths, st)) != hipSuccess)
-    return hip_fail(e, "window counters");
-  // a window of depth d >= 1 has at most max_K - d rows, so depth max_K - 1 opens none
-  const uint32_t limit = max_levels == 0 || max_levels > max_K - 1 ? max_K - 1 : max_levels;
-  const uint32_t wgrid = (uint32_t)(b.cap < kSegGrid ? b.cap : kSegGrid);
-  const uint32_t sgrid = (uint32_t)((b.cap + kSegNT - 1) / kSegNT < kSegSplitGrid ? (b.cap + kSegNT - 1) / kSegNT
-                                                                                     : kSegSplitGrid);
-  // depth 0: every series
-  launch_kc<RootK>(k_class(max_K), num_series, st, samples, num_samples, desc, num_series, *params, max_K, b.res,
-                   b.rows, max_K);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "root scan launch");
-  hipLaunchKernelGGL(seg_split_kernel, dim3((num_series + kSegNT - 1) / kSegNT), dim3(kSegNT), 0, st, desc, b.res,
-                     num_series, (const uint32_t*)nullptr, (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0u,
-                     (int)(limit > 1), b.win[0], b.wser[0], b.wstart[0], b.ctr + 2, b.cap, cps, counts, max_cp);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "split launch");
-  // later depths in chunks of 4, 8, 16, ... between read-backs of their window counts; a
-  // depth whose count is 0 costs two near-empty launches
-  uint32_t roundK = max_K;
-  uint32_t depth = 1, chunk = 4;
-  while (depth < limit) {
-    const uint32_t end = depth + chunk < limit ? depth + chunk : limit;
-    for (uint32_t d = depth; d < end; ++d) {
-      const int src = (d - 1) & 1, dst = d & 1;
-      launch_kc<WindowK>(k_class(roundK), wgrid, st, b.win[src], (const uint32_t*)(b.ctr + 2 * d), b.wser[src],
-                         b.wstart[src], *params, (const ks::RowMom*)b.rows, max_K, b.res);
-      if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "window scan launch");
-      hipLaunchKernelGGL(seg_split_kernel, dim3(sgrid), dim3(kSegNT), 0, st, b.win[src], b.res, 0u,
-                         (const uint32_t*)(b.ctr + 2 * d), b.wser[src], b.wstart[src], d, (int)(d + 1 < limit),
-                         b.win[dst], b.wser[dst], b.wstart[dst], b.ctr + 2 * (d + 1), b.cap, cps, counts, max_cp);
-      if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "split launch");
-    }
-    // counts of depths depth + 1 .. end
-    if ((e = hipMemcpyAsync(b.host_ctr, b.ctr + 2 * (depth + 1), 2 * sizeof(uint32_t) * (end - depth),
-                            hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-      return hip_fail(e, "window count");
-    bool open = false;
-    for (uint32_t d = 0; d < end - depth; ++d) {
-      if (b.host_ctr[2 * d] > b.cap) return KS_E_STATE;  // cannot happen: windows of a depth are disjoint
-      open = b.host_ctr[2 * d] > 0;
-      if (open && b.host_ctr[2 * d + 1] >= 2) roundK = b.host_ctr[2 * d + 1];
-    }
-    if (!open) break;
-    depth = end;
-    chunk *= 2;
+  const ks::RowMom* rows = nullptr;
+  // fewer than two workgroups per CU: the rows are spread over the device first
+  if (num_series < 2u * (uint32_t)ctx->num_cus) {
+    if (int rc = ensure_seg(ctx, (uint64_t)num_series * max_K, num_series)) return rc;
+    const ks::SplitWs ws{ctx->seg.rows, nullptr, nullptr, ctx->seg.ticket};
+    ks::launch_split_moments(samples, num_samples, desc, num_series, max_K, nullptr, ws, st);
+    rows = ctx->seg.rows;
   }
-  hipLaunchKernelGGL(seg_sort_kernel, dim3((num_series + kSegNT - 1) / kSegNT), dim3(kSegNT), 0, st, cps, counts,
-                     num_series, max_cp);
-  e = hipGetLastError();
-  return e == hipSuccess ? KS_OK : hip_fail(e, "sort launch");
+  auto run = [&](auto f) {
+    f(num_series, st, samples, num_samples, desc, *params, max_K, rows, max_levels, max_cp, cps, counts);
+  };
+  switch (k_class(max_K)) {
+    case 0: run(launch_tree<64>); break;
+    case 1: run(launch_tree<128>); break;
+    case 2: run(launch_tree<256>); break;
+    case 3: run(launch_tree<512>); break;
+    case 4: run(launch_tree<1024>); break;
+    default: run(launch_tree<2048>);
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? KS_OK : hip_fail(e, "segmentation launch");
 }

@@ -30,6 +30,7 @@
 
 namespace ks {
 
+constexpr uint32_t kSplitWGs = 2048;  // eight workgroups per CU stream the rows
 constexpr uint32_t kSplitNT = 256;
 constexpr uint32_t kSplitWalkNT = 512;
 constexpr uint32_t kSplitSlots = KS_MAX_K / kWave;  // 64-candidate slots of a series
@@ -80,6 +81,8 @@ __device__ __forceinline__ bool block_any(bool v, uint32_t* red) {
   return any != 0;
 }
 
+namespace {  // kernels are compiled into each translation unit that launches them
+
 __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t* __restrict__ samples,
                                                                  uint64_t num_samples, const ks_desc* __restrict__ desc,
                                                                  uint32_t max_K, ks_result* __restrict__ out,
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t*
   const ks_desc d = desc[s];
   const uint32_t bad = check_desc(d, num_samples, max_K);
   if (bad) {
-    if (c == 0 && threadIdx.x == 0) write_result(out + s, 0, 0, 0, 0, 0.0, 0.0, 1.0, bad);
+    if (out && c == 0 && threadIdx.x == 0) write_result(out + s, 0, 0, 0, 0, 0.0, 0.0, 1.0, bad);
     return;
   }
   if (c == 0 && threadIdx.x == 0) ws.ticket[s] = 0;
@@ -151,6 +154,15 @@ __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t*
       mom[i] = RowMom{t1, (uint64_t)t2, (uint32_t)(t2 >> 64), tm};
     }
   }
+}
+
+// out: where series of a bad shape or range are flagged (nullable).
+inline void launch_split_moments(const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,
+                                 uint32_t num_series, uint32_t max_K, ks_result* out, const SplitWs& ws,
+                                 hipStream_t st) {
+  const uint32_t chunks = (kSplitWGs + num_series - 1) / num_series;
+  hipLaunchKernelGGL(split_moments_kernel, dim3(chunks < max_K ? chunks : max_K, num_series), dim3(kSplitNT), 0, st,
+                     samples, num_samples, desc, max_K, out, ws);
 }
 
 __global__ __launch_bounds__(kSplitNT) void split_rank_kernel(uint64_t num_samples, const ks_desc* __restrict__ desc,
@@ -358,4 +370,5 @@ __global__ __launch_bounds__(kTinyNT) void tiny_scan_kernel(const uint32_t* __re
   write_choice(out + s, bU, bC, K, prm, 0u);
 }
 
+}  // namespace
 }  // namespace ks

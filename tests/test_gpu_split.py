@@ -10,6 +10,8 @@ import oracle as O
 import paper_2511_05958_amd as P
 
 from test_gpu_learned import _pack, gpu_features, series
+from test_gpu_segment import check_series
+from test_gpu_segment import run as run_segment
 from test_gpu_stats import gpu_stats, same
 
 pytestmark = pytest.mark.gpu
@@ -134,3 +136,21 @@ def test_split_scan_series_counts(ctx, num):
         torch.cuda.synchronize()
         g = P.results_to_numpy(out)
         assert g["flags"][0] == P.KS_BAD_SHAPE and g["cp"][0] == 0 and (g["flags"][1:] & P.KS_BAD_SHAPE == 0).all()
+
+
+@pytest.mark.parametrize("num,K", [(1, 2), (3, 65), (2, 1025), (1, 2048), (511, 24), (512, 24)])
+@pytest.mark.parametrize("kind", ["level", "ties", "wide"])
+def test_segment_edges(ctx, num, K, kind):
+    """Windows around the 64-row and 64-candidate slots and past the workgroup's
+    threads; both sides of the batch size from which a workgroup streams its rows."""
+    rng = np.random.default_rng(K)
+    ss = [_sweep(rng, K if num < 8 else int(rng.integers(2, K)), 7 if K > 100 else 12, kind) for _ in range(num)]
+    if K > 100:  # more levels, so that windows of every size open
+        for r in ss:
+            r[K // 2:K // 2 + 40] += 500
+            r[K - 70:] += 900
+    x, d = _pack(ss, gap=1)
+    cps, counts = run_segment(ctx, x, d, K)
+    for t, r in enumerate(ss):
+        if num < 8 or t % 37 == 0:
+            check_series(cps[t], int(counts[t]), O.segment(r), t)
