@@ -12,7 +12,8 @@
 // (One launch per depth for all open windows, with a split kernel after each, a
 // read-back of the window counts every few depths and a sort at the end took 14
 // depths x 10 - 25 us after a root pass of 107 us on 512 series of 256 rows of
-// 1024 samples, 331 us a call, most depths with a handful of windows.)
+// 1024 samples, 333 us a call, most depths with a handful of windows; the call
+// takes 148 us now, of which the rows' stream is about 95.)
 //
 // A workgroup streams its own series' rows when there are enough series to keep
 // HBM busy that way; with fewer, split_moments_kernel has spread the rows over
@@ -77,6 +78,15 @@ struct TreeSmem {
 
 __device__ __forceinline__ uint64_t pack_window(uint32_t a, uint32_t b, uint32_t depth) {
   return (uint64_t)depth << 32 | (uint64_t)b << 16 | a;
+}
+
+// Publishes this thread's LDS writes to the workgroup. The wait is written out:
+// for a barrier at the head of a loop the compiler left out the wait for LDS
+// writes that reach it over the back edge (a push onto the stack), and the other
+// waves then read the entry before it was there.
+__device__ __forceinline__ void publish() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
 }
 
 // A window of at most kSmall rows and every window that opens inside it, by the
@@ -285,23 +295,28 @@ __global__ __launch_bounds__(kTreeNT) void seg_tree_kernel(const uint32_t* __res
     big ? ++top : ++small;
   };
   open(0, K, 0);
-  while (top > 0) {
-    __syncthreads();
+  publish();
+  while (top > 0) {  // what is read from LDS here is the same for every thread: scalars, so that the loop is the scalar unit's
     const uint64_t e = sm.stack[--top];
-    const uint32_t a = (uint32_t)e & 0xffffu, b = (uint32_t)(e >> 16) & 0xffffu, depth = (uint32_t)(e >> 32);
+    const uint32_t ab = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
+    const uint32_t depth = (uint32_t)__builtin_amdgcn_readfirstlane((int)(e >> 32));
+    const uint32_t a = ab & 0xffffu, b = ab >> 16;
     tree_window<KMAX>(sm, a, b - a, depth, N, prm.c_alpha, found);
-    const uint32_t c = sm.split;
-    if (c == 0) continue;
-    ++found;
-    if (max_levels != 0 && depth + 1 >= max_levels) continue;
-    if (b - a - c >= 2) open(a + c, b, depth + 1);
-    if (c >= 2) open(a, a + c, depth + 1);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.split);
+    if (c != 0) {
+      ++found;
+      if (max_levels == 0 || depth + 1 < max_levels) {
+        if (b - a - c >= 2) open(a + c, b, depth + 1);
+        if (c >= 2) open(a, a + c, depth + 1);
+      }
+    }
+    publish();
   }
   if (tid == 0) {
     sm.found = found;
     sm.next = 0;
   }
-  __syncthreads();
+  publish();
   for (;;) {  // the small windows, a wave each
     uint32_t j = 0;
     if (lane == 0) j = atomicAdd(&sm.next, 1u);
