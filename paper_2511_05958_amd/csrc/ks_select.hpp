@@ -93,6 +93,35 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The window's accesses, every lane 64 bytes of it. Lane after lane 64 bytes
+// apart, a 16-byte access would put the eight lanes of a cycle on two of eight
+// bank groups (a row's clear and totals were 256 of its 343 LDS cycles); the clear
+// goes lane after lane instead, and in the totals pairs of lanes start at
+// different quarters of their 64 bytes.
+__device__ __forceinline__ void clear_window(uint32_t* hist, uint32_t lane) {
+  u32x4* hv = reinterpret_cast<u32x4*>(hist);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hv[i * kWave + lane] = u32x4{0u, 0u, 0u, 0u};
+}
+// bin(v) for each of the lane's 16 bins 16 lane .. 16 lane + 15, in some order.
+template <class Bin>
+__device__ __forceinline__ void for_window_lane(const uint32_t* hist, uint32_t lane, Bin&& bin) {
+  const u32x4* hv = reinterpret_cast<const u32x4*>(hist) + lane * 4;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    const u32x4 q = hv[(i + (lane >> 1)) & 3u];
+    bin(q.x);
+    bin(q.y);
+    bin(q.z);
+    bin(q.w);
+  }
+}
+__device__ __forceinline__ uint32_t window_lane_total(const uint32_t* hist, uint32_t lane) {
+  uint32_t t = 0;
+  for_window_lane(hist, lane, [&](uint32_t v) { t += v; });
+  return t;
+}
+
 // Exclusive prefix sums, in place, over hist[0, 256 nblk), bins in order. Lane
 // l owns bins 256 i + 4 l .. 256 i + 4 l + 3 of block i, so every access is a
 // conflict-free 16-byte one; two blocks share one wave scan, packed as 16-bit
@@ -228,12 +257,7 @@ __device__ __forceinline__ uint32_t window_find(LDS& L, uint32_t N, uint32_t lan
   wave_lds_sync();
   const u32x4* hv = reinterpret_cast<const u32x4*>(L.hist);
   // lane l holds bins 16 l .. 16 l + 15: their total, and the wave scan of the totals
-  uint32_t t = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const u32x4 q = hv[lane * 4 + i];
-    t += q.x + q.y + q.z + q.w;
-  }
+  const uint32_t t = window_lane_total(L.hist, lane);
   const uint32_t incl = wave_incl_scan(t);
   // per target (its rank is wave-uniform): the first lane whose inclusive
   // count exceeds it owns the target's bin; lane j keeps target j's rank and owner
@@ -294,9 +318,7 @@ __device__ __forceinline__ uint32_t wave_select_fn(SelLds& L, KeyFn&& keyf, uint
   // window level: bin min(key, kSelWin - 1); empty slots count in a spare word
   // of their own lane past the window (kSelWin + lane, never read), so that
   // they do not pile onto one address
-  u32x4* hv = reinterpret_cast<u32x4*>(L.hist);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) hv[lane * 4 + i] = u32x4{0u, 0u, 0u, 0u};
+  clear_window(L.hist, lane);
   wave_lds_sync();
 #pragma unroll
   for (int e = 0; e < V; ++e) {
@@ -448,9 +470,7 @@ template <int NB>
 __device__ __forceinline__ RowScan row_scan(RowLds& L, const Batch (&B)[NB], const RowGeo& g, uint32_t N,
                                             uint64_t& s1, uint64_t& s2, uint32_t& s2h, uint32_t lane) {
   // clear the window now: the LDS writes overlap the minimum / maximum pass
-  u32x4* hv = reinterpret_cast<u32x4*>(L.hist);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) hv[lane * 4 + i] = u32x4{0u, 0u, 0u, 0u};
+  clear_window(L.hist, lane);
   uint32_t mn = 0xffffffffu, mx = 0u;
   for_row(
       B, g,
@@ -536,9 +556,7 @@ template <int NB>
 __device__ __forceinline__ bool row_scan_based(RowLds& L, const Batch (&B)[NB], const RowGeo& g, uint32_t N,
                                                uint32_t p, uint64_t& s1, uint64_t& s2, uint32_t& s2h, RowScan& rs,
                                                uint32_t lane) {
-  u32x4* hv = reinterpret_cast<u32x4*>(L.hist);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) hv[lane * 4 + i] = u32x4{0u, 0u, 0u, 0u};
+  clear_window(L.hist, lane);
   wave_lds_sync();
   uint32_t* hist = L.hist;
   uint32_t mn = 0xffffffffu, mx = 0u, t1 = 0, t2b = 0;
@@ -759,9 +777,7 @@ __device__ __forceinline__ void row_exact(RowLds& L, const uint32_t* __restrict_
   const uint32_t rmin = o.rmin;
   const uint32_t range = o.rmax - rmin;
   const uint32_t b = range ? 32u - __clz(range) : 0u;
-  u32x4* hv = reinterpret_cast<u32x4*>(L.hist);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) hv[lane * 4 + i] = u32x4{0u, 0u, 0u, 0u};
+  clear_window(L.hist, lane);
   wave_lds_sync();
   uint32_t unused = 0xffffffffu;
   uint64_t s1 = 0, s2 = 0;
@@ -832,9 +848,7 @@ __device__ __forceinline__ void select_rows_long(RowLds& L, const uint32_t* __re
   auto process = [&](const Batch& B, const Cursor& c) {
     if (c.u == 0) {
       // a new row: clear the window and take the provisional base from this batch
-      u32x4* hv = reinterpret_cast<u32x4*>(hist);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hv[lane * 4 + i] = u32x4{0u, 0u, 0u, 0u};
+      clear_window(hist, lane);
       mn = 0xffffffffu;
       mx = 0u;
       for_batch(B, c.g, 0u, [&](uint32_t x) {
@@ -936,7 +950,6 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
                                                  uint32_t lane, Emit&& emit) {
   RowLds& L = sel[w];
   uint32_t* hist = L.hist;
-  u32x4* hv = reinterpret_cast<u32x4*>(hist);
   auto share = [&](uint64_t s1, uint64_t s2, uint32_t s2h) {  // this wave's totals -> LDS
     if (lane == 0) {
       co.s1[w] = s1;
@@ -958,8 +971,7 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
   for (uint32_t i = begin; i < end; ++i) {
     const RowGeo g = row_geo(samples, off0 + (uint64_t)i * N, N);
     __syncthreads();  // the previous row's windows and totals have been read
-#pragma unroll
-    for (int q = 0; q < 4; ++q) hv[lane * 4 + q] = u32x4{0u, 0u, 0u, 0u};
+    clear_window(hist, lane);
     Batch A, B;
     load_batch(A, samples, g, 0u, lane);
     if (w && w < g.nb) load_batch(B, samples, g, w, lane);
@@ -1025,8 +1037,7 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
       o.s2h = (uint32_t)(q2 >> 64);
     } else {  // the row again: 96-bit moments, keys from its own minimum
       __syncthreads();  // wave 0's window and the totals have been read
-#pragma unroll
-      for (int q = 0; q < 4; ++q) hv[lane * 4 + q] = u32x4{0u, 0u, 0u, 0u};
+      clear_window(hist, lane);
       wave_lds_sync();
       const bool window = b >= 1 && b < 32;
       uint32_t unused = 0xffffffffu, s2h = 0;
@@ -1065,12 +1076,14 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
 // row (g = lane / 16), loaded like the scan's grouped rows (load_group: up to
 // four quads and one head or tail sample per lane). Their minimum, maximum and
 // moments take four in-row DPP steps, and the four rows share one window: row
-// g counts its keys in byte g of each bin (a row has at most 255 keys, so no
-// byte carries into the next), so one lane-total pass, one wave scan and one
-// pass over the owners' bins serve all four. Row g's targets sit on lanes
+// g counts its keys in byte g of each bin (a row has at most 256 keys, and all
+// of them in one bin only if they are equal: such a row is not counted, so no
+// byte carries into the next), so one lane-total pass, two wave scans (rows 0
+// and 2, 1 and 3, in 16-bit halves) and one pass over the owners' bins serve all
+// four. Row g's targets sit on lanes
 // g C .. g C + C - 1 (C = RANKS::kCount); a row whose range needs all 32 bits,
 // or a row with a target past the window, takes stream_select on its own.
-constexpr uint32_t kGroupMaxN = 255;
+constexpr uint32_t kGroupMaxN = 256;
 constexpr int kGroupGL = 16;
 constexpr uint32_t kGroupRows = kWave / kGroupGL;
 
@@ -1115,8 +1128,7 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
   load_group<GL>(cur, samples, off0 + (uint64_t)(begin + g) * N, N, begin + g < end, gl, nqu);
   for (uint32_t i = begin; i < end; i += kGroupRows) {
     const uint32_t nrows = min(kGroupRows, end - i);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) hv[lane * 4 + q] = u32x4{0u, 0u, 0u, 0u};
+    clear_window(hist, lane);
     uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -1135,6 +1147,7 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
     const uint32_t b = range ? 32u - __clz(range) : 0u;
     const uint32_t inc = 1u << (8u * g);
     const bool wide = ballot(has && b > kFastBits) != 0;
+    const bool flat = b == 0;  // equal keys: rmin is every order statistic
     uint64_t s1 = 0, s2 = 0;
     uint32_t s2h = 0;
     wave_lds_sync();  // the window is clear before any count
@@ -1147,7 +1160,7 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
         const uint32_t z = x - rmin;
         t1 += z;
         t2 = __umul24(z, z) + t2;
-        atomicAdd(&hist[min(z, kSelWin - 1u)], inc);
+        if (!flat) atomicAdd(&hist[min(z, kSelWin - 1u)], inc);
       };
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -1171,7 +1184,7 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
         if ((cur.m >> u) & 1u) acc_quad(cur.q[u], unused, s1, s2, s2h);
       if (cur.m & 16u) acc_sample(cur.x, unused, s1, s2, s2h);
       group_total_64_96<GL>(s1, s2, s2h);
-      if (b < 32) {
+      if (b < 32 && !flat) {
         auto one = [&](uint32_t x) { atomicAdd(&hist[min(x - rmin, kSelWin - 1u)], inc); };
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -1189,26 +1202,26 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
     if (nx < end) load_group<GL>(cur, samples, off0 + (uint64_t)(nx + g) * N, N, nx + g < end, gl, nqu);
     // the window of the four rows: lane totals, wave scan, each target's owner lane
     wave_lds_sync();
-    uint32_t t = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32x4 v = hv[lane * 4 + q];
-      t += v.x + v.y + v.z + v.w;
-    }
-    const uint32_t incl = wave_incl_scan(t);
+    uint32_t te = 0, to = 0;  // of rows 0 | 2 << 16 and 1 | 3 << 16
+    for_window_lane(hist, lane, [&](uint32_t v) {
+      te += v & 0x00ff00ffu;
+      to += (v >> 8) & 0x00ff00ffu;
+    });
+    const uint32_t ie = wave_incl_scan(te), io = wave_incl_scan(to);
     uint32_t owner = 0;
 #pragma unroll
     for (uint32_t rg = 0; rg < kGroupRows; ++rg) {
-      const uint32_t f = (incl >> (8u * rg)) & 0xffu;
+      const uint32_t f = ((rg & 1u) ? io : ie) >> (8u * (rg & 2u)) & 0xffffu;
 #pragma unroll
       for (uint32_t j = 0; j < C; ++j) {
-        const uint64_t m = ballot(f > RANKS::rank(j, N));  // empty for a row without a window
+        const uint64_t m = ballot(f > RANKS::rank(j, N));  // empty for a row that is not counted
         const uint32_t o = m ? (uint32_t)__builtin_ctzll(m) : 0u;
         if (lane == rg * C + j) owner = o;
       }
     }
     const uint32_t sh = 8u * tg;
-    const uint32_t below = ((uint32_t)__shfl((int)(incl - t), (int)owner) >> sh) & 0xffu;
+    const uint32_t be = (uint32_t)__shfl((int)(ie - te), (int)owner), bo = (uint32_t)__shfl((int)(io - to), (int)owner);
+    const uint32_t below = ((tg & 1u) ? bo : be) >> (8u * (tg & 2u)) & 0xffffu;
     uint32_t key = 0, r = 0;
     bool last = false;
     if (tl) {
@@ -1245,12 +1258,12 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
       o.s2h = (uint32_t)__builtin_amdgcn_readlane((int)s2h, src);
       const uint32_t bb = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
       const bool mine = tl && tg == rg;
-      o.sel = key + o.rmin;
+      o.sel = bb ? key + o.rmin : o.rmin;
       if (bb >= 32) {
         const RowGeo gr = row_geo(samples, off0 + (uint64_t)(i + rg) * N, N);
         const uint32_t kk = stream_select(L, samples, gr, o.rmin, 0u, 32u, R, mine, lane);
         if (mine) o.sel = kk + o.rmin;
-      } else if (ballot(mine && last) != 0) {
+      } else if (bb && ballot(mine && last) != 0) {
         const RowGeo gr = row_geo(samples, off0 + (uint64_t)(i + rg) * N, N);
         const uint32_t offk = kSelWin - 1u;
         const uint32_t top = o.rmax - o.rmin - offk;
@@ -1277,11 +1290,10 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 // waves on a series; 1% faster than 256 threads on 8192 x 1024 x 2048).
 constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 8u | 16u, kRowsFour = 4u, kRowsAll = 31u;
 __host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return (mask & 2u) ? 512 : 256; }
-// Waves per SIMD the row-pass kernels are compiled for (1 = the compiler's
-// choice): 6 (80 registers) for rows of one batch, the largest target met
+// Waves per SIMD the row-pass kernels are compiled for: 6 (80 registers) for rows of one batch, the largest target met
 // without spills, runs rows of up to 1027 samples 6 - 9% faster than the 5 the
 // compiler picks by itself.
-__host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 6 : mask == kRowsFour ? 3 : 1; }
+__host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : mask == kRowsMid ? 4 : 3; }
 __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
   return N <= kGroupMaxN ? kGrouped
          : (N / 4 + 4u * kWave - 1) / (4u * kWave) <= 1
@@ -1342,24 +1354,36 @@ __device__ __forceinline__ void select_rows(RowLds* sel, CoopLds<W>& co, const u
   } else if constexpr (NB == (int)kGrouped) {
     select_rows_grouped<RANKS>(L, samples, off0, N, sp.begin, sp.end, lane, emit);
   } else {
-    Batch cur[NB];
-    RowGeo g;
-    if (sp.begin < sp.end) g = load_row<NB>(cur, samples, off0 + (uint64_t)sp.begin * N, N, lane);
+    // Rows of one load batch: the next row is in flight while all of this one is
+    // worked on (a second batch of registers, one wave per SIMD fewer). Loaded
+    // only once this row's samples were counted, half of the time no load was
+    // outstanding, and 4.6 TB/s was what that many bytes in flight give.
+    constexpr bool kAhead = NB == 1;
+    Batch cur[NB], nxt[kAhead ? NB : 1];
+    RowGeo g, gn;
+    auto load = [&](Batch(&B)[NB], uint32_t i) { return load_row<NB>(B, samples, off0 + (uint64_t)i * N, N, lane); };
+    if (sp.begin < sp.end) g = load(cur, sp.begin);
     uint32_t p = 0;  // window base from the previous row (none for the first)
     for (uint32_t i = sp.begin; i < sp.end; ++i) {
       RowOut o;
       RowScan rs;
+      if constexpr (kAhead)
+        if (i + 1 < sp.end) gn = load(nxt, i + 1);
       const bool based = i > sp.begin && row_scan_based<NB>(L, cur, g, N, p, o.s1, o.s2, o.s2h, rs, lane);
       if (!based) rs = row_scan<NB>(L, cur, g, N, o.s1, o.s2, o.s2h, lane);
-      // the next row's loads are in flight while this row's order statistics are found
       const RowGeo gi = g;
-      if (i + 1 < sp.end) g = load_row<NB>(cur, samples, off0 + (uint64_t)(i + 1) * N, N, lane);
+      if constexpr (!kAhead)  // the next row's loads are in flight while this row's order statistics are found
+        if (i + 1 < sp.end) g = load(cur, i + 1);
       o.rmin = rs.rmin;
       o.rmax = rs.rmax;
       o.sel = based ? select_from_window<RANKS>(L, samples, gi, p, rs.rmax, N, lane)
                     : row_select<NB, RANKS>(L, samples, gi, rs, N, lane);
       p = rs.rmin > kRowMargin ? rs.rmin - kRowMargin : 0u;
       emit(i, o, 0u);
+      if constexpr (kAhead) {
+        cur[0] = nxt[0];
+        g = gn;
+      }
     }
   }
 }

@@ -21,7 +21,6 @@ namespace {
 
 typedef unsigned __int128 u128;
 
-constexpr int kCheckV = 32;  // steps per lane: K <= 64 * 32 = KS_MAX_K
 constexpr uint32_t kLineMaxJ = 64, kLineMaxA = 256;
 
 // Lower median x_(floor((n - 1) / 2)).
@@ -31,12 +30,12 @@ struct MedianRank {
 };
 
 // Lower median of the values v[e] (step lane + 64 e) whose bit e of `in` is
-// set, n >= 1 of them over the wave; wave-uniform.
-__device__ uint32_t lower_median(ks::SelLds& L, const uint32_t (&v)[kCheckV], uint32_t in, uint32_t n,
-                                 uint32_t lane) {
+// set, n >= 1 of them over the wave; wave-uniform. V: steps per lane (K <= 64 V).
+template <int V>
+__device__ uint32_t lower_median(ks::SelLds& L, const uint32_t (&v)[V], uint32_t in, uint32_t n, uint32_t lane) {
   uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e)
+  for (int e = 0; e < V; ++e)
     if ((in >> e) & 1u) {
       mn = min(mn, v[e]);
       mx = max(mx, v[e]);
@@ -45,43 +44,48 @@ __device__ uint32_t lower_median(ks::SelLds& L, const uint32_t (&v)[kCheckV], ui
   mx = ks::wave_max_u32(mx);
   if (mx == mn) return mn;
   const uint32_t b = 32u - __clz(mx - mn);
-  uint32_t k[kCheckV];
+  uint32_t k[V];
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e) k[e] = ((in >> e) & 1u) ? v[e] - mn : 0xffffffffu;
-  const uint32_t key = ks::wave_select<kCheckV, MedianRank>(L, k, b, n, lane);
+  for (int e = 0; e < V; ++e) k[e] = ((in >> e) & 1u) ? v[e] - mn : 0xffffffffu;
+  const uint32_t key = ks::wave_select<V, MedianRank>(L, k, b, n, lane);
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)key) + mn;  // lane 0 holds the median's key
 }
 
 // Level (median), spread (MAD) and disturbed-step count of the steps [a, b).
-__device__ void side_check(ks::SelLds& L, const uint32_t (&v)[kCheckV], uint32_t a, uint32_t b, uint32_t k,
+template <int V>
+__device__ void side_check(ks::SelLds& L, const uint32_t (&v)[V], uint32_t a, uint32_t b, uint32_t k,
                            uint32_t lane, uint32_t& med, uint32_t& mad, uint32_t& disturbed) {
   uint32_t in = 0;
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e) {
+  for (int e = 0; e < V; ++e) {
     const uint32_t i = lane + ks::kWave * (uint32_t)e;
     in |= (i >= a && i < b) ? 1u << e : 0u;
   }
   const uint32_t n = b - a;
-  med = lower_median(L, v, in, n, lane);
-  uint32_t dev[kCheckV];
+  med = lower_median<V>(L, v, in, n, lane);
+  uint32_t dev[V];
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e) dev[e] = v[e] > med ? v[e] - med : med - v[e];
-  mad = lower_median(L, dev, in, n, lane);
+  for (int e = 0; e < V; ++e) dev[e] = v[e] > med ? v[e] - med : med - v[e];
+  mad = lower_median<V>(L, dev, in, n, lane);
   const uint64_t thr = (uint64_t)k * max(mad, max(1u, med / 64u));
   uint32_t cnt = 0;
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e) cnt += (uint32_t)__popcll(ks::ballot(((in >> e) & 1u) && dev[e] > thr));
+  for (int e = 0; e < V; ++e) cnt += (uint32_t)__popcll(ks::ballot(((in >> e) & 1u) && dev[e] > thr));
   disturbed = cnt;
 }
 
-// One wave per sweep, four per workgroup.
-__global__ __launch_bounds__(256) void check_kernel(const ks_desc* __restrict__ desc, uint32_t num_series,
+// One wave per sweep, a workgroup each, with as many steps per lane as max_K
+// asks for (with 32 for every K and four sweeps to a workgroup, eight sweeps of
+// 256 steps took 17 us, on scratch memory).
+template <int V>
+__global__ __launch_bounds__(64) void check_kernel(const ks_desc* __restrict__ desc, uint32_t num_series,
                                                     uint32_t max_K, const ks_result* __restrict__ res,
                                                     const ks_row_stats* __restrict__ stats, uint64_t stats_rows,
                                                     uint32_t edge, uint32_t k, ks_check* __restrict__ out) {
-  __shared__ ks::SelLds sel[4];
-  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
-  const uint32_t s = blockIdx.x * 4u + w;
+  static_assert(V * ks::kWave <= (int)KS_MAX_K, "steps of a sweep");
+  __shared__ ks::SelLds L;
+  const uint32_t lane = ks::lane_id();
+  const uint32_t s = blockIdx.x;
   if (s >= num_series) return;
   const ks_desc d = desc[s];
   const ks_result r = res[s];
@@ -93,20 +97,19 @@ __global__ __launch_bounds__(256) void check_kernel(const ks_desc* __restrict__ 
     if (lane == 0) out[s] = ks_check{KS_CHECK_INVALID, 0u, 0, 0, 0u, 0u, 0u, 0u};
     return;
   }
-  uint32_t v[kCheckV];
+  uint32_t v[V];
 #pragma unroll
-  for (int e = 0; e < kCheckV; ++e) {
+  for (int e = 0; e < V; ++e) {
     const uint32_t i = lane + ks::kWave * (uint32_t)e;
     v[e] = i < K ? stats[d.aux_offset + i].p50 : 0u;
   }
-  ks::SelLds& L = sel[w];
   const bool sig = (r.flags & KS_SIGNIFICANT) != 0;
   uint32_t med_lo, mad_lo, n_lo, med_hi, mad_hi, n_hi;
   if (sig) {
-    side_check(L, v, 0, r.cp, k, lane, med_lo, mad_lo, n_lo);
-    side_check(L, v, r.cp, K, k, lane, med_hi, mad_hi, n_hi);
+    side_check<V>(L, v, 0, r.cp, k, lane, med_lo, mad_lo, n_lo);
+    side_check<V>(L, v, r.cp, K, k, lane, med_hi, mad_hi, n_hi);
   } else {
-    side_check(L, v, 0, K, k, lane, med_lo, mad_lo, n_lo);
+    side_check<V>(L, v, 0, K, k, lane, med_lo, mad_lo, n_lo);
     med_hi = med_lo;
     mad_hi = mad_lo;
     n_hi = 0;
@@ -167,22 +170,24 @@ __global__ __launch_bounds__(256) void align_kernel(const uint64_t* __restrict__
   distance[i] = (double)bnum / (double)T;   // bnum < 2^52: exact
 }
 
-// One wave per experiment, four per workgroup: lanes over the array sizes
-// (a = lane + 64 t), strides in turn; the scores meet in LDS for lane 0.
+// One workgroup per experiment: lanes over the array sizes (a = lane + 64 t),
+// each wave every fourth stride (a wave taking 16 strides in turn, a 64-bit
+// division each, took 16 us on 256 experiments); the scores meet in LDS for
+// one thread.
 __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ desc, uint32_t num_exp,
                                                    const ks_row_stats* __restrict__ stats, uint64_t stats_rows,
                                                    uint32_t J, const uint32_t* __restrict__ strides,
                                                    ks_line* __restrict__ out) {
-  __shared__ uint64_t score[4][kLineMaxJ];
+  __shared__ uint64_t score[kLineMaxJ];
   const uint32_t lane = ks::lane_id(), w = ks::wave_id();
-  const uint32_t e = blockIdx.x * 4u + w;
+  const uint32_t e = blockIdx.x;
   if (e >= num_exp) return;
   const ks_desc d = desc[e];
   const uint32_t K = d.K, A = K / J;
   const bool bad = A < 1 || A > kLineMaxA || A * J != K || d.aux_offset > stats_rows ||
                    (uint64_t)K > stats_rows - d.aux_offset;
   if (bad) {
-    if (lane == 0) out[e] = ks_line{0u, 0u, KS_LINE_INVALID, 0u, 0.0};
+    if (threadIdx.x == 0) out[e] = ks_line{0u, 0u, KS_LINE_INVALID, 0u, 0.0};
     return;
   }
   const ks_row_stats* x = stats + d.aux_offset;
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
     P[t] = a < A ? x[a].p50 : 0u;
     M[t] = a < A ? x[(uint64_t)(J - 1) * A + a].p50 : 0u;
   }
-  for (uint32_t j = 0; j < J; ++j) {
+  for (uint32_t j = w; j < J; j += 4) {
     uint64_t acc = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -209,14 +214,15 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
     }
     uint32_t unused = 0;
     ks::wave_total_32_64(unused, acc);
-    if (lane == 0) score[w][j] = acc;
+    if (lane == 0) score[j] = acc;
   }
-  if (lane != 0) return;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   const uint64_t W = (uint64_t)A * (A + 1) / 2;
   const uint64_t half = W << 31;
   uint32_t jstar = J;
   for (uint32_t j = 1; j < J; ++j)
-    if (score[w][j] > half) {
+    if (score[j] > half) {
       jstar = j;
       break;
     }
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
   int64_t best = 0;
   uint32_t best_line = 0, ncand = 0, prev_stride = 0;
   for (uint32_t j = 0; j < J; ++j) {
-    uint64_t sc = score[w][j];
+    uint64_t sc = score[j];
     if (j >= jstar) {
       run = max(run, sc);
       sc = run;
@@ -266,8 +272,14 @@ extern "C" int ks_check_batch(ks_ctx* ctx, const ks_desc* desc, uint32_t num_ser
   if (!desc || !res || !stats || !out) return KS_E_INVALID;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  hipLaunchKernelGGL(check_kernel, dim3((num_series + 3) / 4), dim3(256), 0, (hipStream_t)stream, desc, num_series,
-                     max_K, res, stats, stats_rows, edge, k, out);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(num_series), dim3(64), 0, (hipStream_t)stream, desc, num_series, max_K, res, stats,
+                       stats_rows, edge, k, out);
+  };
+  if (max_K <= 256) run(check_kernel<4>);
+  else if (max_K <= 512) run(check_kernel<8>);
+  else if (max_K <= 1024) run(check_kernel<16>);
+  else run(check_kernel<32>);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "check launch");
 }
@@ -290,7 +302,7 @@ extern "C" int ks_line_batch(ks_ctx* ctx, const ks_desc* desc, uint32_t num_exp,
   if (!desc || !stats || !strides || !out) return KS_E_INVALID;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  hipLaunchKernelGGL(line_kernel, dim3((num_exp + 3) / 4), dim3(256), 0, (hipStream_t)stream, desc, num_exp, stats,
+  hipLaunchKernelGGL(line_kernel, dim3(num_exp), dim3(256), 0, (hipStream_t)stream, desc, num_exp, stats,
                      stats_rows, J, strides, out);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "line launch");

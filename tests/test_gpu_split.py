@@ -28,6 +28,8 @@ def _rows(rng, K, N, wide):
     """Latency rows with a level change; `wide` spreads a row over more than the window and the fast moments' range."""
     r = rng.integers(200, 700, (K, N)).astype(np.uint32)
     r[K // 2:] += 150
+    if K > 2:
+        r[1] = 77  # equal samples
     if wide:
         r[0, -1] = 9500
         r[-1, 0] = 1 << 31
