@@ -77,7 +77,7 @@ struct LearnBuffers {
   uint64_t* s2lo = nullptr;
   uint32_t* s2hi = nullptr;
   uint32_t* smin = nullptr;
-  uint32_t* cmin = nullptr;   // minima of the feature pass's row chunks (series * chunks < series + kRowPassWGs)
+  uint32_t* cmin = nullptr;   // minima of the feature pass's row chunks (series * chunks <= series + kChunkWGs)
   uint32_t* K = nullptr;
   float* feat = nullptr;      // [rows][9]
   uint16_t* x0 = nullptr;     // [rows][16] bf16

@@ -20,7 +20,7 @@ struct LearnWs {
   uint64_t* s2lo;
   uint32_t* s2hi;
   uint32_t* smin;   // [num_series]: written by the pack step
-  uint32_t* cmin;   // [num_series * C]: minima of the feature pass's row chunks
+  uint32_t* cmin;   // [num_series * Cs]: minima of the feature pass's row chunks
   uint32_t* K;      // [num_series]: K when the series was valid, 0 otherwise
 };
 
@@ -49,11 +49,12 @@ struct FeatStage {
 template <int NB, int W>
 __device__ __forceinline__ uint32_t feature_rows(RowLds* sel, CoopLds<W>& co, void* stage,
                                                  const uint32_t* __restrict__ samples, const ks_desc& d, uint32_t c,
-                                                 uint32_t C, uint32_t w, uint32_t lane, uint64_t slot, LearnWs lw,
+                                                 uint32_t C, uint32_t num_series, uint32_t w, uint32_t lane, uint64_t slot,
+                                                 LearnWs lw,
                                                  float* __restrict__ feat_ws) {
   constexpr uint32_t kFeatStage = feat_stage_rows(NB);
   static_assert(kFeatStage <= (uint32_t)kWave, "a flush writes one row's moments per lane");
-  const RowSpan sp = row_span<NB, W>(d.K, c, C, w);
+  const RowSpan sp = row_span<NB, W>(d.K, c, C, num_series, w);
   FeatStage<kFeatStage>& st = reinterpret_cast<FeatStage<kFeatStage>*>(stage)[w];
   uint32_t gmin = 0xffffffffu;
   // row i's results; its deciles on lanes first .. first + 8
@@ -85,14 +86,14 @@ __device__ __forceinline__ uint32_t feature_rows(RowLds* sel, CoopLds<W>& co, vo
 }
 
 // First step: one launch over the row classes of MASK, one workgroup per
-// (series, chunk of its rows; row_pass_chunks), the series in the plan's order
-// (descriptor order without one). Malformed series (class 1's) are marked with
+// (series, chunk of its rows; row_pass_chunks, at most Cs), the series in the
+// plan's order (descriptor order without one). Malformed series (class 1's) are marked with
 // K = 0. Each chunk leaves its minimum in cmin; chunk 0 writes the series' K.
 template <uint32_t MASK>
 __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves_per_eu(row_pass_waves(MASK)))) void features_kernel(
     const uint32_t* __restrict__ samples, uint64_t num_samples, const ks_desc* __restrict__ desc, uint32_t num_series,
     uint32_t max_K, uint32_t SR, LearnWs lw, float* __restrict__ feat_ws, const uint32_t* __restrict__ plan,
-    uint32_t C) {
+    uint32_t C, uint32_t Cs) {
   constexpr int W = row_pass_threads(MASK) / kWave;
   constexpr uint32_t kStageMax = MASK == kRowsOne ? 16u : 64u;
   __shared__ RowLds sel[W];
@@ -116,7 +117,8 @@ __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves
     constexpr int NB = decltype(tag)::value;
     if constexpr ((MASK >> feat_class_index(NB)) & 1u)
       if (nb == (uint32_t)NB)
-        gmin = feature_rows<NB, W>(sel, co, stage, samples, d, c, C, w, lane, (uint64_t)s * SR + 2, lw, feat_ws);
+        gmin = feature_rows<NB, W>(sel, co, stage, samples, d, c, C, num_series, w, lane, (uint64_t)s * SR + 2, lw,
+                                   feat_ws);
   };
   rows(std::integral_constant<int, 1>{});
   rows(std::integral_constant<int, 2>{});
@@ -128,8 +130,11 @@ __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves
   if (tid == 0) {
 #pragma unroll
     for (int u = 0; u < W; ++u) gmin = min(gmin, red[u]);
-    lw.cmin[(uint64_t)s * C + c] = gmin;  // 0xffffffff for a chunk past the series' rows
-    if (c == 0) lw.K[s] = d.K;
+    lw.cmin[(uint64_t)s * Cs + c] = gmin;  // 0xffffffff for a chunk past the series' rows
+    if (c == 0) {
+      for (uint32_t q = C; q < Cs; ++q) lw.cmin[(uint64_t)s * Cs + q] = 0xffffffffu;
+      lw.K[s] = d.K;
+    }
   }
 }
 
@@ -147,7 +152,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restrict__ desc, uint32_t num_series,
                                                           float* __restrict__ feat_out, uint64_t feat_rows,
                                                           uint16_t* __restrict__ x0, uint32_t SR, LearnWs lw,
-                                                          float* __restrict__ feat_ws, uint32_t C) {
+                                                          float* __restrict__ feat_ws, uint32_t Cs) {
   static_assert(kRowPassChunks <= (uint32_t)NT, "one thread per chunk minimum");
   __shared__ __align__(16) uint16_t bf[NT * 16];
   __shared__ uint32_t red[NT / kWave];
@@ -164,7 +169,7 @@ __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restr
   const uint32_t lo = r0 < 2u ? 2u - r0 : 0u;
   const uint32_t hi = K + 2u > r0 ? (K + 2u - r0 < nr ? K + 2u - r0 : nr) : 0u;
   if (lo < hi) {
-    const uint32_t gmin = block_min_u32<NT>(tid < C ? lw.cmin[(uint64_t)s * C + tid] : 0xffffffffu, red);
+    const uint32_t gmin = block_min_u32<NT>(tid < Cs ? lw.cmin[(uint64_t)s * Cs + tid] : 0xffffffffu, red);
     if (blockIdx.y == 0 && tid == 0) lw.smin[s] = gmin;
     const double denom = (double)(gmin > 1 ? gmin : 1u);
     const ks_desc d = desc[s];

@@ -2,6 +2,7 @@
 // pass, network forward, proposal, exact refine and one training step.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -50,7 +51,7 @@ int ensure_learn(ks_ctx* c, uint64_t rows, uint64_t series, bool train) {
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_learn(b);
-  bool ok = alloc(b.s1, R) && alloc(b.s2lo, R) && alloc(b.s2hi, R) && alloc(b.smin, S) && alloc(b.cmin, S + ks::kRowPassWGs) &&
+  bool ok = alloc(b.s1, R) && alloc(b.s2lo, R) && alloc(b.s2hi, R) && alloc(b.smin, S) && alloc(b.cmin, S + ks::kChunkWGs) &&
             alloc(b.K, S) &&
             alloc(b.feat, R * 9) && alloc(b.x0, R * 16) && alloc(b.act[0], R * 64) && alloc(b.act[1], R * 64) &&
             alloc(b.act[2], R * 64) && alloc(b.logits, R);
@@ -390,12 +391,16 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
   if (int rc = ensure_learn(ctx, (uint64_t)num_series * SR, num_series, false)) return rc;
   hipStream_t st = (hipStream_t)stream;
   LearnBuffers& b = ctx->learn;
-  const uint32_t C = ks::row_pass_chunks(num_series, max_K);
+  const bool one = num_series <= ks::kRowPassOneLaunch;
+  uint32_t Cs = 1;  // most chunks that a launch below makes of a series
+  for (uint32_t mask : {ks::kRowsOne, ks::kRowsMid, ks::kRowsFour, ks::kRowsAll})
+    if ((mask == ks::kRowsAll) == one) Cs = std::max(Cs, ks::row_pass_chunks(num_series, max_K, mask));
   auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
+    const uint32_t C = ks::row_pass_chunks(num_series, max_K, mask);
     hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
-                       num_series, max_K, SR, learn_ws(ctx), b.feat, plan, C);
+                       num_series, max_K, SR, learn_ws(ctx), b.feat, plan, C, Cs);
   };
-  if (num_series <= ks::kRowPassOneLaunch) {
+  if (one) {
     launch(ks::features_kernel<ks::kRowsAll>, ks::kRowsAll, nullptr);
   } else {
     // the series order per row class, kept in the logits buffer (num_series +
@@ -409,7 +414,7 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
     launch(ks::features_kernel<ks::kRowsFour>, ks::kRowsFour, plan);
   }
   hipLaunchKernelGGL((ks::feature_pack_kernel<kNT>), dim3(num_series, (SR + kNT - 1) / kNT), dim3(kNT), 0, st, desc,
-                     num_series, features, feature_rows, b.x0, SR, learn_ws(ctx), b.feat, C);
+                     num_series, features, feature_rows, b.x0, SR, learn_ws(ctx), b.feat, Cs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "features launch");
   b.stamp_desc = desc;

@@ -1076,11 +1076,11 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
 // row (g = lane / 16), loaded like the scan's grouped rows (load_group: up to
 // four quads and one head or tail sample per lane). Their minimum, maximum and
 // moments take four in-row DPP steps, and the four rows share one window: row
-// g counts its keys in byte g of each bin (a row has at most 256 keys, and all
-// of them in one bin only if they are equal: such a row is not counted, so no
-// byte carries into the next), so one lane-total pass, two wave scans (rows 0
-// and 2, 1 and 3, in 16-bit halves) and one pass over the owners' bins serve all
-// four. Row g's targets sit on lanes
+// g counts its keys in byte g of each bin (a row of up to 255 keys does not
+// carry into the next byte), so one lane-total pass, one wave scan and one pass
+// over the owners' bins serve all four. FULL: rows of 256 keys. All of them are
+// in one bin only if they are equal (such a row is not counted), and the totals
+// are summed as 16-bit halves, rows 0 and 2, 1 and 3, in two wave scans. Row g's targets sit on lanes
 // g C .. g C + C - 1 (C = RANKS::kCount); a row whose range needs all 32 bits,
 // or a row with a target past the window, takes stream_select on its own.
 constexpr uint32_t kGroupMaxN = 256;
@@ -1109,7 +1109,7 @@ __device__ __forceinline__ uint32_t group16_sum(uint32_t v) {
 // Rows begin .. end - 1 of one series (rows of N <= kGroupMaxN samples from
 // element off0), four per step; emit(i, o, first) gets row i's results with
 // its targets on lanes first .. first + C - 1 of o.sel.
-template <class RANKS, class Emit>
+template <class RANKS, bool FULL, class Emit>
 __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* __restrict__ samples, uint64_t off0,
                                                     uint32_t N, uint32_t begin, uint32_t end, uint32_t lane,
                                                     Emit&& emit) {
@@ -1147,7 +1147,7 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
     const uint32_t b = range ? 32u - __clz(range) : 0u;
     const uint32_t inc = 1u << (8u * g);
     const bool wide = ballot(has && b > kFastBits) != 0;
-    const bool flat = b == 0;  // equal keys: rmin is every order statistic
+    const bool flat = FULL && b == 0;
     uint64_t s1 = 0, s2 = 0;
     uint32_t s2h = 0;
     wave_lds_sync();  // the window is clear before any count
@@ -1202,26 +1202,35 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
     if (nx < end) load_group<GL>(cur, samples, off0 + (uint64_t)(nx + g) * N, N, nx + g < end, gl, nqu);
     // the window of the four rows: lane totals, wave scan, each target's owner lane
     wave_lds_sync();
-    uint32_t te = 0, to = 0;  // of rows 0 | 2 << 16 and 1 | 3 << 16
-    for_window_lane(hist, lane, [&](uint32_t v) {
-      te += v & 0x00ff00ffu;
-      to += (v >> 8) & 0x00ff00ffu;
-    });
-    const uint32_t ie = wave_incl_scan(te), io = wave_incl_scan(to);
     uint32_t owner = 0;
-#pragma unroll
-    for (uint32_t rg = 0; rg < kGroupRows; ++rg) {
-      const uint32_t f = ((rg & 1u) ? io : ie) >> (8u * (rg & 2u)) & 0xffffu;
+    auto owners = [&](uint32_t rg, uint32_t f) {  // f: keys of row rg up to this lane's bins
 #pragma unroll
       for (uint32_t j = 0; j < C; ++j) {
         const uint64_t m = ballot(f > RANKS::rank(j, N));  // empty for a row that is not counted
         const uint32_t o = m ? (uint32_t)__builtin_ctzll(m) : 0u;
         if (lane == rg * C + j) owner = o;
       }
-    }
+    };
     const uint32_t sh = 8u * tg;
-    const uint32_t be = (uint32_t)__shfl((int)(ie - te), (int)owner), bo = (uint32_t)__shfl((int)(io - to), (int)owner);
-    const uint32_t below = ((tg & 1u) ? bo : be) >> (8u * (tg & 2u)) & 0xffffu;
+    uint32_t below;
+    if constexpr (FULL) {
+      uint32_t te = 0, to = 0;  // of rows 0 | 2 << 16 and 1 | 3 << 16
+      for_window_lane(hist, lane, [&](uint32_t v) {
+        te += v & 0x00ff00ffu;
+        to += (v >> 8) & 0x00ff00ffu;
+      });
+      const uint32_t ie = wave_incl_scan(te), io = wave_incl_scan(to);
+#pragma unroll
+      for (uint32_t rg = 0; rg < kGroupRows; ++rg) owners(rg, ((rg & 1u) ? io : ie) >> (8u * (rg & 2u)) & 0xffffu);
+      const uint32_t be = (uint32_t)__shfl((int)(ie - te), (int)owner), bo = (uint32_t)__shfl((int)(io - to), (int)owner);
+      below = ((tg & 1u) ? bo : be) >> (8u * (tg & 2u)) & 0xffffu;
+    } else {
+      const uint32_t t = window_lane_total(hist, lane);
+      const uint32_t incl = wave_incl_scan(t);
+#pragma unroll
+      for (uint32_t rg = 0; rg < kGroupRows; ++rg) owners(rg, (incl >> (8u * rg)) & 0xffu);
+      below = ((uint32_t)__shfl((int)(incl - t), (int)owner) >> sh) & 0xffu;
+    }
     uint32_t key = 0, r = 0;
     bool last = false;
     if (tl) {
@@ -1258,12 +1267,12 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
       o.s2h = (uint32_t)__builtin_amdgcn_readlane((int)s2h, src);
       const uint32_t bb = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
       const bool mine = tl && tg == rg;
-      o.sel = bb ? key + o.rmin : o.rmin;
+      o.sel = FULL && bb == 0 ? o.rmin : key + o.rmin;
       if (bb >= 32) {
         const RowGeo gr = row_geo(samples, off0 + (uint64_t)(i + rg) * N, N);
         const uint32_t kk = stream_select(L, samples, gr, o.rmin, 0u, 32u, R, mine, lane);
         if (mine) o.sel = kk + o.rmin;
-      } else if (bb && ballot(mine && last) != 0) {
+      } else if (!(FULL && bb == 0) && ballot(mine && last) != 0) {
         const RowGeo gr = row_geo(samples, off0 + (uint64_t)(i + rg) * N, N);
         const uint32_t offk = kSelWin - 1u;
         const uint32_t top = o.rmax - o.rmin - offk;
@@ -1303,21 +1312,33 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
                     : ((N / 4 + 4u * kWave - 1) / (4u * kWave) <= 4 ? 4u : kStreamed));
 }
 
-// Split of the row passes over workgroups. A series' rows are cut into C chunks
-// (row_pass_chunks, the same for the whole launch), one workgroup each, so that
-// a batch of few series still fills the chip: the statistics of 8 series of 64
-// rows of 65537 samples take 41 us (3.3 TB/s) so split, 1440 us with a workgroup
-// per series; of 8 x 256 rows of 1024 samples 15 us against 145, of 256 x 512
-// rows of 256 samples (four waves per CU unsplit) 91 us against 246. A chunk is not made
-// smaller than a row (or a step of four short rows) per wave; rows too long for
-// the registers go a row at a time to all waves of the workgroup
-// (select_rows_coop) where a chunk has fewer than two rows per wave.
-constexpr uint32_t kRowPassWGs = 2048;   // eight workgroups per CU
-constexpr uint32_t kRowPassChunks = 256; // at most, per series
-__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K) {
-  const uint32_t c = num_series >= kRowPassWGs ? 1u : (kRowPassWGs + num_series - 1) / num_series;
-  const uint32_t m = max_K < kRowPassChunks ? max_K : kRowPassChunks;
-  return c < m ? c : m;
+// Split of the row passes over workgroups. A series' rows are cut into C chunks,
+// one workgroup each, so that a batch of few series still fills the chip: the
+// statistics of 8 series of 64 rows of 65537 samples take 41 us (3.3 TB/s) so
+// split, 1440 us with a workgroup per series; of 8 x 256 rows of 1024 samples 12
+// us against 145, of 256 x 512 rows of 256 samples (four waves per CU unsplit) 60
+// us against 246. A launch is cut to about kChunkWGs workgroups in all and no
+// further, since a wave's first row takes two passes and its load is not hidden:
+// four rounds of the resident workgroups for rows of one batch (the feature pass
+// of 1024 x 256 x 1024 takes 229 us in 1.6 rounds, 206 in four), one round for
+// the other classes (512 x 256 rows of 2048 samples: 200 us in one, 227 in four).
+// A chunk is not made smaller than a row (or a step of four short rows) per
+// wave, except in batches of at most kCoopRows rows (two waves per SIMD with a
+// wave a row): rows too long for the registers then go a row at a time to all
+// waves of a workgroup (select_rows_coop); in larger ones that only reads every
+// row's first batch eight times (512 x 64 rows of 8192 samples 330 us, 220 with
+// a wave a row).
+constexpr uint32_t kRowPassChunks = 256;  // chunks of a series at most
+constexpr uint32_t kCoopRows = 2048;
+__host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 5120u : mask == kRowsAll ? 1024u : 512u; }
+constexpr uint32_t kChunkWGs = 5120;  // the largest of them
+__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, uint32_t mask) {
+  const uint32_t least = (uint64_t)num_series * max_K <= kCoopRows ? 1u : (uint32_t)row_pass_threads(mask) / kWave;
+  const uint32_t most = (max_K + least - 1) / least;
+  uint32_t c = chunk_wgs(mask) / num_series;
+  c = c < most ? c : most;
+  c = c < kRowPassChunks ? c : kRowPassChunks;
+  return c ? c : 1u;
 }
 
 // Rows of chunk c of a K-row series of row class NB in a workgroup of W waves,
@@ -1327,11 +1348,12 @@ struct RowSpan {
   bool coop;
 };
 template <int NB, int W>
-__device__ __forceinline__ RowSpan row_span(uint32_t K, uint32_t c, uint32_t C, uint32_t w) {
+__device__ __forceinline__ RowSpan row_span(uint32_t K, uint32_t c, uint32_t C, uint32_t num_series, uint32_t w) {
   uint32_t R = (K + C - 1) / C;
-  if (NB != (int)kStreamed) R = max(R, (uint32_t)W * (NB == (int)kGrouped ? kGroupRows : 1u));
-  const uint32_t r0 = min((uint64_t)c * R, (uint64_t)K), r1 = min(r0 + R, K);
-  if (NB == (int)kStreamed && R < 2u * W) return RowSpan{r0, r1, true};
+  const bool coop = NB == (int)kStreamed && R < (uint32_t)W && (uint64_t)num_series * K <= kCoopRows;
+  if (!coop) R = max(R, (uint32_t)W * (NB == (int)kGrouped ? kGroupRows : 1u));
+  const uint32_t r0 = (uint32_t)min((uint64_t)c * R, (uint64_t)K), r1 = min(r0 + R, K);
+  if (coop) return RowSpan{r0, r1, true};
   const uint32_t B = (r1 - r0 + W - 1) / W;
   const uint32_t begin = min(r0 + w * B, r1);
   return RowSpan{begin, min(begin + B, r1), false};
@@ -1352,7 +1374,10 @@ __device__ __forceinline__ void select_rows(RowLds* sel, CoopLds<W>& co, const u
       select_rows_long<RANKS>(L, samples, off0, N, sp.end, sp.begin, 1u, lane,
                               [&](uint32_t i, const RowOut& o) { emit(i, o, 0u); });
   } else if constexpr (NB == (int)kGrouped) {
-    select_rows_grouped<RANKS>(L, samples, off0, N, sp.begin, sp.end, lane, emit);
+    if (N < kGroupMaxN)
+      select_rows_grouped<RANKS, false>(L, samples, off0, N, sp.begin, sp.end, lane, emit);
+    else
+      select_rows_grouped<RANKS, true>(L, samples, off0, N, sp.begin, sp.end, lane, emit);
   } else {
     // Rows of one load batch: the next row is in flight while all of this one is
     // worked on (a second batch of registers, one wave per SIMD fewer). Loaded

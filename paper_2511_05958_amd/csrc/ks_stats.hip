@@ -59,11 +59,12 @@ constexpr uint32_t stats_stage_rows(int NB) { return NB == 1 || NB == (int)ks::k
 template <int NB, int W>
 __device__ __forceinline__ void stats_rows(ks::RowLds* sel, ks::CoopLds<W>& co, void* stage,
                                            const uint32_t* __restrict__ samples, const ks_desc& d, uint32_t c,
-                                           uint32_t C, uint32_t w, uint32_t lane, ks_row_stats* __restrict__ o) {
+                                           uint32_t C, uint32_t num_series, uint32_t w, uint32_t lane,
+                                           ks_row_stats* __restrict__ o) {
   constexpr uint32_t kStage = stats_stage_rows(NB);
   static_assert(kStage <= (uint32_t)ks::kWave, "a flush makes one record per lane");
   const uint32_t N = d.N;
-  const ks::RowSpan sp = ks::row_span<NB, W>(d.K, c, C, w);
+  const ks::RowSpan sp = ks::row_span<NB, W>(d.K, c, C, num_series, w);
   RowStage<kStage>& st = reinterpret_cast<RowStage<kStage>*>(stage)[w];
   // row i's results; its p50 and p95 on lanes first and first + 1
   ks::select_rows<NB, StatRanks, W>(sel, co, samples, d.offset, N, sp, w, lane,
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(ks::row_pass_threads(MASK)) __attribute__((amdgpu_w
   auto rows = [&](auto tag) {
     constexpr int NB = decltype(tag)::value;
     if constexpr ((MASK >> ks::feat_class_index(NB)) & 1u)
-      if (nb == (uint32_t)NB) stats_rows<NB, W>(sel, co, stage, samples, d, c, C, w, lane, o);
+      if (nb == (uint32_t)NB) stats_rows<NB, W>(sel, co, stage, samples, d, c, C, num_series, w, lane, o);
   };
   rows(std::integral_constant<int, 1>{});
   rows(std::integral_constant<int, 2>{});
@@ -154,8 +155,8 @@ extern "C" int ks_stats_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t st = (hipStream_t)stream;
-  const uint32_t C = ks::row_pass_chunks(num_series, max_K);
   auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
+    const uint32_t C = ks::row_pass_chunks(num_series, max_K, mask);
     hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
                        num_series, max_K, out, out_rows, plan, C);
   };
