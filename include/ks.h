@@ -200,7 +200,9 @@ typedef struct ks_launch {
 
 /* Record (ks_launch_set) or read (ks_launch_get) the plan ks_scan_batch uses
  * for batches with this max_K class and num_series; without a record the
- * default is {KS_LAUNCH_ORDERED, 1 MiB, 1, 0}. KS_E_INVALID / KS_E_RANGE on
+ * default is {KS_LAUNCH_ORDERED, 1 MiB, 1, 0}, of which the library replaces the
+ * kernel variant and the graph by what is fastest for the batch's sizes.
+ * KS_E_INVALID / KS_E_RANGE on
  * bad values. */
 int ks_launch_set(ks_ctx *ctx, uint32_t max_K, uint32_t num_series, const ks_launch *cfg);
 int ks_launch_get(ks_ctx *ctx, uint32_t max_K, uint32_t num_series, ks_launch *cfg);
@@ -227,7 +229,7 @@ int ks_autotune(ks_ctx *ctx, const uint32_t *samples, uint64_t num_samples, cons
  * plan's two kernels directly (no hipGraph).
  *   Arguments, results and per-series flags as ks_scan_batch; params->opts
  *   is checked but the launch plan is always the ordered grid (with the
- *   scan-kernel variant recorded for this batch shape, else variant 0).
+ *   scan-kernel variant recorded for this batch shape, else one by its sizes).
  *   num_series <= KS_NOALLOC_MAX_SERIES, else KS_E_RANGE (nothing launched).
  *   Scratch: 256 + 24 * KS_NOALLOC_MAX_SERIES bytes (12 MiB + 256 B) per
  *   device, held until the process ends; ks_ctx_create resolves its address

@@ -301,6 +301,23 @@ LaunchCfg config_for(const ks_ctx* c, int kc, uint32_t num_series, uint32_t opts
   return cfg;
 }
 
+// What a batch without a recorded plan runs under the ordered plan: the kernel
+// variant by size, and a direct launch (a graph's update costs more on the host
+// than the second kernel's launch: 1024 series of 64 x 64 34 us a call from a
+// graph, 25 direct). Variant 2, eight waves per series instead of four, for K
+// classes of 1024 and 2048 rows, whose LDS allows as many workgroups either way
+// (1024 series of 2048 x 64 1698 us with four, 1050 with eight; 4096 of 1024 x
+// 256 1731 and 1575), and for 512-row classes with series of more than 640 KB on
+// average, where the largest ones' stream decides (8192 uneven ones up to 512 x
+// 4096 1056 and 997; below, its barriers cost: 8192 of 512 x 256 1022 and 1130).
+// Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671.
+LaunchCfg default_cfg(int kc, uint64_t num_samples, uint32_t num_series) {
+  LaunchCfg cfg;
+  cfg.graph = 0;
+  if (kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && num_samples / num_series > (160u << 10))) cfg.variant = 2;
+  return cfg;
+}
+
 int scan_with(ks_ctx* ctx, const ScanArgs& a, int kc, const LaunchCfg& cfg, hipStream_t st) {
   if (cfg.mode == KS_LAUNCH_GRID) {
     hipError_t e = launch_grid(kc, cfg.variant, a, st);
@@ -454,7 +471,10 @@ int ks_scan_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, co
   const uint32_t max_K = params->max_K ? params->max_K : KS_MAX_K;
   const int kc = k_class(max_K);
   ScanArgs a{samples, num_samples, desc, num_series, *params, max_K, out, all_U, all_U_len, 0, {}};
-  return scan_with(ctx, a, kc, config_for(ctx, kc, num_series, params->opts), (hipStream_t)stream);
+  const bool recorded = ctx->tuned.count(std::make_tuple(kc, num_series)) != 0;
+  const LaunchCfg cfg = recorded || params->opts ? config_for(ctx, kc, num_series, params->opts)
+                                                 : default_cfg(kc, num_samples, num_series);
+  return scan_with(ctx, a, kc, cfg, (hipStream_t)stream);
 }
 
 int ks_launch_set(ks_ctx* ctx, uint32_t max_K, uint32_t num_series, const ks_launch* cfg) {
@@ -563,7 +583,9 @@ int ks_scan_batch_noalloc(ks_ctx* ctx, const uint32_t* samples, uint64_t num_sam
                    reinterpret_cast<uint64_t*>(base + kScratchBase), reinterpret_cast<uint32_t*>(base + kScratchDone),
                    reinterpret_cast<uint32_t*>(base + kScratchMin), nullptr};
   ScanArgs a{samples, num_samples, desc, num_series, *params, max_K, out, all_U, all_U_len, ks::kNoSplit, ws};
-  const int v = config_for(ctx, kc, num_series, 0).variant;  // the tuned kernel variant (a table lookup)
+  // the tuned kernel variant (a table lookup), else the one for these sizes
+  const auto it = ctx->tuned.find(std::make_tuple(kc, num_series));
+  const int v = it != ctx->tuned.end() ? it->second.variant : default_cfg(kc, num_samples, num_series).variant;
   return launch_plan(ctx, kc, v, KS_LAUNCH_ORDERED, a, false, (hipStream_t)stream);
 }
 

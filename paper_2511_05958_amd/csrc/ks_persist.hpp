@@ -87,6 +87,49 @@ static __global__ __launch_bounds__(kPlanNT) void plan_kernel(const ks_desc* __r
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
   for (uint32_t b = tid; b < (uint32_t)kBuckets; b += kPlanNT) hist[b] = 0;
   __syncthreads();
+  if (chunk_bytes == kNoSplit) {
+    // the ordered grid needs the items alone: consecutive threads take
+    // consecutive series, kAhead of them at a time so that their descriptors are
+    // fetched together (a thread walking its own block of series, one fetch after
+    // the other, twice: 28 us for 8192 series)
+    constexpr uint32_t kAhead = 8;
+    auto bucket = [&](uint32_t s) {
+      const ks_desc d = desc[min(s, S - 1)];
+      uint32_t nc, b;
+      item_shape(d, num_samples, max_K, chunk_bytes, nc, b);
+      return b;
+    };
+    auto each = [&](auto&& visit) {
+      if (S <= (uint32_t)kPlanNT) {
+        visit(tid, bucket(tid), tid < S);
+        return;
+      }
+      for (uint32_t s = tid; s < S; s += kAhead * kPlanNT) {
+        uint32_t b[kAhead];
+#pragma unroll
+        for (uint32_t q = 0; q < kAhead; ++q) b[q] = bucket(s + q * kPlanNT);
+#pragma unroll
+        for (uint32_t q = 0; q < kAhead; ++q) visit(s + q * kPlanNT, b[q], s + q * kPlanNT < S);
+      }
+    };
+    each([&](uint32_t, uint32_t b, bool valid) { bin_add(hist, b, valid); });
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t run = 0;
+      for (int b = 0; b < kBuckets; ++b) {
+        start[b] = run;
+        run += hist[b];
+      }
+      ws.hdr[0] = 0;
+      ws.hdr[1] = run;
+    }
+    __syncthreads();
+    each([&](uint32_t s, uint32_t b, bool valid) {
+      const uint32_t at = bin_add(start, b, valid);
+      if (valid) ws.items[at] = Item{s, 0, 1};
+    });
+    return;
+  }
   const uint32_t per = (S + kPlanNT - 1) / kPlanNT;
   const uint32_t s0 = min(S, tid * per), s1 = min(S, s0 + per);
   uint64_t rows = 0;

@@ -115,4 +115,21 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// Per lane (valid): adds 1 to ctr[b] in LDS and returns its value before. Lanes
+// of one bin, as in a batch of equal series, make one addition of their number:
+// 8192 single ones to one address take longer than the rest of a plan.
+__device__ __forceinline__ uint32_t bin_add(uint32_t* ctr, uint32_t b, bool valid) {
+  const uint64_t m = ballot(valid);
+  if (m == 0) return 0;
+  const uint32_t first = (uint32_t)__builtin_ctzll(m);
+  const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)b, (int)first);
+  if (ballot(valid && b != b0) == 0) {
+    uint32_t at = 0;
+    if (lane_id() == first) at = atomicAdd(&ctr[b0], (uint32_t)__popcll(m));
+    at = (uint32_t)__builtin_amdgcn_readlane((int)at, (int)first);
+    return at + mbcnt(m);
+  }
+  return valid ? atomicAdd(&ctr[b], 1u) : 0u;
+}
+
 }  // namespace ks
