@@ -265,7 +265,7 @@ int ks_scan_batch_noalloc(ks_ctx *ctx, const uint32_t *samples, uint64_t num_sam
 
 #define KS_CNN_PARAMS 44993u
 /* Largest N the feature and statistics passes accept: every row length the
- * scan accepts. Rows of up to 4096 + 3 samples are held in registers; longer
+ * scan accepts. Rows of up to 2048 + 3 samples are held in registers; longer
  * rows are streamed through the same order-statistics select. */
 #define KS_FEATURE_MAX_N KS_MAX_N
 

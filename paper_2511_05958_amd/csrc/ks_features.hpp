@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t feature_rows(RowLds* sel, CoopLds<W>& co, vo
                                                  float* __restrict__ feat_ws) {
   constexpr uint32_t kFeatStage = feat_stage_rows(NB);
   static_assert(kFeatStage <= (uint32_t)kWave, "a flush writes one row's moments per lane");
-  const RowSpan sp = row_span<NB, W>(d.K, c, C, num_series, w);
+  const RowSpan sp = row_span<NB, W>(d.K, d.N, c, C, num_series, w);
   FeatStage<kFeatStage>& st = reinterpret_cast<FeatStage<kFeatStage>*>(stage)[w];
   uint32_t gmin = 0xffffffffu;
   // row i's results; its deciles on lanes first .. first + 8
@@ -122,7 +122,6 @@ __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves
   };
   rows(std::integral_constant<int, 1>{});
   rows(std::integral_constant<int, 2>{});
-  rows(std::integral_constant<int, 4>{});
   rows(std::integral_constant<int, (int)kStreamed>{});
   rows(std::integral_constant<int, (int)kGrouped>{});
   if (lane == 0) red[w] = gmin;

@@ -393,7 +393,7 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
   LearnBuffers& b = ctx->learn;
   const bool one = num_series <= ks::kRowPassOneLaunch;
   uint32_t Cs = 1;  // most chunks that a launch below makes of a series
-  for (uint32_t mask : {ks::kRowsOne, ks::kRowsMid, ks::kRowsFour, ks::kRowsAll})
+  for (uint32_t mask : {ks::kRowsOne, ks::kRowsMid, ks::kRowsAll})
     if ((mask == ks::kRowsAll) == one) Cs = std::max(Cs, ks::row_pass_chunks(num_series, max_K, mask));
   auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
     const uint32_t C = ks::row_pass_chunks(num_series, max_K, mask);
@@ -411,7 +411,6 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
                        max_K, plan);
     launch(ks::features_kernel<ks::kRowsOne>, ks::kRowsOne, plan);
     launch(ks::features_kernel<ks::kRowsMid>, ks::kRowsMid, plan);
-    launch(ks::features_kernel<ks::kRowsFour>, ks::kRowsFour, plan);
   }
   hipLaunchKernelGGL((ks::feature_pack_kernel<kNT>), dim3(num_series, (SR + kNT - 1) / kNT), dim3(kNT), 0, st, desc,
                      num_series, features, feature_rows, b.x0, SR, learn_ws(ctx), b.feat, Cs);

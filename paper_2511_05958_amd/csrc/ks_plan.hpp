@@ -13,7 +13,7 @@
 namespace ks {
 namespace {  // the kernel is compiled into each translation unit that launches it
 
-// Series order (one workgroup): per row class (1, 2 or 4 load batches,
+// Series order (one workgroup): per row class (1 or 2 load batches,
 // streamed, or short rows four to a wave) the series largest first, bucketed
 // by the bit length of their sample bytes (a longest-processing-time order,
 // so a class's launch starts its longest workgroups first and no workgroup
@@ -24,9 +24,9 @@ namespace {  // the kernel is compiled into each translation unit that launches 
 constexpr int kFeatPlanNT = 1024;
 constexpr uint32_t kFeatBuckets = 40;
 
-constexpr uint32_t kFeatClasses = 5;
+constexpr uint32_t kFeatClasses = 4;
 __host__ __device__ constexpr uint32_t feat_class_index(uint32_t NB) {
-  return NB == 1 ? 0u : (NB == 2 ? 1u : (NB == 4 ? 2u : (NB == kStreamed ? 3u : 4u)));
+  return NB == 1 ? 0u : (NB == 2 ? 1u : (NB == kStreamed ? 2u : 3u));
 }
 
 __global__ __launch_bounds__(kFeatPlanNT) void feature_plan_kernel(const ks_desc* __restrict__ desc,
@@ -85,7 +85,7 @@ template <uint32_t MASK>
 __device__ __forceinline__ uint32_t row_pass_series(const uint32_t* __restrict__ plan, uint32_t num_series,
                                                     uint32_t t) {
   if (!plan) return t;
-  constexpr uint32_t order[kFeatClasses] = {3u, 2u, 1u, 0u, 4u};
+  constexpr uint32_t order[kFeatClasses] = {2u, 1u, 0u, 3u};
 #pragma unroll
   for (uint32_t q = 0; q < kFeatClasses; ++q) {
     const uint32_t ci = order[q];

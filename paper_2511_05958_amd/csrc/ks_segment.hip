@@ -43,29 +43,26 @@ void free_seg(SegBuffers& b) {
 
 namespace {
 
-constexpr int kTreeNT = 1024;
-constexpr uint32_t kTreeW = kTreeNT / ks::kWave;
+// Threads of a series' workgroup: barriers of eight waves are cheaper, and for
+// K classes of up to 256 rows eight waves are enough for a window (4096 series
+// of 256 x 1024 741 us, 769 with sixteen; 512 of up to 512 x 4096 354 and 269).
+constexpr int tree_nt(int kmax) { return kmax <= 256 ? 512 : 1024; }
 
 constexpr uint32_t kSmall = ks::kWave;  // windows of up to this many rows are a wave's work
 
 template <int KMAX>
 struct TreeSmem {
+  static constexpr int NT = tree_nt(KMAX);
+  static constexpr uint32_t W = NT / ks::kWave;
   uint64_t s1[KMAX], s2lo[KMAX];  // the series' rows
   uint32_t s2hi[KMAX], rmin[KMAX];
   union {
-    struct {  // a window that the workgroup shares
-      uint64_t lo[KMAX], hi[KMAX];
-      uint32_t rank[KMAX];
-      __align__(16) uint16_t is[KMAX];
-      uint16_t pos[KMAX];
-      uint64_t tie[(KMAX + ks::kWave - 1) / ks::kWave];
-      uint32_t partU[kTreeNT], bestU[kTreeW], bestC[kTreeW], red[kTreeW];
-    };
+    ks::RankSmem<KMAX, NT> rw;  // a window that the workgroup shares
     struct {  // a wave's window
       uint64_t lo[kSmall], hi[kSmall];
       uint64_t stack[kSmall / 2];
       uint32_t order[kSmall];
-    } wave[kTreeW];
+    } wave[W];
   };
   // open windows, a | b << 16 | depth << 32, disjoint: those of more than
   // kSmall rows (the workgroup's stack), and the others (the waves' list)
@@ -78,15 +75,6 @@ struct TreeSmem {
 
 __device__ __forceinline__ uint64_t pack_window(uint32_t a, uint32_t b, uint32_t depth) {
   return (uint64_t)depth << 32 | (uint64_t)b << 16 | a;
-}
-
-// Publishes this thread's LDS writes to the workgroup. The wait is written out:
-// for a barrier at the head of a loop the compiler left out the wait for LDS
-// writes that reach it over the back edge (a push onto the stack), and the other
-// waves then read the entry before it was there.
-__device__ __forceinline__ void publish() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __syncthreads();
 }
 
 // A window of at most kSmall rows and every window that opens inside it, by the
@@ -156,110 +144,37 @@ __device__ __forceinline__ void tree_small(TreeSmem<KMAX>& sm, uint64_t window, 
 template <int KMAX>
 __device__ __forceinline__ void tree_window(TreeSmem<KMAX>& sm, uint32_t a, uint32_t K, uint32_t depth, uint32_t N,
                                             double c_alpha, uint32_t n) {
-  const uint32_t tid = threadIdx.x, lane = ks::lane_id(), w = ks::wave_id();
+  constexpr uint32_t kTreeNT = TreeSmem<KMAX>::NT;
+  const uint32_t tid = threadIdx.x;
   uint32_t mn = 0xffffffffu;
   for (uint32_t i = tid; i < K; i += kTreeNT) mn = min(mn, sm.rmin[a + i]);
-  const uint32_t gmin = ks::block_min_u32<kTreeNT>(mn, sm.red);
-  bool w53 = false;
-  for (uint32_t i = tid; i < K; i += kTreeNT) {
-    const ks::SortKey k = ks::sort_key(sm.s1[a + i], sm.s2lo[a + i], sm.s2hi[a + i], i, N, gmin);
-    sm.lo[i] = k.lo;
-    sm.hi[i] = k.hi;
-    sm.rank[i] = 0;
-    w53 |= k.hi != 0;
-  }
-  const bool wide = ks::block_any<kTreeNT>(w53, sm.red);
-  {  // several threads count for one row where there are fewer rows than threads
-    const uint32_t KR = min((K + ks::kWave - 1u) & ~(uint32_t)(ks::kWave - 1), (uint32_t)kTreeNT), P = kTreeNT / KR;
-    const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
-    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
-    if (q < P)
-      for (uint32_t i = i0; i < K; i += KR)
-        atomicAdd(&sm.rank[i], ks::count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
-  }
-  __syncthreads();
-  for (uint32_t i = tid; i < K; i += kTreeNT) {
-    const uint32_t p = sm.rank[i];
-    sm.is[p] = (uint16_t)i;
-    sm.pos[i] = (uint16_t)p;
-  }
-  __syncthreads();
-  bool tied = false;
-  for (uint32_t p0 = w * ks::kWave; p0 < K; p0 += kTreeNT) {
-    const uint32_t p = p0 + lane;
-    bool end = false;
-    if (p < K) {
-      const uint32_t i = sm.is[p], j = sm.is[min(p + 1, K - 1)];
-      end = p + 1 == K || ks::group_end(ks::SortKey{sm.lo[i], sm.hi[i]}, ks::SortKey{sm.lo[j], sm.hi[j]});
-    }
-    const uint64_t m = ks::ballot(end);
-    if (lane == 0) sm.tie[p0 / ks::kWave] = m;
-    tied |= m != ks::ballot(p < K);
-  }
-  const bool ties = ks::block_any<kTreeNT>(tied, sm.red);
-  // 64-candidate slots: the waves of a slot share the positions (shares of a
-  // multiple of 8), or a wave walks its slots one after the other
-  const uint32_t ns = (K - 1u + ks::kWave - 1u) / ks::kWave;
-  uint32_t bU = 0, bC = 0;
-  if (ns < kTreeW) {
-    const uint32_t Q = kTreeW / ns, slot = w / Q, share = w % Q;
-    const uint32_t len = ((K + Q - 1) / Q + 7u) & ~7u;
-    uint32_t c[1] = {1u + slot * ks::kWave + lane}, U[1] = {0};
-    if (slot < ns) {
-      const uint32_t pa = min(K, share * len), pb = min(K, pa + len);
-      if (pa < pb) ks::walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, pa, pb, c, U);
-    }
-    sm.partU[tid] = U[0];
-    __syncthreads();
-    if (slot < ns && share == 0) {
-      for (uint32_t q = 1; q < Q; ++q) U[0] = max(U[0], sm.partU[tid + q * ks::kWave]);
-      if (c[0] < K) {
-        bU = U[0];
-        bC = c[0];
-      }
-    }
-  } else {
-    for (uint32_t slot = w; slot < ns; slot += kTreeW) {
-      uint32_t c[1] = {1u + slot * ks::kWave + lane}, U[1];
-      ks::walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, 0, K, c, U);
-      if (c[0] < K && (bC == 0 || ks::more_significant(U[0], c[0], bU, bC, K))) {
-        bU = U[0];
-        bC = c[0];
-      }
+  const uint32_t gmin = ks::block_min_u32<kTreeNT>(mn, sm.rw.red);
+  uint32_t bU, bC;
+  ks::rank_walk(
+      sm.rw, [&](uint32_t i) { return ks::sort_key(sm.s1[a + i], sm.s2lo[a + i], sm.s2hi[a + i], i, N, gmin); }, K, 1u,
+      K - 1u, nullptr, bU, bC);
+  if (tid == 0) {
+    const bool sig = ks::significant(bU, bC, K, c_alpha);
+    sm.split = sig ? bC : 0u;
+    if (sig) {
+      sm.fU[n] = bU;
+      sm.fa[n] = (uint16_t)a;
+      sm.fb[n] = (uint16_t)(a + K);
+      sm.fc[n] = (uint16_t)(a + bC);
+      sm.fd[n] = (uint16_t)depth;
     }
   }
-  ks::wave_best(bU, bC, K);
-  if (lane == 0) {
-    sm.bestU[w] = bU;
-    sm.bestC[w] = bC;
-  }
-  __syncthreads();
-  if (w == 0) {
-    bU = lane < kTreeW ? sm.bestU[lane] : 0u;
-    bC = lane < kTreeW ? sm.bestC[lane] : 0u;
-    ks::wave_best(bU, bC, K);
-    if (lane == 0) {
-      const bool sig = ks::significant(bU, bC, K, c_alpha);
-      sm.split = sig ? bC : 0u;
-      if (sig) {
-        sm.fU[n] = bU;
-        sm.fa[n] = (uint16_t)a;
-        sm.fb[n] = (uint16_t)(a + K);
-        sm.fc[n] = (uint16_t)(a + bC);
-        sm.fd[n] = (uint16_t)depth;
-      }
-    }
-  }
-  __syncthreads();
+  ks::block_publish();
 }
 
 // rows: the moments of series s at s * max_K (nullptr: streamed here).
 template <int KMAX>
-__global__ __launch_bounds__(kTreeNT) void seg_tree_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
+__global__ __launch_bounds__(tree_nt(KMAX)) void seg_tree_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
                                                            const ks_desc* __restrict__ desc, ks_params prm,
                                                            uint32_t max_K, const ks::RowMom* __restrict__ rows,
                                                            uint32_t max_levels, uint32_t max_cp,
                                                            ks_result* __restrict__ cps, uint32_t* __restrict__ counts) {
+  constexpr uint32_t kTreeNT = TreeSmem<KMAX>::NT, kTreeW = TreeSmem<KMAX>::W;
   __shared__ TreeSmem<KMAX> sm;
   const uint32_t s = blockIdx.x, tid = threadIdx.x, lane = ks::lane_id();
   const ks_desc d = desc[s];
@@ -295,7 +210,7 @@ __global__ __launch_bounds__(kTreeNT) void seg_tree_kernel(const uint32_t* __res
     big ? ++top : ++small;
   };
   open(0, K, 0);
-  publish();
+  ks::block_publish();
   while (top > 0) {  // what is read from LDS here is the same for every thread: scalars, so that the loop is the scalar unit's
     const uint64_t e = sm.stack[--top];
     const uint32_t ab = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
@@ -310,13 +225,13 @@ __global__ __launch_bounds__(kTreeNT) void seg_tree_kernel(const uint32_t* __res
         if (c >= 2) open(a, a + c, depth + 1);
       }
     }
-    publish();
+    ks::block_publish();
   }
   if (tid == 0) {
     sm.found = found;
     sm.next = 0;
   }
-  publish();
+  ks::block_publish();
   for (;;) {  // the small windows, a wave each
     uint32_t j = 0;
     if (lane == 0) j = atomicAdd(&sm.next, 1u);
@@ -346,7 +261,7 @@ template <int KMAX>
 void launch_tree(uint32_t num_series, hipStream_t st, const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,
                  const ks_params& prm, uint32_t max_K, const ks::RowMom* rows, uint32_t max_levels, uint32_t max_cp,
                  ks_result* cps, uint32_t* counts) {
-  hipLaunchKernelGGL(seg_tree_kernel<KMAX>, dim3(num_series), dim3(kTreeNT), 0, st, samples, num_samples, desc, prm,
+  hipLaunchKernelGGL(seg_tree_kernel<KMAX>, dim3(num_series), dim3(tree_nt(KMAX)), 0, st, samples, num_samples, desc, prm,
                      max_K, rows, max_levels, max_cp, cps, counts);
 }
 

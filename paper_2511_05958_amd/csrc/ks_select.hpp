@@ -1,5 +1,5 @@
 // Order statistics of rows of uint32 samples, one wave per row: the row held
-// in registers (1, 2 or 4 load batches per lane) or, for longer rows, streamed
+// in registers (1 or 2 load batches per lane) or, for longer rows, streamed
 // in batches; its minimum and maximum by DPP, its moments (sum r, sum r^2)
 // fused with a histogram of its keys, and a multi-rank select for up to nine
 // target ranks. Used by the learned path's decile features and by the per-row
@@ -48,7 +48,7 @@ constexpr uint32_t kSelW = 7;      // bits of every later digit
 constexpr uint32_t kSelNone = 9;   // group of keys outside every target's prefix
 constexpr uint32_t kSelEmpty = 0xffffffffu;  // key of a slot without a sample
 
-// Row classes of the row passes (feat_batches): 1, 2, 4 load batches per row
+// Row classes of the row passes (feat_batches): 1 or 2 load batches per row
 // held in registers, kStreamed rows read in batches, kGrouped short rows four
 // to a wave.
 constexpr uint32_t kStreamed = 8;
@@ -710,7 +710,7 @@ __device__ __forceinline__ uint32_t row_select(RowLds& L, const uint32_t* __rest
 }
 
 // ------------------------------------------------------- rows of any length
-// Rows longer than four load batches per lane (N > 4096 + 3) do not fit in
+// Rows longer than two load batches per lane (N > 2048 + 3) are not held in
 // registers; one wave streams them in batches of 16 bytes x 4 per lane, the
 // next batch always in flight while the current one is summed.
 
@@ -970,7 +970,7 @@ __device__ __forceinline__ void select_rows_coop(RowLds* sel, CoopLds<W>& co, co
   };
   for (uint32_t i = begin; i < end; ++i) {
     const RowGeo g = row_geo(samples, off0 + (uint64_t)i * N, N);
-    __syncthreads();  // the previous row's windows and totals have been read
+    block_publish();  // the previous row's windows and totals have been read
     clear_window(hist, lane);
     Batch A, B;
     load_batch(A, samples, g, 0u, lane);
@@ -1287,29 +1287,26 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 
 // Row class of the order-statistics kernels: rows of up to kGroupMaxN samples
 // go four to a wave (class kGrouped); otherwise a row of N samples needs
-// ceil(floor(N / 4) / 256) load batches at most, and rows of up to 1, 2 or 4
-// of them are held in registers (class 1, 2, 4), longer rows are streamed
-// (class kStreamed).
+// ceil(floor(N / 4) / 256) load batches at most, and rows of up to 1 or 2 of
+// them are held in registers (class 1, 2), longer rows are streamed (class
+// kStreamed; four batches in registers left three waves per SIMD, and rows of
+// 4096 samples took 835 us for 1024 x 256, 681 streamed).
 // A launch serves a set of classes (a mask of 1 << feat_class_index), classes of
 // like register use together, since an empty launch costs 4.5 us (with one per
-// class four of the five were empty): rows of one load batch; short rows, rows
-// of two batches and streamed rows (four waves per SIMD each); rows of four
-// batches (three); or, for a batch of few series, all of them at once.
+// class most were empty): rows of one load batch (five waves per SIMD); the
+// other classes (four); or, for a batch of few series, all of them at once.
 // Workgroups of 256 threads, 512 where rows of two batches are served (eight
 // waves on a series; 1% faster than 256 threads on 8192 x 1024 x 2048).
-constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 8u | 16u, kRowsFour = 4u, kRowsAll = 31u;
-__host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return (mask & 2u) ? 512 : 256; }
-// Waves per SIMD the row-pass kernels are compiled for: 6 (80 registers) for rows of one batch, the largest target met
-// without spills, runs rows of up to 1027 samples 6 - 9% faster than the 5 the
-// compiler picks by itself.
-__host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : mask == kRowsMid ? 4 : 3; }
+constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 4u | 8u, kRowsAll = 15u;
+__host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return mask == kRowsOne ? 256 : 512; }
+// Waves per SIMD the row-pass kernels are compiled for, the largest without
+// spills.
+__host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : 4; }
 __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
   return N <= kGroupMaxN ? kGrouped
-         : (N / 4 + 4u * kWave - 1) / (4u * kWave) <= 1
-             ? 1u
-             : ((N / 4 + 4u * kWave - 1) / (4u * kWave) <= 2
-                    ? 2u
-                    : ((N / 4 + 4u * kWave - 1) / (4u * kWave) <= 4 ? 4u : kStreamed));
+         : N / 4 <= 4u * kWave ? 1u
+         : N / 4 <= 8u * kWave ? 2u
+                               : kStreamed;
 }
 
 // Split of the row passes over workgroups. A series' rows are cut into C chunks,
@@ -1348,9 +1345,12 @@ struct RowSpan {
   bool coop;
 };
 template <int NB, int W>
-__device__ __forceinline__ RowSpan row_span(uint32_t K, uint32_t c, uint32_t C, uint32_t num_series, uint32_t w) {
+__device__ __forceinline__ RowSpan row_span(uint32_t K, uint32_t N, uint32_t c, uint32_t C, uint32_t num_series,
+                                            uint32_t w) {
   uint32_t R = (K + C - 1) / C;
-  const bool coop = NB == (int)kStreamed && R < (uint32_t)W && (uint64_t)num_series * K <= kCoopRows;
+  const uint64_t rows = (uint64_t)num_series * K;
+  const bool coop = NB == (int)kStreamed && R < (uint32_t)W &&
+                    (rows <= 512 || (rows <= kCoopRows && N >= W * 64u * kWave));
   if (!coop) R = max(R, (uint32_t)W * (NB == (int)kGrouped ? kGroupRows : 1u));
   const uint32_t r0 = (uint32_t)min((uint64_t)c * R, (uint64_t)K), r1 = min(r0 + R, K);
   if (coop) return RowSpan{r0, r1, true};

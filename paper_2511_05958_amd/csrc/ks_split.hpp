@@ -275,21 +275,123 @@ __global__ __launch_bounds__(kSplitWalkNT) void split_walk_kernel(uint64_t num_s
   if (lane == 0) write_choice(out + s, bU, bC, K, prm, 0u);
 }
 
+// ---------------------------------------------------------------- one workgroup
+// Keys, order and the most significant split of one series or window whose row
+// moments are at hand, by one workgroup: every row's rank counted (a few threads
+// to a row where there are fewer rows than threads), the walk shared by all
+// waves. For a few hundred rows that is a handful of barriers, where the radix
+// sort of finish_series makes four for each of some ten digits.
+template <int KMAX, int NT>
+struct RankSmem {
+  static constexpr uint32_t W = NT / kWave;
+  uint64_t lo[KMAX], hi[KMAX];
+  uint32_t rank[KMAX];
+  __align__(16) uint16_t is[KMAX];
+  uint16_t pos[KMAX];
+  uint64_t tie[(KMAX + kWave - 1) / kWave];
+  uint32_t partU[NT], bestU[W], bestC[W], red[W];
+};
+
+// key(i): row i's key (i < K). Candidates c_lo .. c_hi; their statistics to
+// allU (nullable). Wave 0 returns the winner (c = 0: no candidate).
+template <int KMAX, int NT, class Key>
+__device__ __forceinline__ void rank_walk(RankSmem<KMAX, NT>& sm, Key&& key, uint32_t K, uint32_t c_lo, uint32_t c_hi,
+                                          uint32_t* __restrict__ allU, uint32_t& bU, uint32_t& bC) {
+  constexpr uint32_t W = NT / kWave;
+  const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  bool w53 = false;
+  for (uint32_t i = tid; i < K; i += NT) {
+    const SortKey k = key(i);
+    sm.lo[i] = k.lo;
+    sm.hi[i] = k.hi;
+    sm.rank[i] = 0;
+    w53 |= k.hi != 0;
+  }
+  const bool wide = block_any<NT>(w53, sm.red);
+  {  // several threads count for one row where there are fewer rows than threads
+    const uint32_t KR = min((K + kWave - 1u) & ~(uint32_t)(kWave - 1), (uint32_t)NT), P = NT / KR;
+    const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
+    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
+    if (q < P)
+      for (uint32_t i = i0; i < K; i += KR)
+        atomicAdd(&sm.rank[i], count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < K; i += NT) {
+    const uint32_t p = sm.rank[i];
+    sm.is[p] = (uint16_t)i;
+    sm.pos[i] = (uint16_t)p;
+  }
+  __syncthreads();
+  bool tied = false;
+  for (uint32_t p0 = w * kWave; p0 < K; p0 += NT) {
+    const uint32_t p = p0 + lane;
+    bool end = false;
+    if (p < K) {
+      const uint32_t i = sm.is[p], j = sm.is[min(p + 1, K - 1)];
+      end = p + 1 == K || group_end(SortKey{sm.lo[i], sm.hi[i]}, SortKey{sm.lo[j], sm.hi[j]});
+    }
+    const uint64_t m = ballot(end);
+    if (lane == 0) sm.tie[p0 / kWave] = m;
+    tied |= m != ballot(p < K);
+  }
+  const bool ties = block_any<NT>(tied, sm.red);
+  // 64-candidate slots: the waves of a slot share the positions (shares of a
+  // multiple of 8), or a wave walks its slots one after the other
+  const uint32_t ns = (c_hi - c_lo + kWave) / kWave;
+  bU = 0;
+  bC = 0;
+  auto consider = [&](uint32_t c, uint32_t U) {
+    if (c > c_hi) return;
+    if (allU) allU[c] = U;
+    if (bC == 0 || more_significant(U, c, bU, bC, K)) {
+      bU = U;
+      bC = c;
+    }
+  };
+  if (ns < W) {
+    const uint32_t Q = W / ns, slot = w / Q, share = w % Q;
+    const uint32_t len = ((K + Q - 1) / Q + 7u) & ~7u;
+    uint32_t c[1] = {c_lo + slot * kWave + lane}, U[1] = {0};
+    if (slot < ns) {
+      const uint32_t pa = min(K, share * len), pb = min(K, pa + len);
+      if (pa < pb) walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, pa, pb, c, U);
+    }
+    sm.partU[tid] = U[0];
+    __syncthreads();
+    if (slot < ns && share == 0) {
+      for (uint32_t q = 1; q < Q; ++q) U[0] = max(U[0], sm.partU[tid + q * kWave]);
+      consider(c[0], U[0]);
+    }
+  } else {
+    for (uint32_t slot = w; slot < ns; slot += W) {
+      uint32_t c[1] = {c_lo + slot * kWave + lane}, U[1];
+      walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, 0, K, c, U);
+      consider(c[0], U[0]);
+    }
+  }
+  wave_best(bU, bC, K);
+  if (lane == 0) {
+    sm.bestU[w] = bU;
+    sm.bestC[w] = bC;
+  }
+  __syncthreads();
+  if (w == 0) {
+    bU = lane < W ? sm.bestU[lane] : 0u;
+    bC = lane < W ? sm.bestC[lane] : 0u;
+    wave_best(bU, bC, K);
+  }
+}
+
 template <int KMAX>
 __global__ __launch_bounds__(kTinyNT) void tiny_scan_kernel(const uint32_t* __restrict__ samples, uint64_t num_samples,
                                                             const ks_desc* __restrict__ desc, ks_params prm,
                                                             uint32_t max_K, ks_result* __restrict__ out,
                                                             uint32_t* __restrict__ allU, uint64_t allU_len) {
   constexpr uint32_t W = kTinyNT / kWave;
-  constexpr uint32_t P = kTinyNT / KMAX;  // threads counting for one row
-  static_assert(KMAX >= kWave && KMAX * P == kTinyNT && KMAX / kWave <= (int)W, "rows on threads, slots on waves");
-  __shared__ uint64_t s1[KMAX], s2lo[KMAX], lo[KMAX], hi[KMAX];
-  __shared__ uint32_t s2hi[KMAX], rank[KMAX];
-  __shared__ SortKey sk[KMAX];
-  __shared__ __align__(16) uint16_t is[KMAX];
-  __shared__ uint16_t pos[KMAX];
-  __shared__ uint64_t tie[KMAX / kWave];
-  __shared__ uint32_t partU[W * kWave], red[W];
+  __shared__ uint64_t s1[KMAX], s2lo[KMAX];
+  __shared__ uint32_t s2hi[KMAX];
+  __shared__ RankSmem<KMAX, kTinyNT> sm;
   const uint32_t s = blockIdx.x;
   const ks_desc d = desc[s];
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -307,67 +409,14 @@ __global__ __launch_bounds__(kTinyNT) void tiny_scan_kernel(const uint32_t* __re
                                       s2hi[i] = h;
                                     }
                                   });
-  const uint32_t gmin = block_min_u32<kTinyNT>(mn, red);  // its barriers publish the moments
-  bool w53 = false;
-  if (tid < K) {
-    const SortKey k = sort_key(s1[tid], s2lo[tid], s2hi[tid], tid, N, gmin);
-    lo[tid] = k.lo;
-    hi[tid] = k.hi;
-    rank[tid] = 0;
-    w53 = k.hi != 0;
-  }
-  const bool wide = block_any<kTinyNT>(w53, red);
-  {
-    const uint32_t i = tid % KMAX, q = tid / KMAX, len = (K + P - 1) / P;
-    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
-    if (i < K) atomicAdd(&rank[i], count_below(lo, hi, j0, j1, lo[i], hi[i], wide));
-  }
-  __syncthreads();
-  if (tid < K) {
-    const uint32_t p = rank[tid];
-    is[p] = (uint16_t)tid;
-    pos[tid] = (uint16_t)p;
-    sk[p] = SortKey{lo[tid], hi[tid]};
-  }
-  __syncthreads();
-  bool tied = false;
-  if (w * kWave < K) {
-    const uint32_t p = tid;
-    const bool end = p < K && (p + 1 == K || group_end(sk[p], sk[min(p + 1, (uint32_t)KMAX - 1u)]));
-    const uint64_t m = ballot(end);
-    if (lane == 0) tie[w] = m;
-    tied = m != ballot(p < K);
-  }
-  const bool ties = block_any<kTinyNT>(tied, red);
-  // the waves of a slot share the positions (shares of a multiple of 8)
-  const uint32_t ns = (K - 1u + kWave - 1u) / kWave, Q = W / ns;
-  const uint32_t slot = w / Q, share = w % Q;
-  const uint32_t len = ((K + Q - 1) / Q + 7u) & ~7u;
-  uint32_t c[1] = {1u + slot * kWave + lane}, U[1] = {0};
-  if (slot < ns) {
-    const uint32_t pa = min(K, share * len), pb = min(K, pa + len);
-    if (pa < pb) walk_pass<KMAX, 1>(is, pos, tie, ties, K, pa, pb, c, U);
-  }
-  partU[w * kWave + lane] = U[0];
-  __syncthreads();
-  if (w != 0) return;
+  const uint32_t gmin = block_min_u32<kTinyNT>(mn, sm.red);  // its barriers publish the moments
   const bool fits = allU && d.aux_offset <= allU_len && K <= allU_len - d.aux_offset;
-  uint32_t bU = 0, bC = 0;
-  for (uint32_t j = 0; j < ns; ++j) {
-    uint32_t u = 0;
-    for (uint32_t q = 0; q < Q; ++q) u = max(u, partU[(j * Q + q) * kWave + lane]);
-    const uint32_t cc = 1u + j * kWave + lane;
-    if (cc > K - 1u) continue;
-    if (fits) allU[d.aux_offset + cc] = u;
-    if (bC == 0 || more_significant(u, cc, bU, bC, K)) {
-      bU = u;
-      bC = cc;
-    }
-  }
-  wave_best(bU, bC, K);
-  if (lane != 0) return;
-  if (fits) allU[d.aux_offset] = 0;
-  write_choice(out + s, bU, bC, K, prm, 0u);
+  uint32_t* au = fits ? allU + d.aux_offset : nullptr;
+  uint32_t U, c;
+  rank_walk(sm, [&](uint32_t i) { return sort_key(s1[i], s2lo[i], s2hi[i], i, N, gmin); }, K, 1u, K - 1u, au, U, c);
+  if (tid != 0) return;
+  if (fits) au[0] = 0;
+  write_choice(out + s, U, c, K, prm, 0u);
 }
 
 }  // namespace

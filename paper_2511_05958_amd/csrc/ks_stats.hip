@@ -64,7 +64,7 @@ __device__ __forceinline__ void stats_rows(ks::RowLds* sel, ks::CoopLds<W>& co, 
   constexpr uint32_t kStage = stats_stage_rows(NB);
   static_assert(kStage <= (uint32_t)ks::kWave, "a flush makes one record per lane");
   const uint32_t N = d.N;
-  const ks::RowSpan sp = ks::row_span<NB, W>(d.K, c, C, num_series, w);
+  const ks::RowSpan sp = ks::row_span<NB, W>(d.K, d.N, c, C, num_series, w);
   RowStage<kStage>& st = reinterpret_cast<RowStage<kStage>*>(stage)[w];
   // row i's results; its p50 and p95 on lanes first and first + 1
   ks::select_rows<NB, StatRanks, W>(sel, co, samples, d.offset, N, sp, w, lane,
@@ -138,7 +138,6 @@ __global__ __launch_bounds__(ks::row_pass_threads(MASK)) __attribute__((amdgpu_w
   };
   rows(std::integral_constant<int, 1>{});
   rows(std::integral_constant<int, 2>{});
-  rows(std::integral_constant<int, 4>{});
   rows(std::integral_constant<int, (int)ks::kStreamed>{});
   rows(std::integral_constant<int, (int)ks::kGrouped>{});
 }
@@ -171,7 +170,6 @@ extern "C" int ks_stats_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num
                        max_K, plan);
     launch(row_stats_kernel<ks::kRowsOne>, ks::kRowsOne, plan);
     launch(row_stats_kernel<ks::kRowsMid>, ks::kRowsMid, plan);
-    launch(row_stats_kernel<ks::kRowsFour>, ks::kRowsFour, plan);
   }
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "row stats launch");

@@ -132,4 +132,13 @@ __device__ __forceinline__ uint32_t bin_add(uint32_t* ctr, uint32_t b, bool vali
   return valid ? atomicAdd(&ctr[b], 1u) : 0u;
 }
 
+// Publishes this thread's LDS writes to the workgroup. The wait is written out:
+// for a barrier at the head of a loop the compiler left out the wait for LDS
+// writes that reach it over the back edge, and other waves then read what was
+// not there yet.
+__device__ __forceinline__ void block_publish() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
 }  // namespace ks
