@@ -70,13 +70,23 @@ __device__ __forceinline__ float pos_centre(uint32_t t, uint32_t K) {
 // FT + 12 = 128 rows of layer 0 make eight blocks.
 constexpr int FT = 116;
 constexpr int FROWS = 16 * 8 + 4;  // buffer rows: eight blocks and the taps past them
-constexpr int FST = 64 + 8;        // LDS row stride of a 64-channel buffer (bf16)
+// A 64-channel buffer in LDS: two planes of rows, the 8-channel chunks 0, 2, 4, 6
+// in one and 1, 3, 5, 7 in the other, 80 bytes a row. An operand read takes
+// chunk kg (+ 4) of row m for lane (m, kg), and the hardware serves lanes m = 0..3
+// of one kg together with m = 4..7 of the next: in one 144-byte row of all chunks
+// those met on the same banks (45% of the fused forward's LDS cycles), here
+// they are eight different rows at 80 bytes.
+constexpr int FPS = 32 + 8;                             // row stride of a plane (bf16)
+constexpr int FPL = (FROWS * FPS * 2 + 127) / 128 * 64;  // one plane, whole turns of the banks
+__device__ __forceinline__ constexpr uint32_t act_at(uint32_t row, uint32_t chunk) {
+  return (chunk & 1u) * FPL + row * FPS + (chunk >> 1) * 8u;
+}
 constexpr int FXS = 16 + 8;        // LDS row stride of the 16-channel input buffer
 constexpr int FW3 = 320 + 8;       // LDS row stride of the last layer's weights
 constexpr int FWGS = 2;            // workgroups per CU (registers)
 
 struct FusedSmem {
-  uint16_t act[2][FROWS * FST];
+  uint16_t act[2][2 * FPL];
   uint16_t x[FROWS * FXS];
   uint16_t w3[2 * FW3];  // row 0: W3[0][j]; row 1: zeros (output channels 1..15)
   float bias[3 * 64];
@@ -94,11 +104,11 @@ __device__ __forceinline__ uint32_t pack_bf(float a, float b) {
 
 // Products of a CIN-channel kernel-5 layer for G row blocks 32 rows apart and
 // this wave's 32 output channels: in points at this lane's row of the first
-// block (tap 0), Wt holds W[o][32 q + 8 kg .. + 7] of its two channel tiles.
+// block (tap 0; its chunk kg for 64 channels), Wt holds W[o][32 q + 8 kg .. + 7] of its two channel tiles.
 template <int CIN, int NQ, int G>
 __device__ __forceinline__ void conv_blocks(const uint16_t* __restrict__ in, const u32x4 (&Wt)[NQ][2], uint32_t kg,
                                             f32x4 (&acc)[G][2]) {
-  constexpr int ST = CIN == 64 ? FST : FXS;
+  constexpr int ST = CIN == 64 ? FPS : FXS;
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -107,7 +117,7 @@ __device__ __forceinline__ void conv_blocks(const uint16_t* __restrict__ in, con
   // compiler from hoisting every step's loads (and their registers)
   auto load = [&](int q, u32x4 (&x)[G]) {
     const int j0 = q * 32 + (int)kg * 8;
-    const int k = CIN == 64 ? q / 2 : j0 / CIN, i0 = CIN == 64 ? (q & 1) * 32 + (int)kg * 8 : j0 % CIN;
+    const int k = CIN == 64 ? q / 2 : j0 / CIN, i0 = CIN == 64 ? (q & 1) * 16 : j0 % CIN;
 #pragma unroll
     for (int g = 0; g < G; ++g)
       x[g] = (NQ * 32 <= KW * CIN || j0 < KW * CIN) ? *reinterpret_cast<const u32x4*>(&in[(32 * g + k) * ST + i0])
@@ -126,6 +136,14 @@ __device__ __forceinline__ void conv_blocks(const uint16_t* __restrict__ in, con
       for (int n = 0; n < 2; ++n) acc[g][n] = mfma16(Wt[q][n], cur[g], acc[g][n]);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// A copy of v that the compiler takes for a new value: what is computed from it
+// (a layer's LDS addresses) is computed there again and not kept in registers
+// over the tiles beside the weights.
+__device__ __forceinline__ uint32_t renew(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
 }
 
 // Calls run(tag<G>, first block) over a wave's nb <= 4 row blocks, at most GM
@@ -147,15 +165,15 @@ __device__ __forceinline__ void for_blocks(uint32_t nb, Run&& run) {
 template <int CIN, int NQ>
 __device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in, const u32x4 (&Wt)[NQ][2],
                                             const float* __restrict__ bias, uint16_t* __restrict__ out, int32_t tb,
-                                            uint32_t K, uint32_t nb, uint32_t rh, uint32_t ch, uint32_t m,
-                                            uint32_t kg) {
-  constexpr int ST = CIN == 64 ? FST : FXS;
+                                            uint32_t K, uint32_t nb, uint32_t rh, uint32_t ch, uint32_t lane) {
+  lane = renew(lane);
+  const uint32_t m = lane & 15u, kg = lane >> 4;
   // layer 0's weights are not kept: two blocks at a time leave them room
   for_blocks<CIN == 64 ? 4 : 2>((nb + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
     constexpr int G = decltype(tag)::value;
     const uint32_t r0 = 32 * b0 + 16 * rh + m;  // blocks rh, rh + 2, ...
     f32x4 acc[G][2];
-    conv_blocks<CIN, NQ, G>(in + r0 * ST, Wt, kg, acc);
+    conv_blocks<CIN, NQ, G>(in + (CIN == 64 ? act_at(r0, kg) : r0 * FXS), Wt, kg, acc);
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       const f32x4 bv = *reinterpret_cast<const f32x4*>(&bias[ch + 16 * n + 4 * kg]);
@@ -165,7 +183,8 @@ __device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in, con
         const bool v = (uint32_t)(tb + (int32_t)r) < K;
         const f32x4 y = acc[g][n] + bv;
         const uint32_t lo = pack_bf(relu(y[0]), relu(y[1])), hi = pack_bf(relu(y[2]), relu(y[3]));
-        *reinterpret_cast<uint2*>(&out[r * FST + ch + 16 * n + 4 * kg]) = v ? make_uint2(lo, hi) : make_uint2(0u, 0u);
+        *reinterpret_cast<uint2*>(&out[act_at(r, ch / 8 + 2 * n + kg / 2) + (kg & 1u) * 4]) =
+            v ? make_uint2(lo, hi) : make_uint2(0u, 0u);
       }
     }
   });
@@ -250,10 +269,12 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
     auto keep = [&](int l, uint32_t off) {
       if constexpr (TRAIN) {
         const uint16_t* in = l == 0 ? sm.x : sm.act[(l + 1) & 1];
-        const uint32_t sh = l == 0 ? 1u : 3u, msk = (1u << sh) - 1u, st = l == 0 ? FXS : FST;
-        for (uint32_t q = tid; q < T << sh; q += NTC)
+        const uint32_t sh = l == 0 ? 1u : 3u, msk = (1u << sh) - 1u;
+        for (uint32_t q = tid; q < T << sh; q += NTC) {
+          const uint32_t r = off + (q >> sh), c = q & msk;
           *reinterpret_cast<u32x4*>(A.keep[l] + (((base + t0) << sh) + q) * 8) =
-              *reinterpret_cast<const u32x4*>(&in[(off + (q >> sh)) * st + (q & msk) * 8]);
+              *reinterpret_cast<const u32x4*>(&in[l == 0 ? r * FXS + c * 8 : act_at(r, c)]);
+        }
       }
     };
     __syncthreads();
@@ -293,30 +314,31 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
           const int j0 = q * 32 + (int)kg * 8;
           W0[q][n] = j0 < 80 ? *reinterpret_cast<const u32x4*>(w0p + (ch + 16 * n + m) * 80 + j0) : u32x4{0u, 0u, 0u, 0u};
         }
-      fused_layer<16, 3>(sm.x, W0, sm.bias, sm.act[0], tb, K, (T + 12 + 15) / 16, rh, ch, m, kg);
+      fused_layer<16, 3>(sm.x, W0, sm.bias, sm.act[0], tb, K, (T + 12 + 15) / 16, rh, ch, lane);
     }
     __syncthreads();
     keep(1, 6);
-    fused_layer<64, 10>(sm.act[0], W1, sm.bias + 64, sm.act[1], tb + 2, K, (T + 8 + 15) / 16, rh, ch, m, kg);
+    fused_layer<64, 10>(sm.act[0], W1, sm.bias + 64, sm.act[1], tb + 2, K, (T + 8 + 15) / 16, rh, ch, lane);
     __syncthreads();
     keep(2, 4);
-    fused_layer<64, 10>(sm.act[1], W2, sm.bias + 128, sm.act[0], tb + 4, K, (T + 4 + 15) / 16, rh, ch, m, kg);
+    fused_layer<64, 10>(sm.act[1], W2, sm.bias + 128, sm.act[0], tb + 4, K, (T + 4 + 15) / 16, rh, ch, lane);
     __syncthreads();
     keep(3, 2);
     // last layer (one output channel, of 16): wave w takes row blocks w and w + 4
     const uint32_t nb = (T + 15) / 16;
     if (w < nb) {
+      const uint32_t ln = renew(lane), m = ln & 15u, kg = ln >> 4;
       const uint16_t* w3row = &sm.w3[m == 0 ? 0 : FW3];
       const bool two = w + 4 < nb;
-      const uint16_t* in = &sm.act[0][(16 * w + m) * FST];
+      const uint16_t* in = &sm.act[0][act_at(16 * w + m, kg)];
       f32x4 acc[2];
       acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int q = 0; q < 10; ++q) {
-        const int at = (q / 2) * FST + (q & 1) * 32 + (int)kg * 8;
+        const int at = (q / 2) * FPS + (q & 1) * 16;
         const u32x4 a = *reinterpret_cast<const u32x4*>(&w3row[q * 32 + kg * 8]);
         acc[0] = mfma16(a, *reinterpret_cast<const u32x4*>(&in[at]), acc[0]);
-        if (two) acc[1] = mfma16(a, *reinterpret_cast<const u32x4*>(&in[at + 64 * FST]), acc[1]);
+        if (two) acc[1] = mfma16(a, *reinterpret_cast<const u32x4*>(&in[at + 64 * FPS]), acc[1]);
       }
       if (kg == 0) {  // channel 0 of row m of each block
         float* dst = A.logits + base;
@@ -340,14 +362,14 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
 // (a3, a2, a1) is 0 and zero outside the series. The LDS buffers hold bf16 rows
 // for the next layer; the fp32 values of the tile's own rows go to memory for
 // the weight and bias gradients. (A launch per layer with element-wise 2-byte
-// loads took 27 + 52 + 51 us on 69632 rows, this one 33.)
+// loads took 27 + 52 + 51 us on 69632 rows, this one 28.)
 //
 // dz row r is series row t0 - 6 + r; dy2, dy1, dy0 row r is t0 - 4 + r, t0 - 2 +
 // r, t0 + r. BT + 8 = 128 rows of dy2 make eight blocks.
 constexpr int BT = 120;
 
 struct BackSmem {
-  uint16_t dy[2][FROWS * FST];
+  uint16_t dy[2][2 * FPL];
   uint16_t dz[FROWS + 4];
   uint16_t w3[64 * 8];    // flipped taps of layer 3: [input channel][tap]
 };
@@ -384,9 +406,23 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
     if (f >= nt) continue;  // block-uniform
     const uint32_t len = (K + nt - 1) / nt, t0 = f * len, T = min(len, K - t0);
     const uint64_t base = (uint64_t)ser * A.SR + 2;
+    // the layer inputs whose zeros mask a lane's products, fetched before the
+    // products are made
+    auto masks = [&](auto gtag, int l, uint2* mk, uint32_t r0, uint32_t kg, uint32_t off) {
+      constexpr int G = decltype(gtag)::value;
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const uint32_t t = t0 + r0 + 32 * g - off;  // wraps below row 0: not < K
+          mk[g * 2 + n] = t < K ? *reinterpret_cast<const uint2*>(A.a[l] + (base + t) * 64 + ch + 16 * n + 4 * kg)
+                                : make_uint2(0u, 0u);
+        }
+    };
     // masks one layer's products and stores them as out rows; the tile's own
     // rows (off .. off + T - 1) also in fp32
-    auto finish = [&](auto gtag, int l, const f32x4* acc, uint32_t r0, uint32_t off, uint16_t* out) {
+    auto finish = [&](auto gtag, int l, const f32x4* acc, const uint2* mks, uint32_t r0, uint32_t kg, uint32_t off,
+                      uint16_t* out) {
       constexpr int G = decltype(gtag)::value;
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
@@ -396,13 +432,15 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
           const uint32_t r = r0 + 32 * g;
           const uint32_t t = t0 + r - off;  // wraps below row 0: not < K
           const bool v = t < K;
-          const uint2 mk = v ? *reinterpret_cast<const uint2*>(A.a[l] + (base + t) * 64 + c) : make_uint2(0u, 0u);
+          const uint2 mk = mks[g * 2 + n];
           f32x4 d = acc[g * 2 + n];
           d[0] = (mk.x & 0xffffu) ? d[0] : 0.0f;
           d[1] = (mk.x >> 16) ? d[1] : 0.0f;
           d[2] = (mk.y & 0xffffu) ? d[2] : 0.0f;
           d[3] = (mk.y >> 16) ? d[3] : 0.0f;
-          *reinterpret_cast<uint2*>(&out[r * FST + c]) = make_uint2(pack_bf(d[0], d[1]), pack_bf(d[2], d[3]));
+          if (l < 2)  // dy0 feeds no further layer
+            *reinterpret_cast<uint2*>(&out[act_at(r, c / 8) + (c & 4u)]) =
+                make_uint2(pack_bf(d[0], d[1]), pack_bf(d[2], d[3]));
           if (v && r >= off && r < off + T) *reinterpret_cast<f32x4*>(A.dy[l] + (base + t) * 64 + c) = d;
         }
       }
@@ -410,10 +448,12 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
     auto layer = [&](int l, const u32x4 (&Wt)[10][2], const uint16_t* in, uint32_t rows, uint32_t off, uint16_t* out) {
       for_blocks<4>(((rows + 15) / 16 + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
         constexpr int G = decltype(tag)::value;
-        const uint32_t r0 = 32 * b0 + 16 * rh + m;
+        const uint32_t ln = renew(lane), kg = ln >> 4, r0 = 32 * b0 + 16 * rh + (ln & 15u);
         f32x4 acc[G][2];
-        conv_blocks<64, 10, G>(in + r0 * FST, Wt, kg, acc);
-        finish(tag, l, &acc[0][0], r0, off, out);
+        uint2 mk[G * 2];
+        masks(tag, l, mk, r0, kg, off);
+        conv_blocks<64, 10, G>(in + act_at(r0, kg), Wt, kg, acc);
+        finish(tag, l, &acc[0][0], mk, r0, kg, off, out);
       });
     };
     __syncthreads();
@@ -426,8 +466,10 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
     // lane groups 0 and 2 (taps 2 q and 2 q + 1) is not 0
     for_blocks<4>(((T + 8 + 15) / 16 + 1 - rh) / 2, [&](auto tag, uint32_t b0) {
       constexpr int G = decltype(tag)::value;
-      const uint32_t r0 = 32 * b0 + 16 * rh + m;
+      const uint32_t ln = renew(lane), m = ln & 15u, kg = ln >> 4, r0 = 32 * b0 + 16 * rh + m;
       f32x4 acc[G][2];
+      uint2 mk[G * 2];
+      masks(tag, 0, mk, r0, kg, 4);
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         const uint32_t k = 2 * q + (kg >> 1);
@@ -442,12 +484,12 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(FWGS, FWGS)
           for (int n = 0; n < 2; ++n) acc[g][n] = mfma16(a[n], x, q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[g][n]);
         }
       }
-      finish(tag, 0, &acc[0][0], r0, 4, sm.dy[0]);
+      finish(tag, 0, &acc[0][0], mk, r0, kg, 4, sm.dy[0]);
     });
     __syncthreads();
     layer(1, W2, sm.dy[0], T + 4, 2, sm.dy[1]);
     __syncthreads();
-    layer(2, W1, sm.dy[1], T, 0, sm.dy[0]);
+    layer(2, W1, sm.dy[1], T, 0, nullptr);
   }
 }
 
