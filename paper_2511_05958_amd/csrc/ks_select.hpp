@@ -1295,10 +1295,11 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 // like register use together, since an empty launch costs 4.5 us (with one per
 // class most were empty): rows of one load batch (five waves per SIMD); the
 // other classes (four); or, for a batch of few series, all of them at once.
-// Workgroups of 256 threads, 512 where rows of two batches are served (eight
-// waves on a series; 1% faster than 256 threads on 8192 x 1024 x 2048).
+// Workgroups of 256 threads (with 512 a wave has half as many rows, and its first
+// one, whose load is not hidden, cost 16.8 M rows of 64 samples 5.59 ms against
+// 5.20); 512 in the few series' launch, for the waves that share a long row.
 constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 4u | 8u, kRowsAll = 15u;
-__host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return mask == kRowsOne ? 256 : 512; }
+__host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return mask == kRowsAll ? 512 : 256; }
 // Waves per SIMD the row-pass kernels are compiled for, the largest without
 // spills.
 __host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : 4; }
@@ -1314,11 +1315,15 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
 // statistics of 8 series of 64 rows of 65537 samples take 41 us (3.3 TB/s) so
 // split, 1440 us with a workgroup per series; of 8 x 256 rows of 1024 samples 12
 // us against 145, of 256 x 512 rows of 256 samples (four waves per CU unsplit) 60
-// us against 246. A launch is cut to about kChunkWGs workgroups in all and no
-// further, since a wave's first row takes two passes and its load is not hidden:
-// four rounds of the resident workgroups for rows of one batch (the feature pass
-// of 1024 x 256 x 1024 takes 229 us in 1.6 rounds, 206 in four), one round for
-// the other classes (512 x 256 rows of 2048 samples: 200 us in one, 227 in four).
+// us against 246. A launch is cut to kChunkWGs workgroups at most, since a wave's
+// first row takes two passes and its load is not hidden: into four rounds of the
+// resident workgroups for rows of one batch (the feature pass of 1024 x 256 x 1024
+// takes 229 us in 1.6 rounds, 206 in four); for the other classes into the number
+// of chunks with the least rounds x (rows of a wave + kChunkFixedRows), so that
+// no last round is nearly empty (statistics of 700 x 300 rows of 1800 samples: 366
+// us in one chunk, 303 in four; 2100 x 64 of 2500: 291 in one, 259 in two) and
+// full rounds are not cut further (512 x 256 of 2048: 181 us in one round, 197 in
+// two).
 // A chunk is not made smaller than a row (or a step of four short rows) per
 // wave, except in batches of at most kCoopRows rows (two waves per SIMD with a
 // wave a row): rows too long for the registers then go a row at a time to all
@@ -1327,15 +1332,29 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
 // a wave a row).
 constexpr uint32_t kRowPassChunks = 256;  // chunks of a series at most
 constexpr uint32_t kCoopRows = 2048;
-__host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 5120u : mask == kRowsAll ? 1024u : 512u; }
-constexpr uint32_t kChunkWGs = 5120;  // the largest of them
+__host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 5120u : mask == kRowsAll ? 1024u : 8192u; }
+constexpr uint32_t kChunkWGs = 8192;  // the largest of them
+constexpr uint32_t kMidResident = 1024;   // four workgroups per CU
+constexpr uint32_t kChunkFixedRows = 3;   // what a wave's start costs, in rows
 __host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, uint32_t mask) {
   const uint32_t least = (uint64_t)num_series * max_K <= kCoopRows ? 1u : (uint32_t)row_pass_threads(mask) / kWave;
-  const uint32_t most = (max_K + least - 1) / least;
+  const uint32_t most = min((max_K + least - 1) / least, kRowPassChunks);
   uint32_t c = chunk_wgs(mask) / num_series;
   c = c < most ? c : most;
-  c = c < kRowPassChunks ? c : kRowPassChunks;
-  return c ? c : 1u;
+  c = c ? c : 1u;
+  if (mask != kRowsMid) return c;
+  uint32_t best = 1;
+  uint64_t cost = ~0ull;
+  for (uint32_t q = 1; q <= c; ++q) {
+    const uint64_t rounds = ((uint64_t)num_series * q + kMidResident - 1) / kMidResident;
+    const uint32_t rows = (max_K + q - 1) / q;
+    const uint64_t t = rounds * ((rows + least - 1) / least + kChunkFixedRows);
+    if (t < cost) {
+      cost = t;
+      best = q;
+    }
+  }
+  return best;
 }
 
 // Rows of chunk c of a K-row series of row class NB in a workgroup of W waves,

@@ -1,8 +1,7 @@
 // Per-row latency statistics (ks_stats_batch): the average as the main result,
 // with p50, p95, standard deviation, minimum and maximum beside it, for every
-// row of every series in one read of the samples. One wave per row, the row
-// in registers; the two percentiles come from the same multi-rank radix
-// select as the learned path's deciles.
+// row of every series in one read of the samples: the row pass of the learned
+// path's deciles with two other ranks.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
