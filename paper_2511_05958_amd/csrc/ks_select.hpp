@@ -1300,8 +1300,8 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 // 5.20); 512 in the few series' launch, for the waves that share a long row.
 constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 4u | 8u, kRowsAll = 15u;
 __host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return mask == kRowsAll ? 512 : 256; }
-// Waves per SIMD the row-pass kernels are compiled for, the largest without
-// spills.
+// Waves per SIMD the row-pass kernels are compiled for, the largest that spill
+// no more than one register (the feature pass' kernels of several classes).
 __host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : 4; }
 __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
   return N <= kGroupMaxN ? kGrouped
