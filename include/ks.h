@@ -161,11 +161,12 @@ int ks_reserve(ks_ctx *ctx, uint32_t max_series, uint64_t max_total_steps);
  *
  * Launch plan (ks_launch_set / ks_autotune; default KS_LAUNCH_ORDERED): an
  * on-device planning kernel orders the series largest first, then either one
- * workgroup per series in that order (a batch of few series is instead split
- * over the device by rows and candidates and launched directly), or a persistent kernel drains the
+ * workgroup per series in that order, or a persistent kernel drains the
  * ordered items (large series split into row ranges whose moments meet in
- * the workspace) followed by a finish kernel. Planned launches are replayed
- * from a hipGraph cached per (mode, max_K class, grid) with updated
+ * the workspace) followed by a finish kernel. Without a recorded plan the
+ * kernels are launched directly, and a batch of few series is instead split
+ * over the device by rows and candidates. Recorded plans with graph = 1 are
+ * replayed from a hipGraph cached per (mode, max_K class, grid) with updated
  * arguments. The workspace grows on demand (that growth synchronizes the
  * device); ks_reserve avoids it. */
 int ks_scan_batch(ks_ctx *ctx, const uint32_t *samples, uint64_t num_samples, const ks_desc *desc,
@@ -200,17 +201,17 @@ typedef struct ks_launch {
 
 /* Record (ks_launch_set) or read (ks_launch_get) the plan ks_scan_batch uses
  * for batches with this max_K class and num_series; without a record the
- * default is {KS_LAUNCH_ORDERED, 1 MiB, 1, 0}, of which the library replaces the
- * kernel variant and the graph by what is fastest for the batch's sizes.
- * KS_E_INVALID / KS_E_RANGE on
- * bad values. */
+ * default is {KS_LAUNCH_ORDERED, 1 MiB, 1, 0}. The default, recorded or not,
+ * leaves the kernels of the ordered plan, their variant and the graph to the
+ * library, by the batch's sizes; any other record is run as it says.
+ * KS_E_INVALID / KS_E_RANGE on bad values. */
 int ks_launch_set(ks_ctx *ctx, uint32_t max_K, uint32_t num_series, const ks_launch *cfg);
 int ks_launch_get(ks_ctx *ctx, uint32_t max_K, uint32_t num_series, ks_launch *cfg);
 
 /* Autotuner, on this very batch with HIP events on `stream` (one warm-up,
  * best of three per candidate): every scan-kernel variant (tile, sort radix,
- * walk window) under every launch plan (grid; ordered grid from a hipGraph and
- * direct; persistent with chunk_bytes 1, 4, 16 MiB, from a hipGraph and
+ * walk window) under every launch plan (grid; ordered grid from a hipGraph,
+ * variant 0 of which is the default plan, and direct; persistent with chunk_bytes 1, 4, 16 MiB, from a hipGraph and
  * direct), 6 x 9 candidates. Records the fastest
  * with ks_launch_set and returns it in *best (nullable) and its time in
  * *best_ms (nullable). Blocks until done; writes `out`. When the environment

@@ -291,30 +291,43 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
   return e == hipSuccess ? KS_OK : hip_fail(e, "split scan launch");
 }
 
-LaunchCfg config_for(const ks_ctx* c, int kc, uint32_t num_series, uint32_t opts) {
-  LaunchCfg cfg;
-  auto it = c->tuned.find(std::make_tuple(kc, num_series));
-  if (it != c->tuned.end()) cfg = it->second;
-  if (opts & KS_OPT_GRID) cfg.mode = KS_LAUNCH_GRID;
-  if (opts & KS_OPT_PERSISTENT) cfg.mode = KS_LAUNCH_PERSISTENT;
-  if (opts & KS_OPT_NO_GRAPH) cfg.graph = 0;
-  return cfg;
+// {KS_LAUNCH_ORDERED, 1 MiB, 1, 0}, recorded or not, is the default plan: the
+// library chooses (default_cfg). Every other record is run as it says.
+bool is_default(const LaunchCfg& c) {
+  return c.mode == KS_LAUNCH_ORDERED && c.chunk_bytes == 1u << 20 && c.graph == 1 && c.variant == 0;
 }
 
-// What a batch without a recorded plan runs under the ordered plan: the kernel
-// variant by size, and a direct launch (a graph's update costs more on the host
-// than the second kernel's launch: 1024 series of 64 x 64 34 us a call from a
-// graph, 25 direct). Variant 2, eight waves per series instead of four, for K
+LaunchCfg recorded(const ks_ctx* c, int kc, uint32_t num_series) {
+  const auto it = c->tuned.find(std::make_tuple(kc, num_series));
+  return it != c->tuned.end() ? it->second : LaunchCfg{};
+}
+
+// What a batch runs under the default plan: the scan of few series, or the ordered
+// grid with the kernel variant by size and a direct launch (a graph's update costs
+// more on the host than the second kernel's launch: 1024 series of 64 x 64 34 us a
+// call from a graph, 25 direct). Variant 2, eight waves per series instead of four, for K
 // classes of 1024 and 2048 rows, whose LDS allows as many workgroups either way
 // (1024 series of 2048 x 64 1698 us with four, 1050 with eight; 4096 of 1024 x
 // 256 1731 and 1575), and for 512-row classes with series of more than 640 KB on
 // average, where the largest ones' stream decides (8192 uneven ones up to 512 x
 // 4096 1056 and 997; below, its barriers cost: 8192 of 512 x 256 1022 and 1130).
 // Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671.
-LaunchCfg default_cfg(int kc, uint64_t num_samples, uint32_t num_series) {
+LaunchCfg default_cfg(int kc, const ScanArgs& a) {
   LaunchCfg cfg;
   cfg.graph = 0;
-  if (kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && num_samples / num_series > (160u << 10))) cfg.variant = 2;
+  cfg.spread = a.num_series <= kSplitMaxSeries || tiny_batch(kc, a);
+  if (kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && a.num_samples / a.num_series > (160u << 10))) cfg.variant = 2;
+  return cfg;
+}
+
+// The plan of a call: the record of its shape, with the modes and the graph that
+// its options override.
+LaunchCfg config_for(const ks_ctx* c, int kc, const ScanArgs& a, uint32_t opts) {
+  LaunchCfg cfg = recorded(c, kc, a.num_series);
+  if (opts & KS_OPT_GRID) cfg.mode = KS_LAUNCH_GRID;
+  if (opts & KS_OPT_PERSISTENT) cfg.mode = KS_LAUNCH_PERSISTENT;
+  if (is_default(cfg) && !opts) cfg = default_cfg(kc, a);
+  if (opts & KS_OPT_NO_GRAPH) cfg.graph = 0;
   return cfg;
 }
 
@@ -323,7 +336,7 @@ int scan_with(ks_ctx* ctx, const ScanArgs& a, int kc, const LaunchCfg& cfg, hipS
     hipError_t e = launch_grid(kc, cfg.variant, a, st);
     return e == hipSuccess ? KS_OK : hip_fail(e, "scan launch");
   }
-  if (cfg.mode == KS_LAUNCH_ORDERED && (a.num_series <= kSplitMaxSeries || tiny_batch(kc, a))) return launch_split(ctx, kc, a, st);
+  if (cfg.spread) return launch_split(ctx, kc, a, st);
   const bool split = cfg.mode == KS_LAUNCH_PERSISTENT;
   if (int rc = ensure_workspace(ctx, a.num_series, split ? (uint64_t)a.num_series * a.max_K : 0)) return rc;
   ScanArgs b = a;
@@ -471,10 +484,7 @@ int ks_scan_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, co
   const uint32_t max_K = params->max_K ? params->max_K : KS_MAX_K;
   const int kc = k_class(max_K);
   ScanArgs a{samples, num_samples, desc, num_series, *params, max_K, out, all_U, all_U_len, 0, {}};
-  const bool recorded = ctx->tuned.count(std::make_tuple(kc, num_series)) != 0;
-  const LaunchCfg cfg = recorded || params->opts ? config_for(ctx, kc, num_series, params->opts)
-                                                 : default_cfg(kc, num_samples, num_series);
-  return scan_with(ctx, a, kc, cfg, (hipStream_t)stream);
+  return scan_with(ctx, a, kc, config_for(ctx, kc, a, params->opts), (hipStream_t)stream);
 }
 
 int ks_launch_set(ks_ctx* ctx, uint32_t max_K, uint32_t num_series, const ks_launch* cfg) {
@@ -486,7 +496,7 @@ int ks_launch_set(ks_ctx* ctx, uint32_t max_K, uint32_t num_series, const ks_lau
 
 int ks_launch_get(ks_ctx* ctx, uint32_t max_K, uint32_t num_series, ks_launch* cfg) {
   if (!ctx || !cfg) return KS_E_INVALID;
-  *cfg = to_launch(config_for(ctx, k_class(max_K ? max_K : KS_MAX_K), num_series, 0));
+  *cfg = to_launch(recorded(ctx, k_class(max_K ? max_K : KS_MAX_K), num_series));
   return KS_OK;
 }
 
@@ -526,8 +536,8 @@ int ks_autotune(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
     return rc;
   };
   // every scan-kernel variant (tile, sort radix, walk window) under every
-  // launch plan: the plain grid, the ordered grid from a hipGraph and direct,
-  // the persistent queue with 1 / 4 / 16 MiB splits from a hipGraph and direct
+  // launch plan: the plain grid, the ordered grid from a hipGraph (variant 0: the
+  // default plan) and direct, the persistent queue with 1 / 4 / 16 MiB splits from a hipGraph and direct
   // (the variants rank differently under different plans)
   int rc = KS_OK;
   LaunchCfg bcfg;
@@ -545,7 +555,7 @@ int ks_autotune(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
     }
     for (int i = 0; i < np && rc == KS_OK; ++i) {
       float t = 0.f;
-      rc = time_cfg(plans[i], t);
+      rc = time_cfg(is_default(plans[i]) ? default_cfg(kc, a) : plans[i], t);
       if (rc == KS_OK && (!have || t < bms)) {
         bcfg = plans[i];
         bms = t;
@@ -583,10 +593,7 @@ int ks_scan_batch_noalloc(ks_ctx* ctx, const uint32_t* samples, uint64_t num_sam
                    reinterpret_cast<uint64_t*>(base + kScratchBase), reinterpret_cast<uint32_t*>(base + kScratchDone),
                    reinterpret_cast<uint32_t*>(base + kScratchMin), nullptr};
   ScanArgs a{samples, num_samples, desc, num_series, *params, max_K, out, all_U, all_U_len, ks::kNoSplit, ws};
-  // the tuned kernel variant (a table lookup), else the one for these sizes
-  const auto it = ctx->tuned.find(std::make_tuple(kc, num_series));
-  const int v = it != ctx->tuned.end() ? it->second.variant : default_cfg(kc, num_samples, num_series).variant;
-  return launch_plan(ctx, kc, v, KS_LAUNCH_ORDERED, a, false, (hipStream_t)stream);
+  return launch_plan(ctx, kc, config_for(ctx, kc, a, 0).variant, KS_LAUNCH_ORDERED, a, false, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -61,6 +61,7 @@ struct LaunchCfg {
   uint32_t chunk_bytes = 1u << 20;
   int graph = 1;                 // planned launches replayed from a hipGraph
   int variant = 0;               // kVariants index
+  bool spread = false;           // the scan of few series (the default plan's choice only)
 };
 
 struct GraphEntry {
