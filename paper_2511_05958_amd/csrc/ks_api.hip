@@ -82,16 +82,17 @@ unsigned char* scratch_of(int device) {
   return g_scratch[device];
 }
 
-// Batches of few series under the ordered plan (ks_split.hpp). The spread scan
-// serves up to 384 series (one and a half per CU) of 64 to 2048 rows: there it
-// is ahead at every size measured (256 series of 1024 x 1024: 363 us, 492 with a
-// workgroup per series; 384 of 256 x 1024: 111 against 129, 384 of 1024 x 64: 297
-// against 282), at 512 it is behind for most (512 of 1024 x 64: 393 against
-// 284), since each of its workgroups makes its series' keys again. The
+// Batches of few series under the default plan (ks_split.hpp). The spread scan
+// serves up to 384 series (one and a half per CU) of any K: there it is ahead of a
+// workgroup per series of variant 0 throughout (384 of 1024 x 64: 249 us against
+// 272, of 1024 x 1024 468 against 530, of 64 x 4 under max_K 0 18 against 23) and
+// ahead of variant 2's by far where series are uneven (384 up to 2048 x 4096: 734
+// against 1332), behind it by up to a third for equal ones of 1024 rows and more
+// (256 of 2048 x 64: 565 against 440); past 384 equal ones are behind by more. The
 // one-launch scan serves up to 1024 series of at most 256 rows and (on average)
-// 256 KB: 1024 of 64 x 256 take 24 us against 37, 2048 of 256 x 64 111 against
-// 109; a series of more than 256 KB keeps its one workgroup busy for longer than
-// the spread scan's two more launches take.
+// 256 KB: 1024 of 64 x 256 take 27 us against 29, 512 of 256 x 64 34 against 57; a
+// series of more than 256 KB keeps its one workgroup busy for longer than the
+// spread scan's two more launches take.
 constexpr uint32_t kSplitMaxSeries = 384;
 constexpr uint32_t kTinyMaxSeries = 1024;
 constexpr int kTinyMaxClass = 2;                 // K <= 256
@@ -281,11 +282,10 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
     if (int rc = ensure_workspace(c, a.num_series, 0)) return rc;
     const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
     ks::launch_split_moments(a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
-    hipLaunchKernelGGL(ks::split_rank_kernel, dim3((a.max_K + ks::kWave - 1) / ks::kWave, a.num_series),
-                       dim3(ks::kSplitNT), 0, st, a.num_samples, a.desc, a.max_K, ws);
-    hipLaunchKernelGGL(ks::split_walk_kernel, dim3((a.max_K - 1 + ks::kWave - 1) / ks::kWave, a.num_series),
-                       dim3(ks::kSplitWalkNT), 0, st, a.num_samples, a.desc, a.max_K, a.prm, a.out, a.allU,
-                       a.allU_len, ws);
+    hipLaunchKernelGGL(ks::split_rank_kernel, ks::split_grid(a.num_series, a.max_K), dim3(ks::kSplitNT), 0, st,
+                       a.num_samples, a.desc, a.num_series, a.max_K, ws);
+    hipLaunchKernelGGL(ks::split_walk_kernel, ks::split_grid(a.num_series, a.max_K - 1), dim3(ks::kSplitWalkNT), 0, st,
+                       a.num_samples, a.desc, a.num_series, a.max_K, a.prm, a.out, a.allU, a.allU_len, ws);
   }
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "split scan launch");

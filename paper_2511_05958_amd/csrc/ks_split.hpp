@@ -48,6 +48,32 @@ struct SplitWs {
   uint32_t* ticket;  // per series: finished slots
 };
 
+// Series and slot (or chunk) of the calling workgroup. Workgroups go to the eight
+// XCDs in turn, and there to the four shader engines: series after series, with 32
+// slots each, every series' first slots met on one engine of one XCD, and where K
+// is far below max_K only those have work (under max_K 0 256 series of 64 x 64 took
+// 44 us a call, of 512 x 4 167; 20 and 100 now). So where C, the slots of a series,
+// has a power of two g in common with these 32 places, the slots of each g are
+// exchanged by the series. With more than 32 series per XCD, whose sizes even out,
+// the rank and the walk go slot after slot instead, all slots of a series on one
+// XCD, whose L2 keeps its keys (384 series of 1024 x 64: 302 us exchanged, 249 so;
+// 160 uneven ones up to 2048 x 4096: 283 exchanged, 352 so).
+constexpr uint32_t kXcds = 8, kPlacesLog = 5, kTurnedSeries = 32 * kXcds;
+struct SplitAt {
+  uint32_t s, slot;
+};
+__device__ __forceinline__ SplitAt turned_at(uint32_t C) {
+  const uint32_t l = min((uint32_t)__builtin_ctz(C), kPlacesLog);  // g = 1 << l
+  return SplitAt{blockIdx.y, blockIdx.x ^ ((blockIdx.y >> (kPlacesLog - l)) & ((1u << l) - 1u))};
+}
+__device__ __forceinline__ SplitAt split_at(uint32_t num_series, uint32_t rows) {
+  return num_series > kTurnedSeries ? SplitAt{blockIdx.x, blockIdx.y} : turned_at((rows + kWave - 1) / kWave);
+}
+inline dim3 split_grid(uint32_t num_series, uint32_t rows) {
+  const uint32_t slots = (rows + kWave - 1) / kWave;
+  return num_series > kTurnedSeries ? dim3((num_series + kXcds - 1) / kXcds * kXcds, slots) : dim3(slots, num_series);
+}
+
 __device__ __forceinline__ SortKey sort_key(uint64_t s1, uint64_t s2lo, uint32_t s2hi, uint32_t i, uint32_t N,
                                             uint32_t gmin) {
   const u128 s2 = ((u128)s2hi << 64) | s2lo;
@@ -90,7 +116,9 @@ __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t*
   constexpr uint32_t W = kSplitNT / kWave;
   __shared__ uint64_t p1[W], p2[W];
   __shared__ uint32_t p2h[W], pm[W];
-  const uint32_t s = blockIdx.y, c = blockIdx.x, C = gridDim.x;
+  const uint32_t C = gridDim.x;
+  const SplitAt at = turned_at(C);
+  const uint32_t s = at.s, c = at.slot;
   const ks_desc d = desc[s];
   const uint32_t bad = check_desc(d, num_samples, max_K);
   if (bad) {
@@ -166,11 +194,13 @@ inline void launch_split_moments(const uint32_t* samples, uint64_t num_samples, 
 }
 
 __global__ __launch_bounds__(kSplitNT) void split_rank_kernel(uint64_t num_samples, const ks_desc* __restrict__ desc,
-                                                              uint32_t max_K, SplitWs ws) {
+                                                              uint32_t num_series, uint32_t max_K, SplitWs ws) {
   constexpr uint32_t W = kSplitNT / kWave;
   __shared__ uint64_t lo[KS_MAX_K], hi[KS_MAX_K];
   __shared__ uint32_t part[W * kWave], red[W];
-  const uint32_t s = blockIdx.y, r0 = blockIdx.x * kWave;
+  const SplitAt at = split_at(num_series, max_K);
+  const uint32_t s = at.s, r0 = at.slot * kWave;
+  if (s >= num_series) return;
   const ks_desc d = desc[s];
   if (check_desc(d, num_samples, max_K) || r0 >= d.K) return;
   const uint32_t K = d.K, N = d.N, tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -207,7 +237,7 @@ __device__ __forceinline__ bool group_end(const SortKey& a, const SortKey& b) {
 }
 
 __global__ __launch_bounds__(kSplitWalkNT) void split_walk_kernel(uint64_t num_samples, const ks_desc* __restrict__ desc,
-                                                                  uint32_t max_K, ks_params prm,
+                                                                  uint32_t num_series, uint32_t max_K, ks_params prm,
                                                                   ks_result* __restrict__ out,
                                                                   uint32_t* __restrict__ allU, uint64_t allU_len,
                                                                   SplitWs ws) {
@@ -216,7 +246,9 @@ __global__ __launch_bounds__(kSplitWalkNT) void split_walk_kernel(uint64_t num_s
   __shared__ uint16_t pos[KS_MAX_K];
   __shared__ uint64_t tie[kSplitSlots];
   __shared__ uint32_t partU[W * kWave], red[W];
-  const uint32_t s = blockIdx.y, slot = blockIdx.x;
+  const SplitAt at = split_at(num_series, max_K - 1);
+  const uint32_t s = at.s, slot = at.slot;
+  if (s >= num_series) return;
   const ks_desc d = desc[s];
   const uint32_t K = d.K, tid = threadIdx.x, lane = lane_id(), w = wave_id();
   if (check_desc(d, num_samples, max_K) || 1u + slot * kWave > K - 1u) return;
