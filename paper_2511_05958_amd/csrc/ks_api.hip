@@ -326,7 +326,7 @@ LaunchCfg config_for(const ks_ctx* c, int kc, const ScanArgs& a, uint32_t opts) 
   LaunchCfg cfg = recorded(c, kc, a.num_series);
   if (opts & KS_OPT_GRID) cfg.mode = KS_LAUNCH_GRID;
   if (opts & KS_OPT_PERSISTENT) cfg.mode = KS_LAUNCH_PERSISTENT;
-  if (is_default(cfg) && !opts) cfg = default_cfg(kc, a);
+  if (is_default(cfg)) cfg = default_cfg(kc, a);
   if (opts & KS_OPT_NO_GRAPH) cfg.graph = 0;
   return cfg;
 }

@@ -115,3 +115,11 @@ def test_ordered_graph_of_few_series_with_new_buffers(ctx, chunk, variant):
         g, gU = run_gpu(ctx, x, d, max_K=512, launch=(P.KS_LAUNCH_ORDERED, chunk, 1), variant=variant)
         o, oU, _ = oracle_batch(x, d)
         assert_parity(g, gU, o, oU, d)
+
+
+@pytest.mark.parametrize("num,K,N", [(1, 64, 64), (53, 2048, 5), (1100, 1024, 4), (600, 300, 700)])
+def test_no_graph_option_changes_no_kernel(ctx, num, K, N):
+    """KS_OPT_NO_GRAPH replaces the graph of the plan, the default's kernels stay."""
+    assert Batch(num, K, N, opts=P.KS_OPT_NO_GRAPH).kernels(ctx) == Batch(num, K, N).kernels(ctx)
+    P.ks_launch_set(ctx.handle, K, num, P.KS_LAUNCH_ORDERED, 1 << 20, 1, variant=1)
+    assert Batch(num, K, N, opts=P.KS_OPT_NO_GRAPH).kernels(ctx) == ordered(num, 1)
