@@ -105,14 +105,6 @@ void free_workspace(ks_ctx* c) {
   (void)hipFree(c->done);
   (void)hipFree(c->smin);
   (void)hipFree(c->mom);
-  (void)hipFree(c->split_mom);
-  (void)hipFree(c->split_sorted);
-  (void)hipFree(c->split_best);
-  (void)hipFree(c->split_ticket);
-  c->split_mom = nullptr;
-  c->split_sorted = nullptr;
-  c->split_best = nullptr;
-  c->split_ticket = nullptr;
   c->hdr = nullptr;
   c->items = nullptr;
   c->mom_base = nullptr;
@@ -122,24 +114,61 @@ void free_workspace(ks_ctx* c) {
   c->cap_series = c->cap_rows = 0;
 }
 
+void free_split(ks_ctx* c) {
+  (void)hipFree(c->split_mom);
+  (void)hipFree(c->split_sorted);
+  (void)hipFree(c->split_best);
+  (void)hipFree(c->split_ticket);
+  c->split_mom = nullptr;
+  c->split_sorted = nullptr;
+  c->split_best = nullptr;
+  c->split_ticket = nullptr;
+  c->cap_split_series = c->cap_split_rows = 0;
+}
+
+// Grow the spread scan's workspace to num_series series of max_K rows, 40 B each.
+// KS_E_NOMEM also where `st` is being captured and the workspace would have to
+// grow: the caller runs the ordered grid then.
+int ensure_split(ks_ctx* c, uint64_t num_series, uint64_t max_K, hipStream_t st) {
+  uint64_t ns = num_series, rows = num_series * max_K;
+  if (ns <= c->cap_split_series && rows <= c->cap_split_rows) return KS_OK;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return KS_E_NOMEM;
+  }
+  if (ns < c->cap_split_series) ns = c->cap_split_series;
+  if (rows < c->cap_split_rows) rows = c->cap_split_rows;
+  hipError_t e = hipDeviceSynchronize();
+  if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
+  free_split(c);
+  if (hipMalloc(&c->split_mom, sizeof(ks::RowMom) * rows) != hipSuccess ||
+      hipMalloc(&c->split_sorted, sizeof(ks::SortKey) * rows) != hipSuccess ||
+      hipMalloc(&c->split_best, sizeof(uint32_t) * 2 * ns * ks::kSplitSlots) != hipSuccess ||
+      hipMalloc(&c->split_ticket, sizeof(uint32_t) * ns) != hipSuccess) {
+    free_split(c);
+    (void)hipGetLastError();
+    return KS_E_NOMEM;
+  }
+  c->cap_split_series = ns;
+  c->cap_split_rows = rows;
+  return KS_OK;
+}
+
+}  // namespace
+
 // Grow the workspace to hold num_series series and rows split-series rows.
-int ensure_workspace(ks_ctx* c, uint64_t num_series, uint64_t rows) {
+int ks_host::ensure_workspace(ks_ctx* c, uint64_t num_series, uint64_t rows) {
   if (num_series <= c->cap_series && rows <= c->cap_rows && c->hdr) return KS_OK;
   const uint64_t ns = num_series > c->cap_series ? num_series : c->cap_series;
   const uint64_t nr = rows > c->cap_rows ? rows : c->cap_rows;
-  // the split scan's share: batches of up to kSplitMaxSeries series of any K
-  const uint64_t nsp = ns < kSplitMaxSeries ? (ns ? ns : 1) : kSplitMaxSeries;
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_workspace(c);
   if (hipMalloc(&c->hdr, 256) != hipSuccess || hipMalloc(&c->items, sizeof(ks::Item) * ks::kMaxChunks * ns) != hipSuccess ||
       hipMalloc(&c->mom_base, sizeof(uint64_t) * ns) != hipSuccess || hipMalloc(&c->done, sizeof(uint32_t) * ns) != hipSuccess ||
       hipMalloc(&c->smin, sizeof(uint32_t) * ns) != hipSuccess ||
-      hipMalloc(&c->mom, sizeof(ks::RowMom) * (nr ? nr : 1)) != hipSuccess ||
-      hipMalloc(&c->split_mom, sizeof(ks::RowMom) * nsp * KS_MAX_K) != hipSuccess ||
-      hipMalloc(&c->split_sorted, sizeof(ks::SortKey) * nsp * KS_MAX_K) != hipSuccess ||
-      hipMalloc(&c->split_best, sizeof(uint32_t) * 2 * nsp * ks::kSplitSlots) != hipSuccess ||
-      hipMalloc(&c->split_ticket, sizeof(uint32_t) * nsp) != hipSuccess) {
+      hipMalloc(&c->mom, sizeof(ks::RowMom) * (nr ? nr : 1)) != hipSuccess) {
     free_workspace(c);
     (void)hipGetLastError();
     return KS_E_NOMEM;
@@ -148,6 +177,8 @@ int ensure_workspace(ks_ctx* c, uint64_t num_series, uint64_t rows) {
   c->cap_rows = nr;
   return KS_OK;
 }
+
+namespace {
 
 ks::Workspace workspace_of(const ks_ctx* c) {
   return ks::Workspace{c->hdr, c->items, c->mom_base, c->done, c->smin, c->mom};
@@ -264,7 +295,8 @@ bool tiny_batch(int kc, const ScanArgs& a) {
   return kc <= kTinyMaxClass && a.num_series <= kTinyMaxSeries && a.num_samples / a.num_series <= kTinyMaxSamples;
 }
 
-// The scan of a batch of few series. Launched directly: replaying one or three
+// The scan of a batch of few series (KS_E_NOMEM, nothing launched, where its
+// workspace cannot grow). Launched directly: replaying one or three
 // kernels from a graph costs more on the host (27 us a call for one sweep,
 // against 8).
 int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
@@ -279,7 +311,7 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
       default: run(ks::tiny_scan_kernel<256>);
     }
   } else {
-    if (int rc = ensure_workspace(c, a.num_series, 0)) return rc;
+    if (int rc = ensure_split(c, a.num_series, a.max_K, st)) return rc;
     const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
     ks::launch_split_moments(a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
     hipLaunchKernelGGL(ks::split_rank_kernel, ks::split_grid(a.num_series, a.max_K), dim3(ks::kSplitNT), 0, st,
@@ -336,7 +368,10 @@ int scan_with(ks_ctx* ctx, const ScanArgs& a, int kc, const LaunchCfg& cfg, hipS
     hipError_t e = launch_grid(kc, cfg.variant, a, st);
     return e == hipSuccess ? KS_OK : hip_fail(e, "scan launch");
   }
-  if (cfg.spread) return launch_split(ctx, kc, a, st);
+  if (cfg.spread) {
+    const int rc = launch_split(ctx, kc, a, st);
+    if (rc != KS_E_NOMEM) return rc;
+  }
   const bool split = cfg.mode == KS_LAUNCH_PERSISTENT;
   if (int rc = ensure_workspace(ctx, a.num_series, split ? (uint64_t)a.num_series * a.max_K : 0)) return rc;
   ScanArgs b = a;
@@ -457,6 +492,7 @@ int ks_ctx_destroy(ks_ctx* ctx) {
       (void)hipGraphDestroy(kv.second.graph);
     }
     free_workspace(ctx);
+    free_split(ctx);
     free_learn(ctx->learn);
     free_seg(ctx->seg);
   }
@@ -468,7 +504,11 @@ int ks_reserve(ks_ctx* ctx, uint32_t max_series, uint64_t max_total_steps) {
   if (!ctx) return KS_E_INVALID;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  return ensure_workspace(ctx, max_series, max_total_steps);
+  if (int rc = ensure_workspace(ctx, max_series, max_total_steps)) return rc;
+  // and the scan of few series, which does without where the device is full
+  const uint32_t few = max_series < kSplitMaxSeries ? max_series : kSplitMaxSeries;
+  const int rc = few ? ensure_split(ctx, few, KS_MAX_K, nullptr) : KS_OK;
+  return rc == KS_E_NOMEM ? KS_OK : rc;
 }
 
 int ks_scan_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,

@@ -163,7 +163,7 @@ extern "C" int ks_stats_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num
   } else {
     // the series order per row class (the feature pass's plan), kept in the
     // context's scan workspace (its queue items: 512 bytes per series)
-    if (int rc = ks_reserve(ctx, num_series, 0)) return rc;
+    if (int rc = ensure_workspace(ctx, num_series, 0)) return rc;
     uint32_t* plan = reinterpret_cast<uint32_t*>(ctx->items);
     hipLaunchKernelGGL(ks::feature_plan_kernel, dim3(1), dim3(ks::kFeatPlanNT), 0, st, desc, num_series, num_samples,
                        max_K, plan);
