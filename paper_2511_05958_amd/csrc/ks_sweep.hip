@@ -179,27 +179,10 @@ __global__ __launch_bounds__(256) void align_kernel(const uint64_t* __restrict__
   distance[i] = (double)bnum / (double)T;   // bnum < 2^52: exact
 }
 
-// One workgroup per experiment: lanes over the array sizes (a = lane + 64 t),
-// each wave every fourth stride (a wave taking 16 strides in turn, a 64-bit
-// division each, took 16 us on 256 experiments); the scores meet in LDS for
-// one thread.
-__global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ desc, uint32_t num_exp,
-                                                   const ks_row_stats* __restrict__ stats, uint64_t stats_rows,
-                                                   uint32_t J, const uint32_t* __restrict__ strides,
-                                                   ks_line* __restrict__ out) {
-  __shared__ uint64_t score[kLineMaxJ];
-  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
-  const uint32_t e = blockIdx.x;
-  if (e >= num_exp) return;
-  const ks_desc d = desc[e];
-  const uint32_t K = d.K, A = K / J;
-  const bool bad = A < 1 || A > kLineMaxA || A * J != K || d.aux_offset > stats_rows ||
-                   (uint64_t)K > stats_rows - d.aux_offset;
-  if (bad) {
-    if (threadIdx.x == 0) out[e] = ks_line{0u, 0u, KS_LINE_INVALID, 0u, 0.0};
-    return;
-  }
-  const ks_row_stats* x = stats + d.aux_offset;
+// The scores of one experiment's strides w, w + step, ... by the calling wave,
+// lanes over the array sizes (a = lane + 64 t).
+__device__ __forceinline__ void line_scores(const ks_row_stats* __restrict__ x, uint32_t A, uint32_t J, uint32_t w,
+                                            uint32_t step, uint32_t lane, uint64_t* score) {
   constexpr int T = kLineMaxA / ks::kWave;
   uint32_t P[T], M[T];
 #pragma unroll
@@ -208,7 +191,7 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
     P[t] = a < A ? x[a].p50 : 0u;
     M[t] = a < A ? x[(uint64_t)(J - 1) * A + a].p50 : 0u;
   }
-  for (uint32_t j = w; j < J; j += 4) {
+  for (uint32_t j = w; j < J; j += step) {
     uint64_t acc = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -225,8 +208,11 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
     ks::wave_total_32_64(unused, acc);
     if (lane == 0) score[j] = acc;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
+}
+
+// The record of one experiment from its scores (one thread).
+__device__ __forceinline__ ks_line line_record(const uint64_t* score, uint32_t A, uint32_t J,
+                                               const uint32_t* __restrict__ strides) {
   const uint64_t W = (uint64_t)A * (A + 1) / 2;
   const uint64_t half = W << 31;
   uint32_t jstar = J;
@@ -260,12 +246,38 @@ __global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ d
     ++ncand;
   }
   uint32_t flags = jstar < J ? 0u : KS_LINE_NO_MAX_LIKE;
-  if (ncand < 2) {
-    out[e] = ks_line{0u, jstar, flags | KS_LINE_INCONCLUSIVE, 0u, 0.0};
+  if (ncand < 2) return ks_line{0u, jstar, flags | KS_LINE_INCONCLUSIVE, 0u, 0.0};
+  if (best <= 0) flags |= KS_LINE_NO_INCREASE;
+  return ks_line{best_line, jstar, flags, 0u, (double)best / (double)(W << 32)};
+}
+
+// E experiments to a workgroup of four waves. E = 1: the waves share the strides
+// (a wave taking 16 strides in turn, a 64-bit division each, took 16 us on 256
+// experiments). E = 4, for thousands of experiments: a wave each, with nothing
+// read or started four times (60000 of 2 x 64 43 us, 69 with E = 1).
+template <uint32_t E>
+__global__ __launch_bounds__(256) void line_kernel(const ks_desc* __restrict__ desc, uint32_t num_exp,
+                                                   const ks_row_stats* __restrict__ stats, uint64_t stats_rows,
+                                                   uint32_t J, const uint32_t* __restrict__ strides,
+                                                   ks_line* __restrict__ out) {
+  __shared__ uint64_t scores[E][kLineMaxJ];
+  const uint32_t lane = ks::lane_id(), w = ks::wave_id();
+  const uint32_t e = E == 1 ? blockIdx.x : blockIdx.x * E + w;
+  const bool first = E == 1 ? threadIdx.x == 0 : lane == 0;
+  uint64_t* score = scores[E == 1 ? 0 : w];
+  if (e >= num_exp) return;
+  const ks_desc d = desc[e];
+  const uint32_t K = d.K, A = K / J;
+  const bool bad = A < 1 || A > kLineMaxA || A * J != K || d.aux_offset > stats_rows ||
+                   (uint64_t)K > stats_rows - d.aux_offset;
+  if (bad) {
+    if (first) out[e] = ks_line{0u, 0u, KS_LINE_INVALID, 0u, 0.0};
     return;
   }
-  if (best <= 0) flags |= KS_LINE_NO_INCREASE;
-  out[e] = ks_line{best_line, jstar, flags, 0u, (double)best / (double)(W << 32)};
+  line_scores(stats + d.aux_offset, A, J, E == 1 ? w : 0u, E == 1 ? 4u : 1u, lane, score);
+  if constexpr (E == 1) ks::block_publish();
+  else ks::wave_lds_sync();
+  if (first) out[e] = line_record(score, A, J, strides);
 }
 
 }  // namespace
@@ -311,8 +323,18 @@ extern "C" int ks_line_batch(ks_ctx* ctx, const ks_desc* desc, uint32_t num_exp,
   if (!desc || !stats || !strides || !out) return KS_E_INVALID;
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  hipLaunchKernelGGL(line_kernel, dim3(num_exp), dim3(256), 0, (hipStream_t)stream, desc, num_exp, stats,
-                     stats_rows, J, strides, out);
+  // a wave per experiment: of two or three strides from 1024 experiments on (2000 of
+  // 2 x 256 9 us against 13, 20000 of 2 x 64 18 against 26; 6000 of 8 x 32 17.4 against
+  // 16.5), of up to 16 from 32768 (60000 of 8 x 32 117 against 136, of 16 x 32 220
+  // against 238; of 64 x 16 829 against 804), and where a grid of 2^32 - 1 threads
+  // does not hold a workgroup each
+  const bool many = num_exp > (J < 4 ? 1024u : J <= 16 ? 32768u : (1u << 24) - 1u);
+  auto run = [&](auto kernel, uint32_t grid) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, desc, num_exp, stats, stats_rows, J,
+                       strides, out);
+  };
+  if (many) run(line_kernel<4>, (num_exp + 3) / 4);
+  else run(line_kernel<1>, num_exp);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? KS_OK : hip_fail(e, "line launch");
 }
