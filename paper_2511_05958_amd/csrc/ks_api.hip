@@ -343,12 +343,14 @@ LaunchCfg recorded(const ks_ctx* c, int kc, uint32_t num_series) {
 // 256 1731 and 1575), and for 512-row classes with series of more than 640 KB on
 // average, where the largest ones' stream decides (8192 uneven ones up to 512 x
 // 4096 1056 and 997; below, its barriers cost: 8192 of 512 x 256 1022 and 1130).
-// Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671.
+// Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671. From 2^23
+// series on a grid of 2^32 - 1 threads does not hold them with eight waves each.
 LaunchCfg default_cfg(int kc, const ScanArgs& a) {
   LaunchCfg cfg;
   cfg.graph = 0;
   cfg.spread = a.num_series <= kSplitMaxSeries || tiny_batch(kc, a);
-  if (kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && a.num_samples / a.num_series > (160u << 10))) cfg.variant = 2;
+  const bool long_series = kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && a.num_samples / a.num_series > (160u << 10));
+  if (long_series && a.num_series < (1u << 23)) cfg.variant = 2;
   return cfg;
 }
 

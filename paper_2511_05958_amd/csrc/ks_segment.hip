@@ -48,6 +48,8 @@ namespace {
 // of 256 x 1024 741 us, 769 with sixteen; 512 of up to 512 x 4096 354 and 269).
 constexpr int tree_nt(int kmax) { return kmax <= 256 ? 512 : 1024; }
 
+constexpr uint32_t kTreeSeries = 1u << 21;  // series of a launch
+
 constexpr uint32_t kSmall = ks::kWave;  // windows of up to this many rows are a wave's work
 
 template <int KMAX>
@@ -307,7 +309,12 @@ extern "C" int ks_segment_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t n
     rows = ctx->seg.rows;
   }
   auto run = [&](auto f) {
-    f(num_series, st, samples, num_samples, desc, *params, max_K, rows, max_levels, max_cp, cps, counts);
+    // a grid holds up to 2^32 - 1 threads
+    for (uint32_t s = 0, n; s < num_series; s += n) {
+      n = num_series - s < kTreeSeries ? num_series - s : kTreeSeries;
+      f(n, st, samples, num_samples, desc + s, *params, max_K, rows, max_levels, max_cp, cps + (uint64_t)s * max_cp,
+        counts + s);
+    }
   };
   switch (k_class(max_K)) {
     case 0: run(launch_tree<64>); break;
