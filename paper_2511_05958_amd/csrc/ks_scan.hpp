@@ -585,8 +585,10 @@ __device__ __forceinline__ void walk_step(uint32_t r, const uint32_t (&c)[G], co
 
 // Positions [pa, pb) of one pass. TIES = false: every position ends a group
 // (no two Q equal), so the walk takes eight positions per broadcast read with
-// no per-position test; TIES = true reads the group-end bits.
-template <int KMAX, int G, bool TIES>
+// no per-position test; TIES = true reads the group-end bits, one position at a
+// time or (MASKED) eight, D replaced by 0, which neither bound passes, where no
+// group ends.
+template <int KMAX, int G, bool TIES, bool MASKED = false>
 __device__ __forceinline__ void walk_positions(const uint16_t* __restrict__ is, const uint64_t* __restrict__ tie,
                                                uint32_t pa, uint32_t pb, uint32_t K, const uint32_t (&c)[G],
                                                int32_t (&D)[G], int32_t (&mx)[G], int32_t (&mn)[G]) {
@@ -597,20 +599,25 @@ __device__ __forceinline__ void walk_positions(const uint16_t* __restrict__ is, 
     dn[g] = -(int32_t)c[g];
   }
   uint32_t p = pa;
-  if constexpr (!TIES) {
+  if constexpr (!TIES || MASKED) {
     // pa is a multiple of 8: two 8-byte aligned broadcast reads per group,
     // the next group's issued before this one's arithmetic (the address
     // clamped inside the KMAX-entry array; a clamped read goes unused)
     uint2 na = make_uint2(0u, 0u), nb = make_uint2(0u, 0u);
+    const uint8_t* ends8 = reinterpret_cast<const uint8_t*>(tie);
+    uint32_t ne = 0;
     if (p + 8 <= pb) {
       na = *reinterpret_cast<const uint2*>(is + p);
       nb = *reinterpret_cast<const uint2*>(is + p + 4);
+      if constexpr (TIES) ne = ends8[p / 8];
     }
     for (; p + 8 <= pb; p += 8) {
       const uint2 ra = na, rb = nb;
       const uint32_t pn = min(p + 8, KMAX - 8u);
+      const uint32_t ends = TIES ? (uint32_t)__builtin_amdgcn_readfirstlane((int)ne) : 0xffu;
       na = *reinterpret_cast<const uint2*>(is + pn);
       nb = *reinterpret_cast<const uint2*>(is + pn + 4);
+      if constexpr (TIES) ne = ends8[pn / 8];
       const uint32_t w[4] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)ra.x),
                              (uint32_t)__builtin_amdgcn_readfirstlane((int)ra.y),
                              (uint32_t)__builtin_amdgcn_readfirstlane((int)rb.x),
@@ -623,7 +630,7 @@ __device__ __forceinline__ void walk_positions(const uint16_t* __restrict__ is, 
         for (int j = 0; j < 8; ++j) {
           const uint32_t r = (j & 1) ? (w[j >> 1] >> 16) : (w[j >> 1] & 0xffffu);
           x += r < c[g] ? up[g] : dn[g];
-          v[j] = x;
+          v[j] = TIES ? x & ((int32_t)(ends << (31 - j)) >> 31) : x;
         }
 #pragma unroll
         for (int j = 0; j < 8; j += 2) {
@@ -634,7 +641,7 @@ __device__ __forceinline__ void walk_positions(const uint16_t* __restrict__ is, 
       }
     }
   }
-  // the rest one position at a time (TIES: all of [pa, pb))
+  // the rest one position at a time (all of [pa, pb) where they are not taken eight at a time)
   for (; p < pb; ++p) {
     const uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)is[p]);
     walk_step<G>(r, c, up, dn, D);
@@ -685,7 +692,7 @@ __device__ __forceinline__ void wave_best(uint32_t& U, uint32_t& c, uint32_t K) 
 // Walk of one pass over G slots (wave-uniform) on positions [pa, pb); with
 // pa > 0, D starts from K i_c(pa - 1) - c pa, the count taken from pos[]
 // (the sorted position of every row). Returns the partial U per slot.
-template <int KMAX, int G>
+template <int KMAX, int G, bool MASKED = false>
 __device__ __forceinline__ void walk_pass(const uint16_t* __restrict__ is, const uint16_t* __restrict__ pos,
                                           const uint64_t* __restrict__ tie, bool ties, uint32_t K, uint32_t pa,
                                           uint32_t pb, const uint32_t (&c)[G], uint32_t (&U)[G]) {
@@ -715,7 +722,7 @@ __device__ __forceinline__ void walk_pass(const uint16_t* __restrict__ is, const
     for (int g = 0; g < G; ++g) D[g] = (int32_t)(K * cnt[g]) - (int32_t)(c[g] * pa);
   }
   if (ties)
-    walk_positions<KMAX, G, true>(is, tie, pa, pb, K, c, D, mx, mn);
+    walk_positions<KMAX, G, true, MASKED>(is, tie, pa, pb, K, c, D, mx, mn);
   else
     walk_positions<KMAX, G, false>(is, tie, pa, pb, K, c, D, mx, mn);
 #pragma unroll

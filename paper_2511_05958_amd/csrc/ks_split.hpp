@@ -311,8 +311,8 @@ __global__ __launch_bounds__(kSplitWalkNT) void split_walk_kernel(uint64_t num_s
 // Keys, order and the most significant split of one series or window whose row
 // moments are at hand, by one workgroup: every row's rank counted (a few threads
 // to a row where there are fewer rows than threads), the walk shared by all
-// waves. For a few hundred rows that is a handful of barriers, where the radix
-// sort of finish_series makes four for each of some ten digits.
+// waves. That is a handful of barriers, where the radix sort of finish_series makes
+// four for each of some ten digits.
 template <int KMAX, int NT>
 struct RankSmem {
   static constexpr uint32_t W = NT / kWave;
@@ -324,43 +324,114 @@ struct RankSmem {
   uint32_t partU[NT], bestU[W], bestC[W], red[W];
 };
 
+// Ranks of K > kRankBlock keys: counted within blocks of kRankBlock keys, which
+// are then in order in LDS, and searched for in every other block (2048 keys: 256
+// compares and 63 reads a key in place of 2048 compares; with the masked walk a
+// segmentation's window of 2048 rows takes 220 us alone on its CU, 603 before).
+// Leaves keys, is and pos in order.
+constexpr uint32_t kRankBlock = 256;
+template <int KMAX, int NT>
+__device__ __forceinline__ void rank_blocks(RankSmem<KMAX, NT>& sm, const SortKey (&mine)[(KMAX + NT - 1) / NT],
+                                            uint32_t K, bool wide) {
+  constexpr int E = (KMAX + NT - 1) / NT;
+  const uint32_t tid = threadIdx.x, w0 = wave_id() * kWave;
+  uint32_t rank[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t b0 = (w0 + e * NT) & ~(kRankBlock - 1), b1 = min(K, b0 + kRankBlock);  // the wave's block
+    rank[e] = b0 < K ? b0 + count_below(sm.lo, sm.hi, b0, b1, mine[e].lo, mine[e].hi, wide) : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (tid + e * NT < K) {
+      sm.lo[rank[e]] = mine[e].lo;
+      sm.hi[rank[e]] = mine[e].hi;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t own = (w0 + e * NT) & ~(kRankBlock - 1);
+    if (own >= K) continue;
+    rank[e] -= own;
+    for (uint32_t b0 = 0; b0 < K; b0 += kRankBlock) {
+      if (b0 == own) continue;
+      const uint32_t n = min(K - b0, kRankBlock);
+      auto below = [&](uint32_t j) {  // key j of the block (j < n) is below this one
+        const uint64_t lo = sm.lo[b0 + j];
+        if (!wide) return lo < mine[e].lo;
+        const uint64_t hi = sm.hi[b0 + j];
+        return hi < mine[e].hi || (hi == mine[e].hi && lo < mine[e].lo);
+      };
+      uint32_t at = 0;
+#pragma unroll
+      for (uint32_t s = kRankBlock / 2; s; s >>= 1)
+        if (at + s <= n && below(at + s - 1)) at += s;
+      rank[e] += at + (at < n && below(at) ? 1u : 0u);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t i = tid + e * NT;
+    if (i < K) {
+      sm.lo[rank[e]] = mine[e].lo;
+      sm.hi[rank[e]] = mine[e].hi;
+      sm.is[rank[e]] = (uint16_t)i;
+      sm.pos[i] = (uint16_t)rank[e];
+    }
+  }
+  __syncthreads();
+}
+
 // key(i): row i's key (i < K). Candidates c_lo .. c_hi; their statistics to
 // allU (nullable). Wave 0 returns the winner (c = 0: no candidate).
 template <int KMAX, int NT, class Key>
 __device__ __forceinline__ void rank_walk(RankSmem<KMAX, NT>& sm, Key&& key, uint32_t K, uint32_t c_lo, uint32_t c_hi,
                                           uint32_t* __restrict__ allU, uint32_t& bU, uint32_t& bC) {
   constexpr uint32_t W = NT / kWave;
+  constexpr int E = (KMAX + NT - 1) / NT;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
   bool w53 = false;
-  for (uint32_t i = tid; i < K; i += NT) {
-    const SortKey k = key(i);
-    sm.lo[i] = k.lo;
-    sm.hi[i] = k.hi;
-    sm.rank[i] = 0;
-    w53 |= k.hi != 0;
+  SortKey mine[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t i = tid + e * NT;
+    mine[e] = SortKey{0, 0};
+    if (i < K) {
+      mine[e] = key(i);
+      sm.lo[i] = mine[e].lo;
+      sm.hi[i] = mine[e].hi;
+      if (K <= kRankBlock) sm.rank[i] = 0;
+      w53 |= mine[e].hi != 0;
+    }
   }
   const bool wide = block_any<NT>(w53, sm.red);
-  {  // several threads count for one row where there are fewer rows than threads
+  const bool blocks = KMAX > (int)kRankBlock && K > kRankBlock;
+  if (blocks) {
+    if constexpr (KMAX > (int)kRankBlock) rank_blocks<KMAX, NT>(sm, mine, K, wide);
+  } else {  // several threads count for one row where there are fewer rows than threads
     const uint32_t KR = min((K + kWave - 1u) & ~(uint32_t)(kWave - 1), (uint32_t)NT), P = NT / KR;
     const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
     const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
     if (q < P)
       for (uint32_t i = i0; i < K; i += KR)
         atomicAdd(&sm.rank[i], count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
+    __syncthreads();
+    for (uint32_t i = tid; i < K; i += NT) {
+      const uint32_t p = sm.rank[i];
+      sm.is[p] = (uint16_t)i;
+      sm.pos[i] = (uint16_t)p;
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  for (uint32_t i = tid; i < K; i += NT) {
-    const uint32_t p = sm.rank[i];
-    sm.is[p] = (uint16_t)i;
-    sm.pos[i] = (uint16_t)p;
-  }
-  __syncthreads();
   bool tied = false;
   for (uint32_t p0 = w * kWave; p0 < K; p0 += NT) {
     const uint32_t p = p0 + lane;
     bool end = false;
     if (p < K) {
-      const uint32_t i = sm.is[p], j = sm.is[min(p + 1, K - 1)];
+      const uint32_t q = min(p + 1, K - 1);
+      const uint32_t i = blocks ? p : sm.is[p], j = blocks ? q : sm.is[q];
       end = p + 1 == K || group_end(SortKey{sm.lo[i], sm.hi[i]}, SortKey{sm.lo[j], sm.hi[j]});
     }
     const uint64_t m = ballot(end);
@@ -387,7 +458,7 @@ __device__ __forceinline__ void rank_walk(RankSmem<KMAX, NT>& sm, Key&& key, uin
     uint32_t c[1] = {c_lo + slot * kWave + lane}, U[1] = {0};
     if (slot < ns) {
       const uint32_t pa = min(K, share * len), pb = min(K, pa + len);
-      if (pa < pb) walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, pa, pb, c, U);
+      if (pa < pb) walk_pass<KMAX, 1, (KMAX > (int)kRankBlock)>(sm.is, sm.pos, sm.tie, ties, K, pa, pb, c, U);
     }
     sm.partU[tid] = U[0];
     __syncthreads();
@@ -398,7 +469,7 @@ __device__ __forceinline__ void rank_walk(RankSmem<KMAX, NT>& sm, Key&& key, uin
   } else {
     for (uint32_t slot = w; slot < ns; slot += W) {
       uint32_t c[1] = {c_lo + slot * kWave + lane}, U[1];
-      walk_pass<KMAX, 1>(sm.is, sm.pos, sm.tie, ties, K, 0, K, c, U);
+      walk_pass<KMAX, 1, (KMAX > (int)kRankBlock)>(sm.is, sm.pos, sm.tie, ties, K, 0, K, c, U);
       consider(c[0], U[0]);
     }
   }
