@@ -43,20 +43,7 @@ __global__ __launch_bounds__(kFeatPlanNT) void feature_plan_kernel(const ks_desc
     const uint32_t bl = 64u - (uint32_t)__clzll(bytes);
     return feat_class_index(feat_batches(d.N)) * kFeatBuckets + (kFeatBuckets - 2 - min(bl, kFeatBuckets - 2));
   };
-  constexpr uint32_t kAhead = 8;  // descriptors fetched together
-  auto each = [&](auto&& visit) {
-    if (num_series <= (uint32_t)kFeatPlanNT) {
-      visit(tid, key(min(tid, num_series - 1)), tid < num_series);
-      return;
-    }
-    for (uint32_t s = tid; s < num_series; s += kAhead * kFeatPlanNT) {
-      uint32_t k[kAhead];
-#pragma unroll
-      for (uint32_t q = 0; q < kAhead; ++q) k[q] = key(min(s + q * kFeatPlanNT, num_series - 1));
-#pragma unroll
-      for (uint32_t q = 0; q < kAhead; ++q) visit(s + q * kFeatPlanNT, k[q], s + q * kFeatPlanNT < num_series);
-    }
-  };
+  auto each = [&](auto&& visit) { each_series<kFeatPlanNT>(num_series, key, visit); };
   each([&](uint32_t, uint32_t k, bool valid) { bin_add(cnt, k, valid); });
   __syncthreads();
   if (tid == 0) {

@@ -132,6 +132,25 @@ __device__ __forceinline__ uint32_t bin_add(uint32_t* ctr, uint32_t b, bool vali
   return valid ? atomicAdd(&ctr[b], 1u) : 0u;
 }
 
+// visit(s, bin(s), valid) for the series s < S, a workgroup of NT threads taking
+// them in order, every lane in each call. bin reads the series' descriptor; up to
+// eight are fetched together, only as many as there are left (1100 series
+// with eight all the same: 9 us a plan, 5.5 so).
+template <int NT, class Bin, class Visit>
+__device__ __forceinline__ void each_series(uint32_t S, Bin&& bin, Visit&& visit) {
+  constexpr uint32_t kAhead = 8;
+  for (uint32_t s0 = 0; s0 < S; s0 += kAhead * NT) {
+    const uint32_t n = (S - s0 + NT - 1) / NT;
+    uint32_t b[kAhead];
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q)
+      if (q < n) b[q] = bin(min(s0 + q * NT + threadIdx.x, S - 1));
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q)
+      if (q < n) visit(s0 + q * NT + threadIdx.x, b[q], s0 + q * NT + threadIdx.x < S);
+  }
+}
+
 // Publishes this thread's LDS writes to the workgroup. The wait is written out:
 // for a barrier at the head of a loop the compiler left out the wait for LDS
 // writes that reach it over the back edge, and other waves then read what was
