@@ -1323,32 +1323,45 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
 // no last round is nearly empty (statistics of 700 x 300 rows of 1800 samples: 366
 // us in one chunk, 303 in four; 2100 x 64 of 2500: 291 in one, 259 in two) and
 // full rounds are not cut further (512 x 256 of 2048: 181 us in one round, 197 in
-// two).
+// two). One chunk that fills less than kFullRound of the device counts for more, as
+// it does not keep HBM busy (600 x 40 rows of 9000: 181 us in one chunk, 162 in
+// three); where series are of at most kFewRows rows and the batch's samples say that
+// they are short, a wave's steps of four of them count instead (features of 1500 x
+// 40 rows of 16: 48.6 us in two chunks, 42.7 in one; of longer series smaller
+// chunks even out: 900 x 1024 rows of 16 322 us in nine, 364 in one).
 // A chunk is not made smaller than a row (or a step of four short rows) per
-// wave, except in batches of at most kCoopRows rows (two waves per SIMD with a
-// wave a row): rows too long for the registers then go a row at a time to all
-// waves of a workgroup (select_rows_coop); in larger ones that only reads every
-// row's first batch eight times (512 x 64 rows of 8192 samples 330 us, 220 with
-// a wave a row).
+// wave, except in batches of at most kCoopRows rows by max_K (two waves per SIMD
+// with a wave a row): there rows too long for the registers may go a row at a time
+// to all waves of a workgroup (select_rows_coop), which row_span has done for
+// series of at most 512 rows in all (K times the series) or, up to kCoopRows, of
+// rows of W x 4096 samples or more; in larger ones that only reads every row's
+// first batch eight times (512 x 64 rows of 8192 samples 330 us, 220 with a wave a
+// row). Other rows get chunks of a row or step per wave there, the rest stay empty.
 constexpr uint32_t kRowPassChunks = 256;  // chunks of a series at most
 constexpr uint32_t kCoopRows = 2048;
 __host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 5120u : mask == kRowsAll ? 1024u : 8192u; }
 constexpr uint32_t kChunkWGs = 8192;  // the largest of them
 constexpr uint32_t kMidResident = 1024;   // four workgroups per CU
-constexpr uint32_t kChunkFixedRows = 3;   // what a wave's start costs, in rows
-__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, uint32_t mask) {
-  const uint32_t least = (uint64_t)num_series * max_K <= kCoopRows ? 1u : (uint32_t)row_pass_threads(mask) / kWave;
+constexpr double kChunkFixedRows = 3.0;   // what a wave's start costs, in rows
+constexpr double kChunkFixedSteps = 0.5;  // and in steps of four short rows
+constexpr double kFullRound = 0.8;
+constexpr uint32_t kFewRows = 64;
+__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, uint64_t num_samples, uint32_t mask) {
+  const uint64_t max_rows = (uint64_t)num_series * max_K;
+  const uint32_t least = max_rows <= kCoopRows ? 1u : (uint32_t)row_pass_threads(mask) / kWave;
   const uint32_t most = min((max_K + least - 1) / least, kRowPassChunks);
   uint32_t c = chunk_wgs(mask) / num_series;
   c = c < most ? c : most;
   c = c ? c : 1u;
   if (mask != kRowsMid) return c;
+  const bool short_rows = max_K <= kFewRows && num_samples <= max_rows * kGroupMaxN;
   uint32_t best = 1;
-  uint64_t cost = ~0ull;
+  double cost = 1e300;
   for (uint32_t q = 1; q <= c; ++q) {
-    const uint64_t rounds = ((uint64_t)num_series * q + kMidResident - 1) / kMidResident;
-    const uint32_t rows = (max_K + q - 1) / q;
-    const uint64_t t = rounds * ((rows + least - 1) / least + kChunkFixedRows);
+    const double fill = (double)num_series * q / kMidResident;
+    const double rounds = ceil(fill) + (q == 1 && fill < kFullRound ? (kFullRound - fill) / 2 : 0.0);
+    const uint32_t rows = ((max_K + q - 1) / q + least - 1) / least;  // of a wave
+    const double t = rounds * (short_rows ? (rows + kGroupRows - 1) / kGroupRows + kChunkFixedSteps : rows + kChunkFixedRows);
     if (t < cost) {
       cost = t;
       best = q;
