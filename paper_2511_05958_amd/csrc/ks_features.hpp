@@ -143,10 +143,7 @@ __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves
 // buffer, element by element (consecutive threads, consecutive elements);
 // then the chunk's network input rows (bf16 of the nine features and the two
 // position channels, channels 11..15 zero), staged in LDS, are written as
-// 16-byte stores. The two slot rows on each side of [2, 2 + K) (the
-// convolutions' zero padding) and the first four rows of a malformed series
-// (K = 0) are zero; a chunk wholly past row K + 4 writes nothing, as no
-// output row of the network reads its inputs there.
+// 16-byte stores. Only the series' own rows: the network masks what lies outside.
 template <int NT>
 __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restrict__ desc, uint32_t num_series,
                                                           float* __restrict__ feat_out, uint64_t feat_rows,
@@ -162,41 +159,35 @@ __global__ __launch_bounds__(NT) void feature_pack_kernel(const ks_desc* __restr
   if (r0 >= SR) return;
   const uint32_t nr = SR - r0 < (uint32_t)NT ? SR - r0 : (uint32_t)NT;
   const uint32_t K = lw.K[s];
-  if (r0 >= K + 4u) return;
   const uint64_t row0 = (uint64_t)s * SR + r0;
   // rows [lo, hi) of the chunk hold data
   const uint32_t lo = r0 < 2u ? 2u - r0 : 0u;
   const uint32_t hi = K + 2u > r0 ? (K + 2u - r0 < nr ? K + 2u - r0 : nr) : 0u;
-  if (lo < hi) {
-    const uint32_t gmin = block_min_u32<NT>(tid < Cs ? lw.cmin[(uint64_t)s * Cs + tid] : 0xffffffffu, red);
-    if (blockIdx.y == 0 && tid == 0) lw.smin[s] = gmin;
-    const double denom = (double)(gmin > 1 ? gmin : 1u);
-    const ks_desc d = desc[s];
-    const bool to_user = feat_out && d.aux_offset <= feat_rows && K <= feat_rows - d.aux_offset;
-    for (uint32_t q = lo * 9u + tid; q < hi * 9u; q += NT) {
-      const uint32_t rr = q / 9u, k = q - rr * 9u;
-      const uint64_t e = row0 * 9u + q;
-      const uint32_t x = __float_as_uint(feat_ws[e]);
-      const float f = (float)((double)(x - gmin) / denom);
-      feat_ws[e] = f;
-      if (to_user) feat_out[(d.aux_offset + r0 + rr - 2) * 9 + k] = f;
-      bf[rr * 16 + k] = cnn::f2bf(f);
-    }
+  if (lo >= hi) return;
+  const uint32_t gmin = block_min_u32<NT>(tid < Cs ? lw.cmin[(uint64_t)s * Cs + tid] : 0xffffffffu, red);
+  if (blockIdx.y == 0 && tid == 0) lw.smin[s] = gmin;
+  const double denom = (double)(gmin > 1 ? gmin : 1u);
+  const ks_desc d = desc[s];
+  const bool to_user = feat_out && d.aux_offset <= feat_rows && K <= feat_rows - d.aux_offset;
+  for (uint32_t q = lo * 9u + tid; q < hi * 9u; q += NT) {
+    const uint32_t rr = q / 9u, k = q - rr * 9u;
+    const uint64_t e = row0 * 9u + q;
+    const uint32_t x = __float_as_uint(feat_ws[e]);
+    const float f = (float)((double)(x - gmin) / denom);
+    feat_ws[e] = f;
+    if (to_user) feat_out[(d.aux_offset + r0 + rr - 2) * 9 + k] = f;
+    bf[rr * 16 + k] = cnn::f2bf(f);
   }
   __syncthreads();
-  for (uint32_t q = tid; q < nr * 2u; q += NT) {
-    const uint32_t rr = q >> 1, h = q & 1u;
-    u32x4 v{0u, 0u, 0u, 0u};
-    if (rr >= lo && rr < hi) {
-      const uint32_t t = r0 + rr - 2;
-      if (h == 0) {
-        const u32x4 a = *reinterpret_cast<const u32x4*>(&bf[rr * 16]);
-        v = a;
-      } else {
-        const uint32_t b8 = bf[rr * 16 + 8];
-        const uint32_t p9 = cnn::f2bf(cnn::pos_frac(t, K)), p10 = cnn::f2bf(cnn::pos_centre(t, K));
-        v = u32x4{b8 | (p9 << 16), p10, 0u, 0u};
-      }
+  for (uint32_t q = lo * 2u + tid; q < hi * 2u; q += NT) {
+    const uint32_t rr = q >> 1, h = q & 1u, t = r0 + rr - 2;
+    u32x4 v;
+    if (h == 0) {
+      v = *reinterpret_cast<const u32x4*>(&bf[rr * 16]);
+    } else {
+      const uint32_t b8 = bf[rr * 16 + 8];
+      const uint32_t p9 = cnn::f2bf(cnn::pos_frac(t, K)), p10 = cnn::f2bf(cnn::pos_centre(t, K));
+      v = u32x4{b8 | (p9 << 16), p10, 0u, 0u};
     }
     *reinterpret_cast<u32x4*>(x0 + (row0 + rr) * 16 + h * 8) = v;
   }
