@@ -100,8 +100,7 @@ struct LearnBuffers {
 // Workspace of the binary segmentation (ks_segment_batch), grown on demand.
 struct SegBuffers {
   ks::RowMom* rows = nullptr;  // per-row moments and minimum (s * max_K + i)
-  uint32_t* ticket = nullptr;
-  uint64_t cap_rows = 0, cap_series = 0;
+  uint64_t cap_rows = 0;
 };
 
 int hip_fail(hipError_t e, const char* what);

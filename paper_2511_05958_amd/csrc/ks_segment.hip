@@ -35,7 +35,6 @@ namespace ks_host {
 
 void free_seg(SegBuffers& b) {
   (void)hipFree(b.rows);
-  (void)hipFree(b.ticket);
   b = SegBuffers{};
 }
 
@@ -267,22 +266,18 @@ void launch_tree(uint32_t num_series, hipStream_t st, const uint32_t* samples, u
                      max_K, rows, max_levels, max_cp, cps, counts);
 }
 
-int ensure_seg(ks_ctx* c, uint64_t rows, uint64_t series) {
+int ensure_seg(ks_ctx* c, uint64_t rows) {
   SegBuffers& b = c->seg;
-  if (rows <= b.cap_rows && series <= b.cap_series) return KS_OK;
-  if (rows < b.cap_rows) rows = b.cap_rows;
-  if (series < b.cap_series) series = b.cap_series;
+  if (rows <= b.cap_rows) return KS_OK;
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   free_seg(b);
-  if (hipMalloc(&b.rows, sizeof(ks::RowMom) * rows) != hipSuccess ||
-      hipMalloc(&b.ticket, sizeof(uint32_t) * series) != hipSuccess) {
+  if (hipMalloc(&b.rows, sizeof(ks::RowMom) * rows) != hipSuccess) {
     free_seg(b);
     (void)hipGetLastError();
     return KS_E_NOMEM;
   }
   b.cap_rows = rows;
-  b.cap_series = series;
   return KS_OK;
 }
 
@@ -303,8 +298,8 @@ extern "C" int ks_segment_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t n
   const ks::RowMom* rows = nullptr;
   // fewer than two workgroups per CU: the rows are spread over the device first
   if (num_series < 2u * (uint32_t)ctx->num_cus) {
-    if (int rc = ensure_seg(ctx, (uint64_t)num_series * max_K, num_series)) return rc;
-    const ks::SplitWs ws{ctx->seg.rows, nullptr, nullptr, ctx->seg.ticket};
+    if (int rc = ensure_seg(ctx, (uint64_t)num_series * max_K)) return rc;
+    const ks::SplitWs ws{ctx->seg.rows, nullptr, nullptr, nullptr};
     ks::launch_split_moments(samples, num_samples, desc, num_series, max_K, nullptr, ws, st);
     rows = ctx->seg.rows;
   }

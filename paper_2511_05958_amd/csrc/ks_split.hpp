@@ -45,7 +45,7 @@ struct SplitWs {
   RowMom* mom;       // series s, row i at s * max_K + i
   SortKey* sorted;   // the same layout, in key order
   uint32_t* best;    // series s, slot j: U and c at (s * kSplitSlots + j) * 2
-  uint32_t* ticket;  // per series: finished slots
+  uint32_t* ticket;  // per series: finished slots (nullptr: no walk follows the moments)
 };
 
 // Series and slot (or chunk) of the calling workgroup. Workgroups go to the eight
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t*
     if (out && c == 0 && threadIdx.x == 0) write_result(out + s, 0, 0, 0, 0, 0.0, 0.0, 1.0, bad);
     return;
   }
-  if (c == 0 && threadIdx.x == 0) ws.ticket[s] = 0;
+  if (ws.ticket && c == 0 && threadIdx.x == 0) ws.ticket[s] = 0;
   const uint32_t K = d.K, N = d.N, lane = lane_id(), w = wave_id();
   uint32_t R = (K + C - 1) / C;
   // fewer rows than waves and more than a batch of samples per wave: all waves on each row
