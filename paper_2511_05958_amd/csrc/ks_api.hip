@@ -93,8 +93,8 @@ unsigned char* scratch_of(int device) {
 // 256 KB: 1024 of 64 x 256 take 27 us against 29, 512 of 256 x 64 34 against 57; a
 // series of more than 256 KB keeps its one workgroup busy for longer than the
 // spread scan's two more launches take.
-constexpr uint32_t kSplitMaxSeries = 384;
-constexpr uint32_t kTinyMaxSeries = 1024;
+uint32_t split_max_series(const ks_ctx* c) { return 3u * (uint32_t)c->num_cus / 2u; }
+uint32_t tiny_max_series(const ks_ctx* c) { return 4u * (uint32_t)c->num_cus; }
 constexpr int kTinyMaxClass = 2;                 // K <= 256
 constexpr uint64_t kTinyMaxSamples = 1u << 16;   // 256 KB a series
 
@@ -291,8 +291,8 @@ int launch_plan(ks_ctx* c, int kc, int v, int mode, const ScanArgs& a, bool use_
 
 // Whether a batch takes the one-launch scan (by the mean size of its series, if
 // the sample buffer holds no more than the batch; any series is scanned right).
-bool tiny_batch(int kc, const ScanArgs& a) {
-  return kc <= kTinyMaxClass && a.num_series <= kTinyMaxSeries && a.num_samples / a.num_series <= kTinyMaxSamples;
+bool tiny_batch(const ks_ctx* c, int kc, const ScanArgs& a) {
+  return kc <= kTinyMaxClass && a.num_series <= tiny_max_series(c) && a.num_samples / a.num_series <= kTinyMaxSamples;
 }
 
 // The scan of a batch of few series (KS_E_NOMEM, nothing launched, where its
@@ -300,7 +300,7 @@ bool tiny_batch(int kc, const ScanArgs& a) {
 // kernels from a graph costs more on the host (27 us a call for one sweep,
 // against 8).
 int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
-  if (tiny_batch(kc, a)) {
+  if (tiny_batch(c, kc, a)) {
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(a.num_series), dim3(ks::kTinyNT), 0, st, a.samples, a.num_samples, a.desc, a.prm,
                          a.max_K, a.out, a.allU, a.allU_len);
@@ -313,7 +313,7 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
   } else {
     if (int rc = ensure_split(c, a.num_series, a.max_K, st)) return rc;
     const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
-    ks::launch_split_moments(a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
+    ks::launch_split_moments((uint32_t)c->num_cus, a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
     hipLaunchKernelGGL(ks::split_rank_kernel, ks::split_grid(a.num_series, a.max_K), dim3(ks::kSplitNT), 0, st,
                        a.num_samples, a.desc, a.num_series, a.max_K, ws);
     hipLaunchKernelGGL(ks::split_walk_kernel, ks::split_grid(a.num_series, a.max_K - 1), dim3(ks::kSplitWalkNT), 0, st,
@@ -345,10 +345,10 @@ LaunchCfg recorded(const ks_ctx* c, int kc, uint32_t num_series) {
 // 4096 1056 and 997; below, its barriers cost: 8192 of 512 x 256 1022 and 1130).
 // Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671. From 2^23
 // series on a grid of 2^32 - 1 threads does not hold them with eight waves each.
-LaunchCfg default_cfg(int kc, const ScanArgs& a) {
+LaunchCfg default_cfg(const ks_ctx* c, int kc, const ScanArgs& a) {
   LaunchCfg cfg;
   cfg.graph = 0;
-  cfg.spread = a.num_series <= kSplitMaxSeries || tiny_batch(kc, a);
+  cfg.spread = a.num_series <= split_max_series(c) || tiny_batch(c, kc, a);
   const bool long_series = kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && a.num_samples / a.num_series > (160u << 10));
   if (long_series && a.num_series < (1u << 23)) cfg.variant = 2;
   return cfg;
@@ -360,7 +360,7 @@ LaunchCfg config_for(const ks_ctx* c, int kc, const ScanArgs& a, uint32_t opts) 
   LaunchCfg cfg = recorded(c, kc, a.num_series);
   if (opts & KS_OPT_GRID) cfg.mode = KS_LAUNCH_GRID;
   if (opts & KS_OPT_PERSISTENT) cfg.mode = KS_LAUNCH_PERSISTENT;
-  if (is_default(cfg)) cfg = default_cfg(kc, a);
+  if (is_default(cfg)) cfg = default_cfg(c, kc, a);
   if (opts & KS_OPT_NO_GRAPH) cfg.graph = 0;
   return cfg;
 }
@@ -508,7 +508,7 @@ int ks_reserve(ks_ctx* ctx, uint32_t max_series, uint64_t max_total_steps) {
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   if (int rc = ensure_workspace(ctx, max_series, max_total_steps)) return rc;
   // and the scan of few series, which does without where the device is full
-  const uint32_t few = max_series < kSplitMaxSeries ? max_series : kSplitMaxSeries;
+  const uint32_t most = split_max_series(ctx), few = max_series < most ? max_series : most;
   const int rc = few ? ensure_split(ctx, few, KS_MAX_K, nullptr) : KS_OK;
   return rc == KS_E_NOMEM ? KS_OK : rc;
 }
@@ -597,7 +597,7 @@ int ks_autotune(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
     }
     for (int i = 0; i < np && rc == KS_OK; ++i) {
       float t = 0.f;
-      rc = time_cfg(is_default(plans[i]) ? default_cfg(kc, a) : plans[i], t);
+      rc = time_cfg(is_default(plans[i]) ? default_cfg(ctx, kc, a) : plans[i], t);
       if (rc == KS_OK && (!have || t < bms)) {
         bcfg = plans[i];
         bms = t;

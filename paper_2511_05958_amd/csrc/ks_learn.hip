@@ -394,9 +394,9 @@ int ks_features(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
   const bool one = num_series <= ks::kRowPassOneLaunch;
   uint32_t Cs = 1;  // most chunks that a launch below makes of a series
   for (uint32_t mask : {ks::kRowsOne, ks::kRowsMid, ks::kRowsAll})
-    if ((mask == ks::kRowsAll) == one) Cs = std::max(Cs, ks::row_pass_chunks(num_series, max_K, num_samples, mask));
+    if ((mask == ks::kRowsAll) == one) Cs = std::max(Cs, ks::row_pass_chunks((uint32_t)ctx->num_cus, num_series, max_K, num_samples, mask));
   auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
-    const uint32_t C = ks::row_pass_chunks(num_series, max_K, num_samples, mask);
+    const uint32_t C = ks::row_pass_chunks((uint32_t)ctx->num_cus, num_series, max_K, num_samples, mask);
     hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
                        num_series, max_K, SR, learn_ws(ctx), b.feat, plan, C, Cs);
   };

@@ -300,7 +300,7 @@ extern "C" int ks_segment_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t n
   if (num_series < 2u * (uint32_t)ctx->num_cus) {
     if (int rc = ensure_seg(ctx, (uint64_t)num_series * max_K)) return rc;
     const ks::SplitWs ws{ctx->seg.rows, nullptr, nullptr, nullptr};
-    ks::launch_split_moments(samples, num_samples, desc, num_series, max_K, nullptr, ws, st);
+    ks::launch_split_moments((uint32_t)ctx->num_cus, samples, num_samples, desc, num_series, max_K, nullptr, ws, st);
     rows = ctx->seg.rows;
   }
   auto run = [&](auto f) {

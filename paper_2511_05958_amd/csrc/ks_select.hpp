@@ -1339,18 +1339,20 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
 // row). Other rows get chunks of a row or step per wave there, the rest stay empty.
 constexpr uint32_t kRowPassChunks = 256;  // chunks of a series at most
 constexpr uint32_t kCoopRows = 2048;
-__host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 5120u : mask == kRowsAll ? 1024u : 8192u; }
-constexpr uint32_t kChunkWGs = 8192;  // the largest of them
-constexpr uint32_t kMidResident = 1024;   // four workgroups per CU
+// workgroups per CU of a launch at most, and the most that a launch has
+__host__ __device__ constexpr uint32_t chunk_wgs(uint32_t mask) { return mask == kRowsOne ? 20u : mask == kRowsAll ? 4u : 32u; }
+constexpr uint32_t kChunkWGs = 8192;
+constexpr uint32_t kMidResident = 4;      // resident workgroups per CU
 constexpr double kChunkFixedRows = 3.0;   // what a wave's start costs, in rows
 constexpr double kChunkFixedSteps = 0.5;  // and in steps of four short rows
 constexpr double kFullRound = 0.8;
 constexpr uint32_t kFewRows = 64;
-__host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, uint64_t num_samples, uint32_t mask) {
+__host__ inline uint32_t row_pass_chunks(uint32_t num_cus, uint32_t num_series, uint32_t max_K, uint64_t num_samples,
+                                         uint32_t mask) {
   const uint64_t max_rows = (uint64_t)num_series * max_K;
   const uint32_t least = max_rows <= kCoopRows ? 1u : (uint32_t)row_pass_threads(mask) / kWave;
   const uint32_t most = min((max_K + least - 1) / least, kRowPassChunks);
-  uint32_t c = chunk_wgs(mask) / num_series;
+  uint32_t c = min(chunk_wgs(mask) * num_cus, kChunkWGs) / num_series;
   c = c < most ? c : most;
   c = c ? c : 1u;
   if (mask != kRowsMid) return c;
@@ -1358,7 +1360,7 @@ __host__ inline uint32_t row_pass_chunks(uint32_t num_series, uint32_t max_K, ui
   uint32_t best = 1;
   double cost = 1e300;
   for (uint32_t q = 1; q <= c; ++q) {
-    const double fill = (double)num_series * q / kMidResident;
+    const double fill = (double)num_series * q / (kMidResident * num_cus);
     const double rounds = ceil(fill) + (q == 1 && fill < kFullRound ? (kFullRound - fill) / 2 : 0.0);
     const uint32_t rows = ((max_K + q - 1) / q + least - 1) / least;  // of a wave
     const double t = rounds * (short_rows ? (rows + kGroupRows - 1) / kGroupRows + kChunkFixedSteps : rows + kChunkFixedRows);

@@ -30,7 +30,7 @@
 
 namespace ks {
 
-constexpr uint32_t kSplitWGs = 2048;  // eight workgroups per CU stream the rows
+constexpr uint32_t kSplitWGs = 8;  // workgroups per CU stream the rows
 constexpr uint32_t kSplitNT = 256;
 constexpr uint32_t kSplitWalkNT = 512;
 constexpr uint32_t kSplitSlots = KS_MAX_K / kWave;  // 64-candidate slots of a series
@@ -185,10 +185,10 @@ __global__ __launch_bounds__(kSplitNT) void split_moments_kernel(const uint32_t*
 }
 
 // out: where series of a bad shape or range are flagged (nullable).
-inline void launch_split_moments(const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,
+inline void launch_split_moments(uint32_t num_cus, const uint32_t* samples, uint64_t num_samples, const ks_desc* desc,
                                  uint32_t num_series, uint32_t max_K, ks_result* out, const SplitWs& ws,
                                  hipStream_t st) {
-  const uint32_t chunks = (kSplitWGs + num_series - 1) / num_series;
+  const uint32_t chunks = (kSplitWGs * num_cus + num_series - 1) / num_series;
   hipLaunchKernelGGL(split_moments_kernel, dim3(chunks < max_K ? chunks : max_K, num_series), dim3(kSplitNT), 0, st,
                      samples, num_samples, desc, max_K, out, ws);
 }

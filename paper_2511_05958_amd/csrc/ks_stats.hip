@@ -154,7 +154,7 @@ extern "C" int ks_stats_batch(ks_ctx* ctx, const uint32_t* samples, uint64_t num
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t st = (hipStream_t)stream;
   auto launch = [&](auto kernel, uint32_t mask, const uint32_t* plan) {
-    const uint32_t C = ks::row_pass_chunks(num_series, max_K, num_samples, mask);
+    const uint32_t C = ks::row_pass_chunks((uint32_t)ctx->num_cus, num_series, max_K, num_samples, mask);
     hipLaunchKernelGGL(kernel, dim3(num_series * C), dim3(ks::row_pass_threads(mask)), 0, st, samples, num_samples, desc,
                        num_series, max_K, out, out_rows, plan, C);
   };
