@@ -324,17 +324,51 @@ struct RankSmem {
   uint32_t partU[NT], bestU[W], bestC[W], red[W];
 };
 
-// Ranks of K > kRankBlock keys: counted within blocks of kRankBlock keys, which
-// are then in order in LDS, and searched for in every other block (2048 keys: 256
-// compares and 63 reads a key in place of 2048 compares; with the masked walk a
-// segmentation's window of 2048 rows takes 220 us alone on its CU, 603 before).
-// Leaves keys, is and pos in order.
 constexpr uint32_t kRankBlock = 256;
-template <int KMAX, int NT>
-__device__ __forceinline__ void rank_blocks(RankSmem<KMAX, NT>& sm, const SortKey (&mine)[(KMAX + NT - 1) / NT],
-                                            uint32_t K, bool wide) {
+
+// Ends of the groups of equal Q to sm.tie, where sorted position p's key is at
+// at(p); whether some two are equal.
+template <int KMAX, int NT, class At>
+__device__ __forceinline__ bool group_ends(RankSmem<KMAX, NT>& sm, uint32_t K, uint32_t w, At&& at) {
+  const uint32_t lane = lane_id();
+  bool tied = false;
+  for (uint32_t p0 = w * kWave; p0 < K; p0 += NT) {
+    const uint32_t p = p0 + lane;
+    bool end = false;
+    if (p < K) {
+      const uint32_t i = at(p), j = at(min(p + 1, K - 1));
+      end = p + 1 == K || group_end(SortKey{sm.lo[i], sm.hi[i]}, SortKey{sm.lo[j], sm.hi[j]});
+    }
+    const uint64_t m = ballot(end);
+    if (lane == 0) sm.tie[p0 / kWave] = m;
+    tied |= m != ballot(p < K);
+  }
+  return block_any<NT>(tied, sm.red);
+}
+
+// Order of K > kRankBlock keys: ranks are counted within blocks of kRankBlock keys,
+// which are then in order in LDS, and searched for in every other block (2048
+// keys: 256 compares and 63 reads a key in place of 2048 compares; with the masked
+// walk a segmentation's window of 2048 rows takes 220 us alone on its CU, 603
+// before). Leaves keys, is and pos in order; whether some two Q are equal.
+template <int KMAX, int NT, class Key>
+__device__ __forceinline__ bool order_blocks(RankSmem<KMAX, NT>& sm, Key&& key, uint32_t K, uint32_t w) {
   constexpr int E = (KMAX + NT - 1) / NT;
-  const uint32_t tid = threadIdx.x, w0 = wave_id() * kWave;
+  const uint32_t tid = threadIdx.x, w0 = w * kWave;
+  bool w53 = false;
+  SortKey mine[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t i = tid + e * NT;
+    mine[e] = SortKey{0, 0};
+    if (i < K) {
+      mine[e] = key(i);
+      sm.lo[i] = mine[e].lo;
+      sm.hi[i] = mine[e].hi;
+      w53 |= mine[e].hi != 0;
+    }
+  }
+  const bool wide = block_any<NT>(w53, sm.red);
   uint32_t rank[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -382,6 +416,39 @@ __device__ __forceinline__ void rank_blocks(RankSmem<KMAX, NT>& sm, const SortKe
     }
   }
   __syncthreads();
+  return group_ends(sm, K, w, [](uint32_t p) { return p; });
+}
+
+// The same for fewer keys, every rank one count over all of them; the keys stay in
+// row order.
+template <int KMAX, int NT, class Key>
+__device__ __forceinline__ bool order_counts(RankSmem<KMAX, NT>& sm, Key&& key, uint32_t K, uint32_t w) {
+  const uint32_t tid = threadIdx.x;
+  bool w53 = false;
+  for (uint32_t i = tid; i < K; i += NT) {
+    const SortKey k = key(i);
+    sm.lo[i] = k.lo;
+    sm.hi[i] = k.hi;
+    sm.rank[i] = 0;
+    w53 |= k.hi != 0;
+  }
+  const bool wide = block_any<NT>(w53, sm.red);
+  {  // several threads count for one row where there are fewer rows than threads
+    const uint32_t KR = min((K + kWave - 1u) & ~(uint32_t)(kWave - 1), (uint32_t)NT), P = NT / KR;
+    const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
+    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
+    if (q < P)
+      for (uint32_t i = i0; i < K; i += KR)
+        atomicAdd(&sm.rank[i], count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < K; i += NT) {
+    const uint32_t p = sm.rank[i];
+    sm.is[p] = (uint16_t)i;
+    sm.pos[i] = (uint16_t)p;
+  }
+  __syncthreads();
+  return group_ends(sm, K, w, [&](uint32_t p) { return (uint32_t)sm.is[p]; });
 }
 
 // key(i): row i's key (i < K). Candidates c_lo .. c_hi; their statistics to
@@ -390,55 +457,10 @@ template <int KMAX, int NT, class Key>
 __device__ __forceinline__ void rank_walk(RankSmem<KMAX, NT>& sm, Key&& key, uint32_t K, uint32_t c_lo, uint32_t c_hi,
                                           uint32_t* __restrict__ allU, uint32_t& bU, uint32_t& bC) {
   constexpr uint32_t W = NT / kWave;
-  constexpr int E = (KMAX + NT - 1) / NT;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = wave_id();
-  bool w53 = false;
-  SortKey mine[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const uint32_t i = tid + e * NT;
-    mine[e] = SortKey{0, 0};
-    if (i < K) {
-      mine[e] = key(i);
-      sm.lo[i] = mine[e].lo;
-      sm.hi[i] = mine[e].hi;
-      if (K <= kRankBlock) sm.rank[i] = 0;
-      w53 |= mine[e].hi != 0;
-    }
-  }
-  const bool wide = block_any<NT>(w53, sm.red);
-  const bool blocks = KMAX > (int)kRankBlock && K > kRankBlock;
-  if (blocks) {
-    if constexpr (KMAX > (int)kRankBlock) rank_blocks<KMAX, NT>(sm, mine, K, wide);
-  } else {  // several threads count for one row where there are fewer rows than threads
-    const uint32_t KR = min((K + kWave - 1u) & ~(uint32_t)(kWave - 1), (uint32_t)NT), P = NT / KR;
-    const uint32_t i0 = tid % KR, q = tid / KR, len = (K + P - 1) / P;
-    const uint32_t j0 = min(K, q * len), j1 = min(K, j0 + len);
-    if (q < P)
-      for (uint32_t i = i0; i < K; i += KR)
-        atomicAdd(&sm.rank[i], count_below(sm.lo, sm.hi, j0, j1, sm.lo[i], sm.hi[i], wide));
-    __syncthreads();
-    for (uint32_t i = tid; i < K; i += NT) {
-      const uint32_t p = sm.rank[i];
-      sm.is[p] = (uint16_t)i;
-      sm.pos[i] = (uint16_t)p;
-    }
-    __syncthreads();
-  }
-  bool tied = false;
-  for (uint32_t p0 = w * kWave; p0 < K; p0 += NT) {
-    const uint32_t p = p0 + lane;
-    bool end = false;
-    if (p < K) {
-      const uint32_t q = min(p + 1, K - 1);
-      const uint32_t i = blocks ? p : sm.is[p], j = blocks ? q : sm.is[q];
-      end = p + 1 == K || group_end(SortKey{sm.lo[i], sm.hi[i]}, SortKey{sm.lo[j], sm.hi[j]});
-    }
-    const uint64_t m = ballot(end);
-    if (lane == 0) sm.tie[p0 / kWave] = m;
-    tied |= m != ballot(p < K);
-  }
-  const bool ties = block_any<NT>(tied, sm.red);
+  bool ties;
+  if (KMAX > (int)kRankBlock && K > kRankBlock) ties = order_blocks<KMAX, NT>(sm, key, K, w);
+  else ties = order_counts<KMAX, NT>(sm, key, K, w);
   // 64-candidate slots: the waves of a slot share the positions (shares of a
   // multiple of 8), or a wave walks its slots one after the other
   const uint32_t ns = (c_hi - c_lo + kWave) / kWave;
