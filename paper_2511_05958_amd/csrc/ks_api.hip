@@ -336,20 +336,26 @@ LaunchCfg recorded(const ks_ctx* c, int kc, uint32_t num_series) {
 
 // What a batch runs under the default plan: the scan of few series, or the ordered
 // grid with the kernel variant by size and a direct launch (a graph's update costs
-// more on the host than the second kernel's launch: 1024 series of 64 x 64 34 us a
-// call from a graph, 25 direct). Variant 2, eight waves per series instead of four, for K
-// classes of 1024 and 2048 rows, whose LDS allows as many workgroups either way
-// (1024 series of 2048 x 64 1698 us with four, 1050 with eight; 4096 of 1024 x
-// 256 1731 and 1575), and for 512-row classes with series of more than 640 KB on
-// average, where the largest ones' stream decides (8192 uneven ones up to 512 x
-// 4096 1056 and 997; below, its barriers cost: 8192 of 512 x 256 1022 and 1130).
+// more on the host than the second kernel's launch: 1100 series of 64 x 64 30
+// us a call from a graph, 24 direct). Variant 2, eight waves per series instead of
+// four, for K classes of 1024 and 2048 rows, whose LDS allows as many workgroups
+// either way (1024 series of 2048 x 64 1702 us with four, 1137 with eight; 4096 of
+// 1024 x 256 1722 and 1507), and in the 512-row class for series of more than 640 KB
+// on average up to 40 of them per CU, where a wait for the largest ones' stream is
+// left at the end: 4096 uneven ones up to 512 x 4096 755 us with four waves, 530
+// with eight, 8192 of them 1010 and 951; 16384 1807 and 1876, as there is always
+// another series to hide it. Of smaller equal series the barriers cost more: 8192
+// of 512 x 256 972 and 1033, of 512 x 384 1257 and 1259, of 512 x 512 1512 and 1459
+// (variant 5, two walk slots, is within 1% of variant 0 in all of these).
 // Smaller classes have waves enough: 4096 of 256 x 1024 take 668 and 671. From 2^23
 // series on a grid of 2^32 - 1 threads does not hold them with eight waves each.
 LaunchCfg default_cfg(const ks_ctx* c, int kc, const ScanArgs& a) {
   LaunchCfg cfg;
   cfg.graph = 0;
   cfg.spread = a.num_series <= split_max_series(c) || tiny_batch(c, kc, a);
-  const bool long_series = kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && a.num_samples / a.num_series > (160u << 10));
+  const bool few = a.num_series <= 40u * (uint32_t)c->num_cus;
+  const bool long_series =
+      kKClass[kc] >= 1024 || (kKClass[kc] >= 512 && few && a.num_samples / a.num_series > (160u << 10));
   if (long_series && a.num_series < (1u << 23)) cfg.variant = 2;
   return cfg;
 }

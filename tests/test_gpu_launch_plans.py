@@ -123,3 +123,16 @@ def test_no_graph_option_changes_no_kernel(ctx, num, K, N):
     assert Batch(num, K, N, opts=P.KS_OPT_NO_GRAPH).kernels(ctx) == Batch(num, K, N).kernels(ctx)
     P.ks_launch_set(ctx.handle, K, num, P.KS_LAUNCH_ORDERED, 1 << 20, 1, variant=1)
     assert Batch(num, K, N, opts=P.KS_OPT_NO_GRAPH).kernels(ctx) == ordered(num, 1)
+
+
+@pytest.mark.parametrize("num,N,threads", [(600, 300, 256), (600, 321, 512), (10240, 321, 512), (10241, 321, 256)])
+def test_default_variant_of_512_row_series(ctx, num, N, threads):
+    """Eight waves per series above 160 Ki samples on average, in batches of up to 40 series per CU (of 256); the
+    descriptors share one series' samples, num_samples counts as in a batch that does not."""
+    import torch
+
+    b = Batch(1, 512, N)
+    d = P.to_device(P.make_desc(np.zeros(num, np.int64), [512] * num, [N] * num, np.zeros(num, np.int64)))
+    b.n, b.desc, b.out = num, d, P.empty_results(num)
+    b.samples = torch.randint(100, 400, (num * 512 * N,), dtype=torch.int32, device="cuda")
+    assert b.kernels(ctx) == [((1, 1), 1024), ((num, 1), threads)]
