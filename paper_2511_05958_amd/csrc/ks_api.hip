@@ -603,9 +603,10 @@ int ks_autotune(ks_ctx* ctx, const uint32_t* samples, uint64_t num_samples, cons
     }
     for (int i = 0; i < np && rc == KS_OK; ++i) {
       float t = 0.f;
-      rc = time_cfg(is_default(plans[i]) ? default_cfg(ctx, kc, a) : plans[i], t);
+      const LaunchCfg run = is_default(plans[i]) ? default_cfg(ctx, kc, a) : plans[i];
+      rc = time_cfg(run, t);
       if (rc == KS_OK && (!have || t < bms)) {
-        bcfg = plans[i];
+        bcfg = run.spread ? plans[i] : run;  // the scan of few series has no record but the default
         bms = t;
         have = true;
       }
