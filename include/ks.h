@@ -369,7 +369,8 @@ int ks_cnn_backward(ks_ctx *ctx, const ks_model *model, const float *features, u
                     uint64_t dlogit_rows, float *grads, void *stream);
 
 /* The network's intermediate values, for checking each layer on its own
- * inputs: the training step's forward pass (one kernel per layer) on caller
+ * inputs: the training step's forward pass (the fused kernel, its activations
+ * kept) on caller
  * features and, when labels or dlogits is given, its backward pass.
  *   labels     device int32[num_series], nullable: when given, the logit
  *              gradient is the training step's (softmax cross-entropy, label

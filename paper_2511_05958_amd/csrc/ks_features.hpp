@@ -31,8 +31,8 @@ struct LearnWs {
 // pass and made its time depend on where the buffers lay in memory). Rows of
 // two or more load batches stage 64 rows (fewer, longer write bursts among
 // the reads: the learned step on 8192 x 1024 x 2048 ran 1 - 4% faster than
-// with 16); one-batch and short rows stage 16, which keeps their LDS within
-// six workgroups per CU.
+// with 16), one-batch and short rows 16; a kernel's LDS is for the largest of
+// its classes.
 // (at most 64: a flush writes one row's moments per lane)
 __host__ __device__ constexpr uint32_t feat_stage_rows(int NB) { return NB == 1 || NB == (int)kGrouped ? 16u : 64u; }
 

@@ -86,9 +86,10 @@ __device__ __forceinline__ uint32_t row_pass_series(const uint32_t* __restrict__
 
 // Batches of up to this many series skip the plan and take one launch for all
 // row classes: their workgroups are chunks of series, small enough that the
-// order does not matter, and the plan and two more launches cost 13 us. (At 64
-// series of 256 x 1024 the one launch takes 32 us, the plan and the three 27:
-// all classes' registers leave it half of the waves.)
+// order does not matter, and the plan and a second launch cost 5 us (statistics of
+// 16 series of 256 x 257 8 us, of 17 13). (At 64 series of 256 x 1024 the one launch
+// takes 32 us, the plan and the two 27: all classes' registers leave it half of the
+// waves.)
 constexpr uint32_t kRowPassOneLaunch = 16;
 
 }  // namespace

@@ -1,5 +1,5 @@
 // Binary segmentation over a batch: every level boundary of each series, in one
-// launch with one workgroup per series.
+// launch with one workgroup per series (more than 2^21 in several).
 //
 // The row moments (sum r, sum r^2) and minima of a series are kept in LDS. A
 // window [a, b) of rows is a series of its own, but its eq. 2 keys need only its
@@ -13,7 +13,7 @@
 // read-back of the window counts every few depths and a sort at the end took 14
 // depths x 10 - 25 us after a root pass of 107 us on 512 series of 256 rows of
 // 1024 samples, 333 us a call, most depths with a handful of windows; the call
-// takes 148 us now, of which the rows' stream is about 95.)
+// takes 145 us now, of which the rows' stream is about 95.)
 //
 // A workgroup streams its own series' rows when there are enough series to keep
 // HBM busy that way; with fewer, split_moments_kernel has spread the rows over

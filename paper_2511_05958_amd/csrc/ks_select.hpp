@@ -61,7 +61,7 @@ struct __align__(16) SelLds {
 
 // The row pass's share of LDS per wave: the window, which stream_select's
 // levels reuse (later digits of kSelWs bits, so that nine groups' bins fit),
-// and the groups' prefixes. 4.2 KiB, so that eight waves per SIMD fit.
+// and the groups' prefixes. 4.2 KiB.
 constexpr uint32_t kSelWs = 6;
 struct __align__(16) RowLds {
   uint32_t hist[kSelWin];
@@ -1301,7 +1301,10 @@ __device__ __forceinline__ void select_rows_grouped(RowLds& L, const uint32_t* _
 constexpr uint32_t kRowsOne = 1u, kRowsMid = 2u | 4u | 8u, kRowsAll = 15u;
 __host__ __device__ constexpr int row_pass_threads(uint32_t mask) { return mask == kRowsAll ? 512 : 256; }
 // Waves per SIMD the row-pass kernels are compiled for, the largest that spill
-// no more than one register (the feature pass' kernels of several classes).
+// no more than one vector register (the feature pass' kernels of several classes).
+// The scalar spills of such a kernel, 240, are the sum of its classes', 19 to 78
+// each, as each class is code of its own; without the cooperative rows it spills
+// 204 and no vector register, in the same time within 1%.
 __host__ __device__ constexpr int row_pass_waves(uint32_t mask) { return mask == kRowsOne ? 5 : 4; }
 __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
   return N <= kGroupMaxN ? kGrouped
@@ -1312,7 +1315,7 @@ __host__ __device__ constexpr uint32_t feat_batches(uint32_t N) {
 
 // Split of the row passes over workgroups. A series' rows are cut into C chunks,
 // one workgroup each, so that a batch of few series still fills the chip: the
-// statistics of 8 series of 64 rows of 65537 samples take 41 us (3.3 TB/s) so
+// statistics of 8 series of 64 rows of 65537 samples take 39 us (3.4 TB/s) so
 // split, 1440 us with a workgroup per series; of 8 x 256 rows of 1024 samples 12
 // us against 145, of 256 x 512 rows of 256 samples (four waves per CU unsplit) 60
 // us against 246. A launch is cut to kChunkWGs workgroups at most, since a wave's
