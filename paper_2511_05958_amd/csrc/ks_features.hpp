@@ -108,7 +108,7 @@ __global__ __launch_bounds__(row_pass_threads(MASK)) __attribute__((amdgpu_waves
   const bool bad = check_desc(d, num_samples, max_K) || d.N > KS_FEATURE_MAX_N;
   const uint32_t nb = bad ? 1u : feat_batches(d.N);
   if (!((MASK >> feat_class_index(nb)) & 1u)) return;
-  if (bad) {  // the pack step zeroes its network input rows
+  if (bad) {  // no rows to pack
     if (tid == 0 && c == 0) lw.K[s] = 0;
     return;
   }
