@@ -213,10 +213,10 @@ int ks_launch_get(ks_ctx *ctx, uint32_t max_K, uint32_t num_series, ks_launch *c
 /* Autotuner, on this very batch with HIP events on `stream` (one warm-up,
  * best of three per candidate): every scan-kernel variant (tile, sort radix,
  * walk window) under every launch plan (grid; ordered grid from a hipGraph,
- * variant 0 of which is the default plan, and direct; persistent with chunk_bytes 1, 4, 16 MiB, from a hipGraph and
- * direct), 6 x 9 candidates. Records the fastest
- * with ks_launch_set and returns it in *best (nullable) and its time in
- * *best_ms (nullable). Blocks until done; writes `out`. When the environment
+ * variant 0 of which is the default plan, and direct; persistent with
+ * chunk_bytes 1, 4, 16 MiB, from a hipGraph and direct), 6 x 9 candidates.
+ * Records the fastest with ks_launch_set and returns it in *best (nullable)
+ * and its time in *best_ms (nullable). Blocks until done; writes `out`. When the environment
  * variable KS_TUNE_CACHE names a file, the choice is appended to it, and
  * ks_ctx_create loads the records written for the same device (architecture
  * and CU count). Arguments as ks_scan_batch. */
