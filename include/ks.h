@@ -143,8 +143,9 @@ int ks_ctx_destroy(ks_ctx *ctx);
 /* Pre-allocate workspace for batches of up to max_series series and
  * max_total_steps total rows, so that later calls of that size allocate
  * nothing. Optional; calls grow the workspace on demand otherwise. (The scan of
- * few series has up to 31 MB of its own; where they cannot be had, or under
- * capture, ks_scan_batch runs the ordered plan's two kernels instead.) */
+ * few series has 31 MB of its own, taken once; where they cannot be had, or under
+ * capture before that, ks_scan_batch runs the ordered plan's two kernels
+ * instead.) */
 int ks_reserve(ks_ctx *ctx, uint32_t max_series, uint64_t max_total_steps);
 
 /* Exact scan of a batch (eq. 2 reduction, K-S at every candidate, choice,

@@ -123,25 +123,19 @@ void free_split(ks_ctx* c) {
   c->split_sorted = nullptr;
   c->split_best = nullptr;
   c->split_ticket = nullptr;
-  c->cap_split_series = c->cap_split_rows = 0;
 }
 
-// Grow the spread scan's workspace to num_series series of max_K rows, 40 B each.
-// KS_E_NOMEM also where `st` is being captured and the workspace would have to
-// grow: the caller runs the ordered grid then.
-int ensure_split(ks_ctx* c, uint64_t num_series, uint64_t max_K, hipStream_t st) {
-  uint64_t ns = num_series, rows = num_series * max_K;
-  if (ns <= c->cap_split_series && rows <= c->cap_split_rows) return KS_OK;
+// The spread scan's workspace, for all that it serves (31 MB) at once: it never
+// moves, and calls that were captured keep theirs. KS_E_NOMEM also where there is
+// none yet and `st` is being captured: the caller runs the ordered grid then.
+int ensure_split(ks_ctx* c, hipStream_t st) {
+  if (c->split_ticket) return KS_OK;
+  const uint64_t ns = split_max_series(c), rows = ns * KS_MAX_K;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     return KS_E_NOMEM;
   }
-  if (ns < c->cap_split_series) ns = c->cap_split_series;
-  if (rows < c->cap_split_rows) rows = c->cap_split_rows;
-  hipError_t e = hipDeviceSynchronize();
-  if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-  free_split(c);
   if (hipMalloc(&c->split_mom, sizeof(ks::RowMom) * rows) != hipSuccess ||
       hipMalloc(&c->split_sorted, sizeof(ks::SortKey) * rows) != hipSuccess ||
       hipMalloc(&c->split_best, sizeof(uint32_t) * 2 * ns * ks::kSplitSlots) != hipSuccess ||
@@ -150,8 +144,6 @@ int ensure_split(ks_ctx* c, uint64_t num_series, uint64_t max_K, hipStream_t st)
     (void)hipGetLastError();
     return KS_E_NOMEM;
   }
-  c->cap_split_series = ns;
-  c->cap_split_rows = rows;
   return KS_OK;
 }
 
@@ -296,7 +288,7 @@ bool tiny_batch(const ks_ctx* c, int kc, const ScanArgs& a) {
 }
 
 // The scan of a batch of few series (KS_E_NOMEM, nothing launched, where its
-// workspace cannot grow). Launched directly: replaying one or three
+// workspace cannot be had). Launched directly: replaying one or three
 // kernels from a graph costs more on the host (27 us a call for one sweep,
 // against 8).
 int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
@@ -311,7 +303,7 @@ int launch_split(ks_ctx* c, int kc, const ScanArgs& a, hipStream_t st) {
       default: run(ks::tiny_scan_kernel<256>);
     }
   } else {
-    if (int rc = ensure_split(c, a.num_series, a.max_K, st)) return rc;
+    if (int rc = ensure_split(c, st)) return rc;
     const ks::SplitWs ws{c->split_mom, c->split_sorted, c->split_best, c->split_ticket};
     ks::launch_split_moments((uint32_t)c->num_cus, a.samples, a.num_samples, a.desc, a.num_series, a.max_K, a.out, ws, st);
     hipLaunchKernelGGL(ks::split_rank_kernel, ks::split_grid(a.num_series, a.max_K), dim3(ks::kSplitNT), 0, st,
@@ -514,8 +506,7 @@ int ks_reserve(ks_ctx* ctx, uint32_t max_series, uint64_t max_total_steps) {
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   if (int rc = ensure_workspace(ctx, max_series, max_total_steps)) return rc;
   // and the scan of few series, which does without where the device is full
-  const uint32_t most = split_max_series(ctx), few = max_series < most ? max_series : most;
-  const int rc = few ? ensure_split(ctx, few, KS_MAX_K, nullptr) : KS_OK;
+  const int rc = max_series ? ensure_split(ctx, nullptr) : KS_OK;
   return rc == KS_E_NOMEM ? KS_OK : rc;
 }
 

@@ -155,7 +155,7 @@ struct ks_ctx {
   ks::SortKey* split_sorted = nullptr;
   uint32_t* split_best = nullptr;
   uint32_t* split_ticket = nullptr;
-  uint64_t cap_series = 0, cap_rows = 0, cap_split_series = 0, cap_split_rows = 0;
+  uint64_t cap_series = 0, cap_rows = 0;
   std::map<std::tuple<int, int, int, uint32_t>, ks_host::GraphEntry> graphs;  // (mode, K class, variant, grid)
   std::map<std::tuple<int, uint32_t>, ks_host::LaunchCfg> tuned;         // (K class, num_series)
   ks_host::LearnBuffers learn;

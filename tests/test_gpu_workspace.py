@@ -1,6 +1,5 @@
 """What calls allocate: the scan of few series has a workspace of its own, taken
-by the calls that run it and by ks_reserve; where it cannot grow the ordered grid
-runs.
+by the first call that runs it and by ks_reserve; without it the ordered grid runs.
 """
 
 import numpy as np
@@ -57,3 +56,25 @@ def test_captured_scan_without_its_workspace_runs_the_ordered_grid(ctx):
     spread = b.kernels(ctx)
     assert len(spread) == 3
     assert captured(lambda st: b.scan(ctx, st)) == spread
+
+
+@pytest.mark.parametrize("n", [1, 57, 384])
+def test_workspace_of_the_scan_does_not_move(ctx, n):
+    import torch
+
+    small, large = Batch(n, 300, 5), Batch(384, 2048, 2)
+    small.scan(ctx)
+    want = small.out.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        small.scan(ctx, torch.cuda.current_stream().cuda_stream)
+    g.replay()
+    before = _free()
+    large.scan(ctx)
+    assert _free() == before
+    for _ in range(3):
+        small.out.zero_()
+        g.replay()
+        large.scan(ctx)
+        torch.cuda.synchronize()
+        assert torch.equal(small.out, want)
